@@ -3,7 +3,7 @@
 //
 // Table: open addressing over a power-of-two number of slots, keys claimed
 // with a 64-bit compare-and-swap (INT64_MIN marks an empty slot; the key
-// INT64_MIN itself lives in one extra slot), linear probing bounded by the
+// INT64_MIN itself lives in one extra slot), double hashing bounded by the
 // table size -- no thread ever waits on another.  Rows are first aggregated
 // into a workgroup's own table in LDS (a few probes per row; a row whose key
 // finds no LDS slot goes straight to the global table) and each LDS table is
@@ -112,7 +112,8 @@ struct Table {
   int64_t* dig;        // float SUM: kDigits per slot
   int32_t* flags;      // float SUM: 1 NaN, 2 +Inf, 4 -Inf seen
   int32_t* state;      // [0] slot cap used, [1] overflow, [2..3] emitted count (uint64)
-  int64_t cap;
+  int64_t cap;         // slots, a power of two >= 64
+  int32_t cap_log2;
 };
 
 // Radix partitioning of one chunk of rows.
@@ -146,52 +147,32 @@ constexpr int64_t val_identity() {
   return (G == G_MIN_INT || G == G_MIN_F32) ? INT64_MAX : (G == G_MAX_INT || G == G_MAX_F32) ? INT64_MIN : 0;
 }
 
-__device__ __forceinline__ uint64_t mix64(uint64_t k) {  // MurmurHash3's 64-bit finaliser
-  k ^= k >> 33;
-  k *= 0xFF51AFD7ED558CCDull;
-  k ^= k >> 33;
-  k *= 0xC4CEB9FE1A85EC53ull;
-  k ^= k >> 33;
-  return k;
-}
-
 __device__ __forceinline__ int64_t ceil_div_dev(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// The hash of a key that places it in LDS tables and partitions.  int64
-// keys: the 64-bit finaliser above.  int32 keys: one 32 x 64-bit multiply by
-// an odd constant (2^64 / golden ratio) and a fold of the high half into the
-// low one -- two quarter-rate multiplies instead of the finaliser's eight,
-// and a bijection on the 32-bit keys; the top bits (partitions, passes) come
-// from the product's high half, the low bits (slots) mix both halves, and
-// bits 32.. give the probe step.
+// The hash of a key: one 32-bit multiply by 2^32 / golden ratio (int64 keys
+// add the high word times a second odd constant, the fraction of sqrt 2).
+// Everything that places a key reads bits from the top of it downwards: its
+// partition, then its sub-partition pass, then its LDS slot, and its home in
+// the global table.  Dictionary codes and surrogate keys, which run densely,
+// then spread evenly by themselves (the multiples of the golden ratio mod 1),
+// so a wave's 64 first probes nearly all hit, and the slots of a workgroup's
+// table lie in the order of their homes in the global table, which a flush
+// walks almost sequentially.  Two quarter-rate multiplies (one for int32
+// keys) against the eight of a 64-bit finaliser: an LDS fold is bound by its
+// instructions, not by its bytes.
 template <int KD>
-__device__ __forceinline__ uint64_t key_hash(int64_t k) {
-  if constexpr (KD == AGG_I32) {
-    const uint64_t p = (uint64_t)(uint32_t)k * 0x9E3779B97F4A7C15ull;
-    return p ^ (p >> 32);
-  } else {
-    return mix64((uint64_t)k);
-  }
+__device__ __forceinline__ uint32_t key_hash(typename std::conditional<KD == AGG_I32, int32_t, int64_t>::type k) {
+  const uint32_t lo = (uint32_t)k * 0x9638806Du;
+  if constexpr (KD == AGG_I32) return lo;
+  else return lo + (uint32_t)((uint64_t)k >> 32) * 0x69C77F93u;
 }
 
-// Partition of a key: the top bits of its hash (table slots use the low bits).
-template <int KD>
-__device__ __forceinline__ uint32_t part_of(int64_t k, int bits) {
-  return (uint32_t)(key_hash<KD>(k) >> (64 - bits));
-}
+// The odd step of a key's further probes (double hashing: keys that share a
+// home part ways).  Only a probe that misses its home computes it.
+__device__ __forceinline__ uint32_t probe_step(uint32_t h) { return ((h * 0x85EBCA6Bu) >> 15) | 1u; }
 
-// The hash placing a key in a few-groups table (at most 256 slots, a single pass):
-// one 32-bit multiply by 2^32 / golden ratio instead of key_hash's wider
-// product.  Bits 24..31 pick the slot, bits 16..23 the probe step (the
-// table reads the slot from the low half and the step from the high half).
-// Where a key lands never shows in a result: only the probe count changes.
-template <int KD>
-__device__ __forceinline__ uint64_t few_hash(int64_t k) {
-  uint32_t x = (uint32_t)k;
-  if constexpr (KD != AGG_I32) x ^= (uint32_t)((uint64_t)k >> 32);
-  const uint32_t h = x * 0x9E3779B1u;
-  return ((uint64_t)(h >> 16) << 32) | (h >> 24);
-}
+// Partition of a key: the top bits of its hash.
+__device__ __forceinline__ uint32_t part_of(uint32_t h, int bits) { return h >> (32 - bits); }
 
 // 7 * x for x < 2^24 as one full-rate 24-bit multiply (left to itself the
 // compiler issues a quarter-rate 32-bit one for the float-sum slot's digit
@@ -295,15 +276,17 @@ __device__ __forceinline__ void apply(CT* cnt, int64_t* val, int64_t* dig, int32
   }
 }
 
-// The global slot of key k, claiming an empty one; -1 when the table is full.
-__device__ __forceinline__ int64_t global_slot(const Table& t, int64_t k) {
+// The global slot of key k with hash h, claiming an empty one; -1 when the
+// table is full.  The home is the top bits of the hash (see key_hash).
+__device__ __forceinline__ int64_t global_slot(const Table& t, int64_t k, uint32_t h) {
   if (k == kEmpty) {
     t.state[0] = 1;
     return t.cap;
   }
   const uint64_t mask = (uint64_t)t.cap - 1;
-  uint64_t s = mix64((uint64_t)k) & mask;
-  for (int64_t p = 0; p < t.cap; ++p, s = (s + 1) & mask) {
+  uint64_t s = t.cap_log2 <= 32 ? (uint64_t)(h >> (32 - t.cap_log2)) : (uint64_t)h << (t.cap_log2 - 32);
+  const uint64_t step = probe_step(h);
+  for (int64_t p = 0; p < t.cap; ++p, s = (s + step) & mask) {
     const int64_t cur = t.key[s];
     if (cur == k) return (int64_t)s;
     if (cur == kEmpty) {
@@ -346,7 +329,7 @@ __global__ void __launch_bounds__(kThreads) gb_hist_kernel(Args a) {
     for (int r = 0; r < kAggRows; ++r) __asm__ volatile("" : "+v"(kk[r]));
 #pragma unroll
     for (int r = 0; r < kAggRows; ++r)
-      if ((uint32_t)(r * kThreads) < left) atomicAdd(&h[part_of<KD>((int64_t)kk[r], a.pt.bits)], 1u);
+      if ((uint32_t)(r * kThreads) < left) atomicAdd(&h[part_of(key_hash<KD>(kk[r]), a.pt.bits)], 1u);
   };
   // two batches alternate, so the next batch's loads are in flight while this
   // one is counted (2^28 rows: 1-3% off the partitioned paths)
@@ -467,7 +450,7 @@ __global__ void __launch_bounds__(kTileThreads) gb_scatter_tiled_kernel(Args a) 
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       if (r * kTileThreads + tid < rows) {
-        pp[r] = part_of<KD>((int64_t)k[r], a.pt.bits);
+        pp[r] = part_of(key_hash<KD>(k[r]), a.pt.bits);
         rank[r] = atomicAdd(&tcnt[pp[r]], 1u);
       }
     }
@@ -504,7 +487,7 @@ __global__ void __launch_bounds__(kTileThreads) gb_scatter_tiled_kernel(Args a) 
     __syncthreads();
     for (int j = tid; j < rows; j += kTileThreads) {
       uint32_t q;
-      if constexpr (HASV) q = part_of<KD>((int64_t)skey[j], a.pt.bits);
+      if constexpr (HASV) q = part_of(key_hash<KD>(skey[j]), a.pt.bits);
       else q = spart[j];
       const uint32_t pos = cur[q] + (uint32_t)j - toff[q];
       if ((int64_t)pos >= a.n) continue;  // cannot happen: counts match the histogram
@@ -532,6 +515,22 @@ __global__ void __launch_bounds__(kTileThreads) gb_scatter_tiled_kernel(Args a) 
 
 // ---- aggregation into LDS tables, flushed into the global table ----
 
+// V consecutive items of a column at base + tid * V, as one vector load (8 or
+// 16 bytes) at any item alignment; non-temporal, since a row is read once.
+template <int V, typename T>
+__device__ __forceinline__ void load_items(T (&x)[V], const T* base, uint32_t tid) {
+  typedef uint32_t vec __attribute__((ext_vector_type(V * sizeof(T) / 4), aligned(4)));
+  static_assert(sizeof(vec) == sizeof(x), "a vector of whole items");
+  const vec v = __builtin_nontemporal_load(reinterpret_cast<const vec*>(base) + tid);
+  __builtin_memcpy(x, &v, sizeof(x));
+}
+
+// 32-bit words of a row's key and value.
+template <int KD, int VD, int G>
+constexpr int row_words() {
+  return (KD == AGG_I64 ? 2 : 1) + (G == G_COUNT ? 0 : VD == AGG_I64 ? 2 : 1);
+}
+
 // One workgroup's table: L hashed slots keyed in the key column's own width
 // (4-byte keys fit twice the slots of 8-byte ones), plus slot L for the one
 // key whose bit pattern marks an empty slot.  Each slot has REP copies of its
@@ -545,11 +544,20 @@ struct LdsTable {
   using UKT = typename std::conditional<KD == AGG_I32, unsigned int, unsigned long long>::type;
   static constexpr KT kMark = std::numeric_limits<KT>::min();  // empty hashed slot
   static constexpr int L = L_;
+  static constexpr int kLog2L = __builtin_ctz((unsigned)L_);
   static constexpr int E = (L + 1) * REP;  // accumulator entries: slot s, copy c at s * REP + c
   static constexpr bool kDig = G == G_SUM_F32;
   static constexpr bool kVal = !kDig && G != G_COUNT;
   static_assert((REP & (REP - 1)) == 0 && REP <= 64, "copies: a power of two, at most a wave");
-  static_assert(REP == 1 || L <= 256, "tables with copies take few_hash's 8 slot bits");
+  static_assert((L & (L - 1)) == 0, "home_of takes log2(L) hash bits");
+  // Rows a thread folds at a time (two batches are in registers: the next
+  // one's loads are in flight): 8, or 4 where a row has four 32-bit words (8
+  // ran 8% slower: spills) or has two and two workgroups share a CU.
+  template <int VD>
+  static constexpr int tile_rows_of() {
+    constexpr int words = row_words<KD, VD, G>();
+    return words >= 4 || (REP > 1 && words == 2) ? 4 : 8;
+  }
   KT key[L];
   uint32_t cnt[E];  // rows per table stay below 2^32 (a workgroup's share is at most 2^28 rows)
   int64_t val[kVal ? E : 1];
@@ -568,98 +576,154 @@ struct LdsTable {
     }
   }
 
-  // The slot holding key k (hash hk), claiming an empty one; -1 if none
-  // within kLdsProbes probes.  Double hashing: an odd step from the hash's
-  // high half, so probe chains do not cluster (a wave waits for its longest
-  // chain).
-  __device__ __forceinline__ int slot_of(KT k, uint64_t hk) {
+  // The home slot of a key with hash h: the log2(L) hash bits below the
+  // `skip` that chose its partition and pass.
+  static __device__ __forceinline__ uint32_t home_of(uint32_t h, uint32_t skip) {
+    return __builtin_amdgcn_ubfe(h, (uint32_t)(32 - kLog2L) - skip, (uint32_t)kLog2L);
+  }
+
+  // The slot of key k where its home, which read `cur`, does not hold it (or
+  // k is the marker key): claims an empty slot, -1 if there is none within
+  // kLdsProbes probes.
+  __device__ __forceinline__ int slot_of(KT k, uint32_t h, uint32_t home, KT cur) {
     if (k == kMark) return L;
-    int h = (int)(hk & (L - 1));
-    const int step = (int)(((hk >> 32) | 1) & (L - 1));
-    for (int p = 0; p < kLdsProbes; ++p, h = (h + step) & (L - 1)) {
-      const KT cur = key[h];
-      if (cur == k) return h;
+    const uint32_t step = probe_step(h);
+    uint32_t s = home;
+    for (int p = 0; p < kLdsProbes; ++p) {
+      if (cur == k) return (int)s;
       if (cur == kMark) {
-        const KT prev = (KT)atomicCAS(reinterpret_cast<UKT*>(&key[h]), (UKT)kMark, (UKT)k);
-        if (prev == kMark || prev == k) return h;
+        const KT prev = (KT)atomicCAS(reinterpret_cast<UKT*>(&key[s]), (UKT)kMark, (UKT)k);
+        if (prev == kMark || prev == k) return (int)s;
       }
+      s = (s + step) & (uint32_t)(L - 1);
+      cur = key[s];
     }
     return -1;
   }
 
-  // Rows first, first + step, ... below last whose key hash has the bits
-  // (hash >> sub_shift) & sub_mask equal to sub; a row whose key finds no
-  // slot within kLdsProbes goes to the global table.
+  // Folds the rows of the tiles first, first + tile_step, ... (kTile rows
+  // each) below last whose key hash has the bits (hash >> sub_shift) &
+  // sub_mask equal to sub; a row whose key finds no slot within kLdsProbes
+  // probes goes to the global table.
   // ROWS: keys holds staged (key, value) records.  SUB: the plan has
   // sub-partition passes (else every row belongs to the single pass and the
-  // per-row test of its hash bits is left out)
-  template <int VD, bool ROWS = false, bool SUB = true>
-  __device__ __forceinline__ void fold_rows(const Table& t, const void* keys, const void* vals, int64_t first, int64_t last,
-                            int64_t step, uint32_t sub_shift, uint32_t sub_mask, uint32_t sub) {
-    constexpr int R = kAggRows;
+  // per-row test of its hash bits is left out).
+  //
+  // Bound by instructions and LDS atomics, so a full tile's rows carry neither
+  // bounds test nor address arithmetic (a uniform base per row and one lane
+  // offset), the next tile's loads are in flight while a tile is folded, and
+  // the first probes of a batch are read before the first of them is
+  // resolved.
+  template <int VD, bool ROWS, bool SUB>
+  __device__ __forceinline__ void fold_rows(const Table& t, const void* keys, const void* vals, int64_t first,
+                                            int64_t last, int64_t tile_step, uint32_t skip, uint32_t sub_shift,
+                                            uint32_t sub_mask, uint32_t sub) {
+    constexpr int R = tile_rows_of<VD>();
+    constexpr int TR = R * NT;
+    constexpr bool kStaged = ROWS && G != G_COUNT;
     using IVT = typename std::conditional<VD == AGG_I64, int64_t, int32_t>::type;
-    struct Batch {  // R rows' key and value registers
-      KT k[R];
-      IVT iv[R];
-      float fv[R];
+    using SR = StagedRow<KD, VD == AGG_I64 ? AGG_I64 : AGG_I32>;
+    struct Row {
+      KT k;
+      IVT iv;
+      float fv;
     };
-    // rows past the end re-load the last row (in bounds, never folded): no
-    // branch around the loads, so all of them issue before the first wait.
-    // The batch's rows are base + r * step: one 64-bit clamp per batch, then
-    // 32-bit offsets (R * step < 2^31), so a row's address costs a min and one
-    // 64-bit add instead of a 64-bit compare, two selects and three adds
-    const uint32_t step32 = (uint32_t)step;
+    struct Batch {  // R rows' registers
+      Row x[R];
+    };
+    const uint32_t tid = threadIdx.x;
+    auto load_row = [&](Row& x, int64_t base, uint32_t lane) {  // row base + lane (base uniform)
+      x.iv = 0;
+      x.fv = 0.0f;
+      if constexpr (ROWS && G != G_COUNT) {
+        const SR row = (static_cast<const SR*>(keys) + base)[lane];
+        if constexpr (SR::KW == 2) x.k = (KT)(((uint64_t)row.w[1] << 32) | row.w[0]);
+        else x.k = (KT)(int32_t)row.w[0];
+        if constexpr (VD == AGG_F32) x.fv = __uint_as_float(row.w[SR::KW]);
+        else if constexpr (VD == AGG_I64) x.iv = (int64_t)(((uint64_t)row.w[SR::KW + 1] << 32) | row.w[SR::KW]);
+        else x.iv = (int32_t)row.w[SR::KW];
+      } else {
+        x.k = (static_cast<const KT*>(keys) + base)[lane];
+        if constexpr (G != G_COUNT) {
+          if constexpr (VD == AGG_F32) x.fv = (static_cast<const float*>(vals) + base)[lane];
+          else x.iv = (static_cast<const IVT*>(vals) + base)[lane];
+        }
+      }
+    };
+    // Row r of a tile sits at row_at(r) from its base.  Rows of a column: a
+    // thread takes V consecutive ones, so that the wider of key and value is
+    // read in 16-byte vectors and every load of a wave is contiguous; staged
+    // records: one every NT, a whole record a load.
+    constexpr int V = KD == AGG_I64 || (G != G_COUNT && VD == AGG_I64) ? 2 : 4;
+    auto row_at = [&](int r) -> uint32_t {
+      if constexpr (kStaged) return (uint32_t)(r * NT) + tid;
+      else return (uint32_t)(r / V * V * NT + r % V) + tid * V;
+    };
     auto load = [&](Batch& b, int64_t base) {
-      const int64_t b0 = std::min<int64_t>(base, last - 1);
-      const uint32_t room = (uint32_t)std::min<int64_t>(last - 1 - b0, (int64_t)R * step);
+      if constexpr (kStaged) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const uint32_t rel = std::min<uint32_t>((uint32_t)r * step32, room);
-        b.iv[r] = 0;
-        b.fv[r] = 0.0f;
-        if constexpr (ROWS && G != G_COUNT) {
-          using SR = StagedRow<KD, VD == AGG_I64 ? AGG_I64 : AGG_I32>;
-          const SR row = (static_cast<const SR*>(keys) + b0)[rel];
-          if constexpr (SR::KW == 2) b.k[r] = (KT)(((uint64_t)row.w[1] << 32) | row.w[0]);
-          else b.k[r] = (KT)(int32_t)row.w[0];
-          if constexpr (VD == AGG_F32) b.fv[r] = __uint_as_float(row.w[SR::KW]);
-          else if constexpr (VD == AGG_I64) b.iv[r] = (int64_t)(((uint64_t)row.w[SR::KW + 1] << 32) | row.w[SR::KW]);
-          else b.iv[r] = (int32_t)row.w[SR::KW];
-        } else {
-          b.k[r] = (static_cast<const KT*>(keys) + b0)[rel];
+        for (int r = 0; r < R; ++r) load_row(b.x[r], base + r * NT, tid);
+      } else {
+#pragma unroll
+        for (int q = 0; q < R; q += V) {
+          KT kk[V];
+          load_items(kk, static_cast<const KT*>(keys) + base + q * NT, tid);
+#pragma unroll
+          for (int c = 0; c < V; ++c) {
+            b.x[q + c].k = kk[c];
+            b.x[q + c].iv = 0;
+            b.x[q + c].fv = 0.0f;
+          }
           if constexpr (G != G_COUNT) {
-            if constexpr (VD == AGG_F32) b.fv[r] = (static_cast<const float*>(vals) + b0)[rel];
-            else b.iv[r] = (static_cast<const IVT*>(vals) + b0)[rel];
+            IVT vv[V];
+            load_items(vv, static_cast<const IVT*>(vals) + base + q * NT, tid);
+#pragma unroll
+            for (int c = 0; c < V; ++c) {
+              if constexpr (VD == AGG_F32) b.x[q + c].fv = __int_as_float(vv[c]);
+              else b.x[q + c].iv = vv[c];
+            }
           }
         }
       }
     };
-    auto fold = [&](Batch& b, int64_t base) {
-      // rows of this batch that exist: r * step < last - base
-      const uint32_t left = (uint32_t)std::max<int64_t>(0, std::min<int64_t>(last - base, (int64_t)R * step));
+    // the last, partial tile: rows past its end re-load its last row (in
+    // bounds, not folded)
+    auto load_tail = [&](Batch& b, int64_t base, uint32_t left) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) load_row(b.x[r], base, std::min<uint32_t>(row_at(r), left - 1));
+    };
+    auto fold = [&](Batch& b, int64_t base, bool full, uint32_t left) {
       // the batch's loads are complete before its first row is folded: left
       // alone, the compiler sinks a value load into the branch that uses it,
       // and that load's whole latency then stalls the wave
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        __asm__ volatile("" : "+v"(b.k[r]));
+        __asm__ volatile("" : "+v"(b.x[r].k));
         if constexpr (G != G_COUNT) {
-          if constexpr (VD == AGG_F32) __asm__ volatile("" : "+v"(b.fv[r]));
-          else __asm__ volatile("" : "+v"(b.iv[r]));
+          if constexpr (VD == AGG_F32) __asm__ volatile("" : "+v"(b.x[r].fv));
+          else __asm__ volatile("" : "+v"(b.x[r].iv));
         }
+      }
+      uint32_t spill = 0;
+      uint32_t home[R];
+      KT cur[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        home[r] = home_of(key_hash<KD>(b.x[r].k), skip);
+        cur[r] = key[home[r]];
       }
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        if ((uint32_t)r * step32 >= left) break;
-        const KT k = b.k[r];
-        const uint64_t hk = REP > 1 ? few_hash<KD>(k) : key_hash<KD>((int64_t)k);
-        if (SUB && ((uint32_t)(hk >> sub_shift) & sub_mask) != sub) continue;  // another pass's row
-        const float fv = b.fv[r];
-        bool in_lds = true;
-        if constexpr (kDig) in_lds = lds_digits_hold(fv);
-        const int slot = in_lds ? slot_of(k, hk) : -1;  // outside the LDS slot's digits: the global table
+        if (!full && row_at(r) >= left) continue;
+        const KT k = b.x[r].k;
+        if (SUB && ((key_hash<KD>(k) >> sub_shift) & sub_mask) != sub) continue;  // another pass's row
+        const float fv = b.x[r].fv;
+        int slot = (int)home[r];
+        if (cur[r] != k || k == kMark) slot = slot_of(k, key_hash<KD>(k), home[r], cur[r]);
+        if constexpr (kDig)
+          if (!lds_digits_hold(fv)) slot = -1;  // outside the LDS slot's digits: the global table
         if (slot >= 0) {
-          const int s = slot * REP + (int)(threadIdx.x & (REP - 1));  // this lane's copy
+          const int s = slot * REP + (int)(tid & (REP - 1));  // this lane's copy
           if constexpr (kDig) {
             at_add<true>(&cnt[s], 1u);
             if (!__builtin_isfinite(fv)) {
@@ -677,43 +741,41 @@ struct LdsTable {
               at_add<true>(reinterpret_cast<unsigned long long*>(&dig[e0 + 1]), (unsigned long long)dhi);
             }
           } else {
-            apply<G, true>(&cnt[s], &val[kVal ? s : 0], &dig[0], &flags[0], (int64_t)b.iv[r], fv);
+            apply<G, true>(&cnt[s], &val[kVal ? s : 0], &dig[0], &flags[0], (int64_t)b.x[r].iv, fv);
           }
         } else {
-          const int64_t g = global_slot(t, (int64_t)k);
-          if (g >= 0) apply_global<G>(t, g, (int64_t)b.iv[r], fv);
+          spill |= 1u << r;
         }
       }
+      // rows for the global table: rare, so one copy of the code for all of
+      // the batch's rows, which reads them again
+      while (spill) {
+        const uint32_t r = (uint32_t)__builtin_ctz(spill);
+        spill &= spill - 1;
+        Row x;
+        load_row(x, base, row_at((int)r));
+        const int64_t g = global_slot(t, (int64_t)x.k, key_hash<KD>(x.k));
+        if (g >= 0) apply_global<G>(t, g, (int64_t)x.iv, x.fv);
+      }
     };
-    if (first >= last) return;
-    const int64_t adv = step * R;
-    // Rows of at most two 32-bit words (key and value registers): two batches
-    // alternate, so the next batch's loads are in flight while this one is
-    // folded (2^28 rows, int32 keys: COUNT at 16 groups 0.33 -> 0.25 ms, float
-    // SUM at 1024 groups 1.07 -> 0.99 ms).  Wider rows fold one batch at a
-    // time: two batches of int64 values took the fold to 128 registers and
-    // ran 5-15% slower.  The few-groups table (REP > 1) runs two workgroups
-    // per CU, which leaves two batches' registers only to COUNT's key-only rows.
-    constexpr int kWords = (KD == AGG_I64 ? 2 : 1) + (G == G_COUNT ? 0 : VD == AGG_I64 ? 2 : 1);
-    if constexpr (kWords <= 2 && (REP == 1 || kWords == 1)) {
-      Batch A, B;
-      load(A, first);
-      for (int64_t base = first;;) {
-        load(B, base + adv);
-        fold(A, base);
-        base += adv;
-        if (base >= last) break;
-        load(A, base + adv);
-        fold(B, base);
-        base += adv;
-        if (base >= last) break;
+    int64_t b = first;
+    Batch A;
+    if (b + TR <= last) {
+      load(A, b);
+      for (;;) {
+        const int64_t next = b + tile_step;
+        const bool more = next + TR <= last;
+        Batch B;
+        if (more) load(B, next);
+        fold(A, b, true, 0);
+        b = next;
+        if (!more) break;
+        A = B;
       }
-    } else {
-      Batch A;
-      for (int64_t base = first; base < last; base += adv) {
-        load(A, base);
-        fold(A, base);
-      }
+    }
+    if (b < last) {  // the partial tile
+      load_tail(A, b, (uint32_t)(last - b));
+      fold(A, b, false, (uint32_t)(last - b));
     }
   }
 
@@ -731,7 +793,7 @@ struct LdsTable {
       uint64_t c = 0;
       for (int r = 0; r < REP; ++r) c += cnt[e * REP + r];
       if (e < L ? k == kMark : c == 0) continue;
-      const int64_t g = global_slot(t, (int64_t)k);
+      const int64_t g = global_slot(t, (int64_t)k, key_hash<KD>(k));
       if (g < 0) continue;
       atomicAdd(reinterpret_cast<unsigned long long*>(t.cnt + g), (unsigned long long)c);
       if constexpr (kVal) {
@@ -760,44 +822,42 @@ struct LdsTable {
   }
 };
 
-// Float sums of few groups (at most kFewGroups): with a full-size table a
-// wave's 64 rows fall on about as many slots as there are groups, and the
-// LDS atomics of lanes that meet on a slot serialise (measured on MI355X: a
-// 64-bit add from a wave whose rows spread over 16 slots takes about 24
-// clocks, over 64 addresses 6); a float row makes three (two digits and the
-// count).  A small table whose slots carry kFewCopies copies of the
+// Few groups (at most kFewGroups): with a full-size table a wave's 64 rows
+// fall on about as many slots as there are groups, and the LDS atomics of
+// lanes that meet on a slot serialise (measured on MI355X: a 64-bit add from a
+// wave whose rows spread over 16 slots takes about 24 clocks, over 64
+// addresses 6).  A small table whose slots carry kFewCopies copies of the
 // accumulators (lane l updates copy l % kFewCopies) cuts the meetings by that
-// factor.  16 groups, 2^28 rows: 4 copies of 256 slots 0.626 -> 0.594 ms at
-// one workgroup per CU; at two (the table is 65 KiB) 0.45-0.48 ms with 4
-// copies, 0.44-0.45 with 8 copies of 128 slots and 0.44 with 16 of 64 (the
-// 128-slot table keeps 32 groups a quarter full).  COUNT takes the same
-// table (4.6 KiB of LDS) with its key loads pipelined and two workgroups per
-// CU: 0.253 -> 0.241 ms at 16 groups, 0.255 -> 0.239 at 32 (at one
-// workgroup per CU and 4 copies it had been slower: 0.338 -> 0.348 ms).
-// Integer sums keep the full table: with copies and two workgroups per CU
-// they ran 0.54 -> 0.64 ms at 16 groups.
+// factor, and is cleared and flushed in one step.  2^28 rows, int32 keys,
+// full table -> this one: int64 SUM 1056 -> 492 us at 2 groups, 499 -> 495 at
+// 16; COUNT 545 -> 183 and 210 -> 182; float SUM 1580 -> 430 and 620 -> 370.
 constexpr int kFewGroups = 32;
 constexpr int kFewCopies = 8;
 constexpr int kFewSlots = 128;
 
-// Direct path: every workgroup sweeps the rows grid-stride into one LDS
-// table, in 2^sub_bits passes (each taking the keys of one sub-partition:
+// Direct path: every workgroup sweeps its share of the rows' tiles into one
+// LDS table, in 2^sub_bits passes (each taking the keys of one sub-partition:
 // the top bits of the key's hash) when the groups need more than one table.
-// The few-groups table (65 KiB of LDS) leaves room for two workgroups per CU
-// when the fold fits 64 registers: 16 groups, 2^28 rows, float SUM 0.60 ->
-// 0.49 ms (8 waves per SIMD instead of 4 hide the LDS and memory latency).
+// Bound by HBM where a row is 12 bytes or more: 2^28 rows, int32 keys, 1024
+// dense keys: int64 SUM 563 -> 499 us (6.45 TB/s), COUNT 367 -> 207 (5.2),
+// float SUM 923 -> 428 (5.0); the loads alone run at 6.6 TB/s.
+// The few-groups table leaves room for two workgroups per CU where the fold
+// fits 64 registers, which rows of up to two words do (8 waves per SIMD
+// instead of 4 hide the LDS and memory latency; wider rows keep 8 rows in
+// flight per thread instead: int64 SUM of 16 groups 495 us against 519).
 template <int KD, int VD, int G, bool FEW, bool SUB>
-__global__ void __attribute__((amdgpu_flat_work_group_size(1, kDirectThreads), amdgpu_waves_per_eu(FEW ? 8 : 1)))
+__global__ void __attribute__((amdgpu_flat_work_group_size(1, kDirectThreads), amdgpu_waves_per_eu(FEW && row_words<KD, VD, G>() <= 2 ? 8 : 1)))
 gb_aggregate_kernel(Args a) {
-  static_assert(!FEW || G == G_SUM_F32 || G == G_COUNT, "the few-groups table is for float sums and counts");
+  
   __shared__ LdsTable<G, KD, FEW ? kFewSlots : lds_slots<G, KD>(), kDirectThreads, FEW ? kFewCopies : 1> tab;
+  constexpr int TR = decltype(tab)::template tile_rows_of<VD>() * kDirectThreads;
   const uint32_t sub_mask = (1u << a.pt.sub_bits) - 1u;
-  const uint32_t sub_shift = a.pt.sub_bits ? (uint32_t)(64 - a.pt.sub_bits) : 0u;
+  const uint32_t sub_shift = a.pt.sub_bits ? (uint32_t)(32 - a.pt.sub_bits) : 0u;
   for (uint32_t sub = 0; sub <= sub_mask; ++sub) {
     tab.clear();
     __syncthreads();
-    tab.template fold_rows<VD, false, SUB>(a.t, a.keys, a.vals, (int64_t)blockIdx.x * kDirectThreads + threadIdx.x,
-                                           a.n, (int64_t)gridDim.x * kDirectThreads, sub_shift, sub_mask, sub);
+    tab.template fold_rows<VD, false, SUB>(a.t, a.keys, a.vals, (int64_t)blockIdx.x * TR, a.n,
+                                           (int64_t)gridDim.x * TR, (uint32_t)a.pt.sub_bits, sub_shift, sub_mask, sub);
     __syncthreads();
     tab.flush(a.t);
     __syncthreads();
@@ -815,6 +875,7 @@ gb_aggregate_kernel(Args a) {
 template <int KD, int VD, int G, bool SUB>
 __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a) {
   __shared__ LdsTable<G, KD, lds_slots<G, KD>(), kPartThreads> tab;
+  constexpr int TR = decltype(tab)::template tile_rows_of<VD>() * kPartThreads;
   const int P = 1 << a.pt.bits;
   int64_t r = a.n * (int64_t)blockIdx.x / gridDim.x;
   const int64_t r1 = a.n * ((int64_t)blockIdx.x + 1) / gridDim.x;
@@ -827,14 +888,14 @@ __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a)
   }
   int p = lo;
   const uint32_t sub_mask = (1u << a.pt.sub_bits) - 1u;
-  const uint32_t sub_shift = a.pt.sub_bits ? (uint32_t)(64 - a.pt.bits - a.pt.sub_bits) : 0u;
+  const uint32_t sub_shift = a.pt.sub_bits ? (uint32_t)(32 - a.pt.bits - a.pt.sub_bits) : 0u;
   while (r < r1) {
     while ((int64_t)a.pt.start[p + 1] <= r) ++p;  // skip partitions that end before r
     const int64_t seg_end = std::min<int64_t>(r1, (int64_t)a.pt.start[p + 1]);
     for (uint32_t sub = 0; sub <= sub_mask; ++sub) {
       tab.clear();
       __syncthreads();
-      tab.template fold_rows<VD, true, SUB>(a.t, a.pt.pk, a.pt.pv, r + threadIdx.x, seg_end, kPartThreads,
+      tab.template fold_rows<VD, true, SUB>(a.t, a.pt.pk, a.pt.pv, r, seg_end, TR, (uint32_t)(a.pt.bits + a.pt.sub_bits),
                                             sub_shift, sub_mask, sub);
       __syncthreads();
       tab.flush(a.t);
@@ -939,27 +1000,27 @@ int gop_of(int32_t val_dtype, int32_t op) {
   return -1;
 }
 
-// PATH: 0 direct, 1 partitioned, 2 direct for float sums and counts of few
-// groups (accumulator copies), 3 direct in sub-partition passes, 4 partitioned in
-// sub-partition passes.  Plans without passes take kernels whose fold has no
+// PATH: 0 direct, 1 partitioned, 2 direct with few groups (accumulator copies),
+// 3 direct in sub-partition passes (no COUNT: it partitions instead), 4
+// partitioned in sub-partition passes.  Plans without passes take kernels whose fold has no
 // per-row pass test.
 template <int KD, int VD, int PATH>
 const void* agg_row(int g) {
 #define GB_AGG(GG)                                                                                        \
   (PATH == 1 || PATH == 4                                                                                 \
        ? reinterpret_cast<const void*>(&gb_aggregate_part_kernel<KD, VD, GG, PATH == 4>)                  \
-       : reinterpret_cast<const void*>(&gb_aggregate_kernel<KD, VD, GG, PATH == 2 && (GG == G_SUM_F32 || GG == G_COUNT), PATH == 3>))
+       : reinterpret_cast<const void*>(&gb_aggregate_kernel<KD, VD, GG, PATH == 2, PATH == 3>))
   if constexpr (VD == AGG_F32) {
     switch (g) {
-      case G_COUNT: return GB_AGG(G_COUNT);
       case G_SUM_F32: return GB_AGG(G_SUM_F32);
       case G_MIN_F32: return GB_AGG(G_MIN_F32);
       case G_MAX_F32: return GB_AGG(G_MAX_F32);
       default: return nullptr;
     }
   } else {
+    if constexpr (VD == AGG_I32 && PATH != 3)
+      if (g == G_COUNT) return GB_AGG(G_COUNT);
     switch (g) {
-      case G_COUNT: return GB_AGG(G_COUNT);
       case G_SUM_INT: return GB_AGG(G_SUM_INT);
       case G_MIN_INT: return GB_AGG(G_MIN_INT);
       case G_MAX_INT: return GB_AGG(G_MAX_INT);
@@ -971,6 +1032,7 @@ const void* agg_row(int g) {
 
 template <int KD, int PATH>
 const void* agg_kernel_kd(int32_t vd, int g) {
+  if (g == G_COUNT) return agg_row<KD, AGG_I32, PATH>(g);  // reads no values
   switch (vd) {
     case AGG_I32: return agg_row<KD, AGG_I32, PATH>(g);
     case AGG_I64: return agg_row<KD, AGG_I64, PATH>(g);
@@ -1054,7 +1116,7 @@ struct agg_groupby_s {
   void* ws = nullptr;
   Table t{};
   Part pt{};           // bits == 0: the direct path
-  int path = 0;        // 0 direct, 1 partitioned, 2 few-groups float sums, 3 / 4: 0 / 1 in sub-partition passes
+  int path = 0;        // 0 direct, 1 partitioned, 2 few groups, 3 / 4: 0 / 1 in sub-partition passes
   int agg_blocks = 1;  // aggregation workgroups resident per CU
 };
 
@@ -1132,6 +1194,7 @@ int agg_groupby_plan(agg_groupby_t* out, int32_t key_dtype, int32_t val_dtype, i
   p->t.flags = reinterpret_cast<int32_t*>(take(b_flags));
   p->t.state = reinterpret_cast<int32_t*>(take(b_state));
   p->t.cap = cap;
+  p->t.cap_log2 = __builtin_ctzll((unsigned long long)cap);
   p->pt.hist = reinterpret_cast<uint32_t*>(take(b_hist));
   p->pt.tot = reinterpret_cast<uint32_t*>(take(b_tot));
   p->pt.start = reinterpret_cast<uint32_t*>(take(b_start));
@@ -1148,14 +1211,7 @@ int agg_groupby_plan(agg_groupby_t* out, int32_t key_dtype, int32_t val_dtype, i
   p->max_groups = max_groups;
   // aggregation grids are sized to what the chip holds at once (no second, mostly idle wave of workgroups)
   int nb = 0;
-  // Integer sums of few groups keep the kernel with the per-row pass test
-  // (its masks are zero here, so every row passes): their LDS atomics collide
-  // on a few addresses, and the leaner fold, which issues them faster, ran
-  // slower (16 groups, 2^28 rows: 0.555 against 0.526 ms).
-  p->path = bits ? (sub_bits ? 4 : 1)
-                 : sub_bits ? 3
-                 : max_groups <= kFewGroups ? (g == G_SUM_F32 || g == G_COUNT ? 2 : g == G_SUM_INT ? 3 : 0)
-                                            : 0;
+  p->path = bits ? (sub_bits ? 4 : 1) : sub_bits ? 3 : max_groups <= kFewGroups ? 2 : 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, agg_kernel(key_dtype, val_dtype, g, p->path),
                                                    bits ? kPartThreads : kDirectThreads, 0) !=
           hipSuccess ||

@@ -1,0 +1,65 @@
+"""GPU: the group-by fold's tiles and its hash, against the oracle.
+
+Rows are folded in tiles of 4096 or 8192 per workgroup, read as vectors of 2 or
+4 items; the last tile is partial.  Keys are placed by one multiplicative
+hash, so regular key sets (strides, keys that differ in one word only) are the
+ones that could crowd a partition or a table.  All results are exact."""
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_groupby import agg, compare, make_vals  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+NP = {"i32": np.int32, "i64": np.int64}
+
+
+def run(agg, keys, vals, op, max_groups, ctx, offset=0):
+    """Group-by of device columns that start `offset` items into their allocations."""
+    import torch
+    kdt = "i32" if keys.dtype == np.int32 else "i64"
+    vdt = {"int32": "i32", "int64": "i64", "float32": "f32"}[vals.dtype.name]
+
+    def dev(x):
+        d = torch.zeros(x.size + offset, dtype=torch.from_numpy(x[:0]).dtype, device="cuda")
+        d[offset:].copy_(torch.from_numpy(x))
+        return d[offset:]
+    g = agg.GroupBy(kdt, vdt, op, max_n=max(1, keys.size), max_groups=max_groups)
+    compare(g.run(dev(keys), dev(vals)), oracle.groupby(keys, vals, op), ctx)
+    g.close()
+
+
+@pytest.mark.parametrize("kdt", ["i32", "i64"])
+@pytest.mark.parametrize("vdt,op", [("i32", "sum"), ("i64", "min"), ("f32", "avg"), ("i32", "count")])
+def test_fold_tile_edges(agg, kdt, vdt, op):
+    """One row, and one row either side of one and of several tiles, through the
+    few-groups, direct, two-pass and partitioned paths, from aligned columns and
+    from columns that start one item further on."""
+    r = np.random.default_rng(3)
+    for groups in (3, 700, 6000, 40_000):
+        for n in (1, 3, 4095, 4097, 8191, 8193, 3 * 8192, 40_961):
+            keys = r.integers(0, min(groups, n), size=n).astype(NP[kdt])
+            vals = make_vals(n, vdt, seed=n)
+            for offset in (0, 1):
+                run(agg, keys, vals, op, groups, f"{kdt}/{vdt} {op} n={n} groups={groups} offset={offset}", offset)
+
+
+@pytest.mark.parametrize("kdt,first,stride", [
+    ("i32", 0, 1), ("i32", -5000, 1), ("i32", 7, 1 << 12), ("i32", 0, 75_025), ("i32", -2**31, 2**32 // 10_000),
+    ("i64", 0, 1), ("i64", 10**12, 86_400), ("i64", 0, 1 << 32), ("i64", -2**63, (1 << 32) + 1), ("i64", 5, 1 << 50)])
+def test_regular_key_sets(agg, kdt, first, stride):
+    """Arithmetic key sequences (dense codes, powers of two, a Fibonacci stride,
+    keys that differ in their high words only) through the direct, two-pass,
+    partitioned and sub-partition paths."""
+    n = 100_003
+    bits = 32 if kdt == "i32" else 64
+    pool = [first + i * stride for i in range(10_000)]
+    pool = np.array([(p + 2**(bits - 1)) % 2**bits - 2**(bits - 1) for p in pool], dtype=NP[kdt])
+    r = np.random.default_rng(stride % 1000)
+    for groups in (20, 1000, 10_000):
+        keys = pool[r.integers(0, groups, size=n)]
+        for vdt, op in (("i64", "sum"), ("f32", "sum"), ("i32", "count")):
+            for declared in (groups, 3_000_000):
+                run(agg, keys, make_vals(n, vdt, seed=groups), op, declared,
+                    f"{kdt} {first}+{stride}i groups={groups} declared={declared} {vdt} {op}")
