@@ -3,12 +3,12 @@
 //
 // Table: open addressing over a power-of-two number of slots, keys claimed
 // with a 64-bit compare-and-swap (INT64_MIN marks an empty slot; the key
-// INT64_MIN itself lives in one extra slot), double hashing bounded by the
-// table size -- no thread ever waits on another.  Rows are first aggregated
-// into a workgroup's own table in LDS (a few probes per row; a row whose key
-// finds no LDS slot goes straight to the global table) and each LDS table is
-// flushed into the global table once, so the global table sees one update
-// per (workgroup, key) instead of one per row.
+// INT64_MIN itself lives in one extra slot), every probe of a key hashed anew
+// and their number bounded -- no thread ever waits on another.  Rows are first
+// aggregated into a workgroup's own table in LDS (mostly one probe per row; a
+// row whose key finds no LDS slot goes straight to the global table) and each
+// LDS table is flushed into the global table once, so the global table sees
+// one update per (workgroup, key) instead of one per row.
 //
 // Two paths, chosen from the plan's max_groups:
 //  * direct: workgroups stride over the rows; every workgroup's LDS table
@@ -25,9 +25,9 @@
 //
 // Determinism: integer SUM (mod 2^64), MIN, MAX and COUNT are exact in any
 // order.  A float32 SUM is accumulated exactly: every finite float is
-// m * 2^(k-149) with m < 2^24, added as two integer digits of a base-2^32
-// fixed-point number, so the group sum is exact whatever the order and is
-// rounded once to double at the end.  The row order inside a partition (set
+// m * 2^(k-149) with m < 2^24, added as whole numbers to a fixed-point one (64-bit
+// windows in LDS, base-2^32 digits in the global table), so the group sum is
+// exact whatever the order and is rounded once to double at the end.  The row order inside a partition (set
 // by LDS atomics) therefore never shows in a result.
 #include <hip/hip_runtime.h>
 
@@ -46,6 +46,7 @@ namespace gb {
 constexpr int64_t kEmpty = INT64_MIN;
 constexpr int kThreads = 256;
 constexpr int kLdsProbes = 16;
+constexpr int kGlobalProbes = 32;     // hashed probes of the global table, then linear ones
 constexpr int kAggRows = 8;           // rows whose loads a thread keeps in flight
 constexpr int kMaxPartBits = 14;      // at most 16384 (sub-)partitions
 constexpr int kMinPartBits = 5;       // at least 32
@@ -85,22 +86,38 @@ struct StagedRow {
 enum GOp { G_COUNT = 0, G_SUM_INT, G_MIN_INT, G_MAX_INT, G_SUM_F32, G_MIN_F32, G_MAX_F32 };
 
 // LDS tables: one 1024-thread workgroup per CU with one table of up to
-// 148 KiB, on both paths: 8192 slots for 4-byte keys, 4096 for 8-byte keys
-// (twice that for COUNT, which keeps no value; 2048 for float sums, whose
-// slots carry 7 fixed-point digits).  Measured against three 256-thread
+// 150 KiB, on both paths: 8192 slots for 4-byte keys, 4096 for 8-byte keys
+// (twice that for COUNT, which keeps no value; 4096 for float sums, whose
+// slots carry three 64-bit windows).  Measured against three 256-thread
 // workgroups per CU with half the slots: fewer, larger tables hold 2x the
 // groups at the same load and fold faster.
 constexpr int kDirectThreads = 1024;
 constexpr int lds_slots_of(int g, int kd) {
-  return g == G_SUM_F32 ? 2048 : (g == G_COUNT ? 2 : 1) * (kd == AGG_I32 ? 8192 : 4096);
+  return g == G_SUM_F32 ? 4096 : (g == G_COUNT ? 2 : 1) * (kd == AGG_I32 ? 8192 : 4096);
 }
-// A float sum's LDS slot keeps digits 1..7 of the 9: a finite float
-// m * 2^(k-149) touches digits k/32 and k/32 + 1, both within 1..7 for
-// 32 <= k <= 223 (2^-94 <= |x| < 2^98: normal floats of biased exponent
-// 33..224).  Zeros add nothing and non-finite floats only set flags; every
-// other float is folded straight into the global table.  Seven digits
-// instead of nine fit twice the slots in LDS.
-constexpr int kLdsDigits = 7;
+// A float sum's LDS slot holds kWindows 64-bit fixed-point windows of
+// kWinOctaves exponents each, placed where the column's exponents are
+// (FloatWindows): a float of biased exponent base + 16 w + s adds its signed
+// mantissa << s to window w, one add instead of the two digits it straddles
+// in the global table, and a slot takes 24 bytes instead of the 56 of seven
+// digits.  |mantissa << s| < 2^39, so 2^24 rows fit a window (kMaxTableRows).
+// The flush splits each window into the global table's digits, exactly.
+// One add for two, half the table, and so half the partitions: 2^28 rows, int32
+// keys: 16 groups 370 -> 343 us, 1024 groups 428 -> 380, 2^16 groups 2139 ->
+// 1653, 2^20 groups 2982 -> 2343.
+constexpr int kWindows = 3;
+constexpr int kWinOctaves = 16;
+constexpr int kWinSpan = kWindows * kWinOctaves;  // 48 exponents a pass: 14 decades
+constexpr int64_t kMaxTableRows = (int64_t)1 << 23;
+// The exponents the windows cover: kWinSpan from `first` on in the first of
+// `passes` passes over the rows, the next kWinSpan in the second, and so on.
+struct FloatWindows {
+  int first = 1;
+  int passes = 1;
+  __device__ __forceinline__ uint32_t base(int pass) const { return (uint32_t)(first + pass * kWinSpan); }
+  // exponents of the pass (255 marks non-finite floats and is never one of them)
+  __device__ __forceinline__ uint32_t span(int pass) const { return min((uint32_t)kWinSpan, 255u - base(pass)); }
+};
 template <int G, int KD>
 constexpr int lds_slots() { return lds_slots_of(G, KD); }
 constexpr int kPartThreads = 1024;
@@ -111,7 +128,7 @@ struct Table {
   int64_t* val;        // integer SUM / MIN / MAX; float MIN / MAX as order-preserving ints
   int64_t* dig;        // float SUM: kDigits per slot
   int32_t* flags;      // float SUM: 1 NaN, 2 +Inf, 4 -Inf seen
-  int32_t* state;      // [0] slot cap used, [1] overflow, [2..3] emitted count (uint64)
+  int32_t* state;      // [0] slot cap used, [1] overflow, [2..3] emitted count (uint64), [4..5] float-sum windows
   int64_t cap;         // slots, a power of two >= 64
   int32_t cap_log2;
 };
@@ -167,22 +184,14 @@ __device__ __forceinline__ uint32_t key_hash(typename std::conditional<KD == AGG
   else return lo + (uint32_t)((uint64_t)k >> 32) * 0x69C77F93u;
 }
 
-// The odd step of a key's further probes (double hashing: keys that share a
-// home part ways).  Only a probe that misses its home computes it.
-__device__ __forceinline__ uint32_t probe_step(uint32_t h) { return ((h * 0x85EBCA6Bu) >> 15) | 1u; }
+// The hash of a key's next probe, again read from the top.  Each probe lands
+// somewhere new: with a fixed step (double hashing) a key of a dense set whose
+// step is the distance between two others' homes only ever meets occupied
+// slots.
+__device__ __forceinline__ uint32_t next_probe(uint32_t h) { return h * 0x85EBCA6Bu + 0x7FEB352Du; }
 
 // Partition of a key: the top bits of its hash.
 __device__ __forceinline__ uint32_t part_of(uint32_t h, int bits) { return h >> (32 - bits); }
-
-// 7 * x for x < 2^24 as one full-rate 24-bit multiply (left to itself the
-// compiler issues a quarter-rate 32-bit one for the float-sum slot's digit
-// index).
-static_assert(kLdsDigits == 7, "mul7_u24 scales by the LDS slot's digit count");
-__device__ __forceinline__ uint32_t mul7_u24(uint32_t x) {
-  uint32_t r;
-  __asm__("v_mul_u32_u24 %0, 7, %1" : "=v"(r) : "v"(x));
-  return r;
-}
 
 // Order-preserving map of non-NaN floats to int32 (and back).
 __device__ __forceinline__ int32_t f32_order(float f) {
@@ -204,13 +213,6 @@ __device__ __forceinline__ void f32_digits(float x, int* k0, int64_t* lo, int64_
   *k0 = k >> 5;
   *lo = (int64_t)((uint64_t)sv & 0xFFFFFFFFu);
   *hi = sv >> 32;
-}
-
-// Whether an LDS float-sum slot (digits 1..7) can take x.
-__device__ __forceinline__ bool lds_digits_hold(float x) {
-  const uint32_t b = __float_as_uint(x);
-  const uint32_t e = (b >> 23) & 0xFFu;
-  return (e - 33u) <= 191u || (b << 1) == 0u || e == 0xFFu;
 }
 
 // Atomics on a slot of an LDS table (workgroup scope) or of the global
@@ -284,9 +286,11 @@ __device__ __forceinline__ int64_t global_slot(const Table& t, int64_t k, uint32
     return t.cap;
   }
   const uint64_t mask = (uint64_t)t.cap - 1;
-  uint64_t s = t.cap_log2 <= 32 ? (uint64_t)(h >> (32 - t.cap_log2)) : (uint64_t)h << (t.cap_log2 - 32);
-  const uint64_t step = probe_step(h);
-  for (int64_t p = 0; p < t.cap; ++p, s = (s + step) & mask) {
+  uint64_t s = 0;
+  for (int64_t p = 0; p < t.cap + kGlobalProbes; ++p) {
+    if (p < kGlobalProbes) s = t.cap_log2 <= 32 ? (uint64_t)(h >> (32 - t.cap_log2)) : (uint64_t)h << (t.cap_log2 - 32);
+    else s = (s + 1) & mask;  // from the last of them on, every slot in turn
+    h = next_probe(h);
     const int64_t cur = t.key[s];
     if (cur == k) return (int64_t)s;
     if (cur == kEmpty) {
@@ -552,28 +556,30 @@ struct LdsTable {
   static_assert((L & (L - 1)) == 0, "home_of takes log2(L) hash bits");
   // Rows a thread folds at a time (two batches are in registers: the next
   // one's loads are in flight): 8, or 4 where a row has four 32-bit words (8
-  // ran 8% slower: spills) or has two and two workgroups share a CU.
+  // ran 8% slower: spills).
   template <int VD>
-  static constexpr int tile_rows_of() {
-    constexpr int words = row_words<KD, VD, G>();
-    return words >= 4 || (REP > 1 && words == 2) ? 4 : 8;
-  }
+  static constexpr int tile_rows_of() { return row_words<KD, VD, G>() >= 4 ? 4 : 8; }
   KT key[L];
   uint32_t cnt[E];  // rows per table stay below 2^32 (a workgroup's share is at most 2^28 rows)
   int64_t val[kVal ? E : 1];
-  int64_t dig[kDig ? E * kLdsDigits : 1];  // digits 1..7 of a float sum
-  int32_t flags[kDig ? E : 1];
+  int64_t win[kDig ? kWindows * E : 1];    // float sum: window w of entry e at w * E + e
+  uint32_t flags[kDig ? L / 8 + 1 : 1];    // float sum: non-finite rows seen, four bits a slot
 
-  __device__ __forceinline__ void clear() {
-    for (int e = threadIdx.x; e < L; e += NT) key[e] = kMark;
+  __device__ __forceinline__ void clear(uint32_t skip) {
+    // The marker key's home holds key 0 from the start: a row of the marker key
+    // then never finds its key at home (it would take an empty slot for its
+    // own), and goes on to slot L.  Key 0 may use the slot like any other it
+    // finds itself in; with no rows it is not flushed.
+    const int marker_home = (int)home_of(key_hash<KD>(kMark), skip);
+    for (int e = threadIdx.x; e < L; e += NT) key[e] = e == marker_home ? (KT)0 : kMark;
     for (int e = threadIdx.x; e < E; e += NT) {
       cnt[e] = 0;
       if constexpr (kVal) val[e] = val_identity<G>();
-      if constexpr (kDig) {
-        flags[e] = 0;
-        for (int d = 0; d < kLdsDigits; ++d) dig[e * kLdsDigits + d] = 0;
-      }
+      if constexpr (kDig)
+        for (int w = 0; w < kWindows; ++w) win[w * E + e] = 0;
     }
+    if constexpr (kDig)
+      for (int e = threadIdx.x; e <= L / 8; e += NT) flags[e] = 0;
   }
 
   // The home slot of a key with hash h: the log2(L) hash bits below the
@@ -582,23 +588,35 @@ struct LdsTable {
     return __builtin_amdgcn_ubfe(h, (uint32_t)(32 - kLog2L) - skip, (uint32_t)kLog2L);
   }
 
-  // The slot of key k where its home, which read `cur`, does not hold it (or
-  // k is the marker key): claims an empty slot, -1 if there is none within
-  // kLdsProbes probes.
-  __device__ __forceinline__ int slot_of(KT k, uint32_t h, uint32_t home, KT cur) {
+  // The slot of key k with hash h, claiming an empty one; -1 if there is none
+  // within kLdsProbes probes.
+  __device__ __forceinline__ int slot_of(KT k, uint32_t h, uint32_t skip) {
     if (k == kMark) return L;
-    const uint32_t step = probe_step(h);
-    uint32_t s = home;
+    uint32_t s = home_of(h, skip);
+#pragma unroll 1
     for (int p = 0; p < kLdsProbes; ++p) {
+      const KT cur = key[s];
       if (cur == k) return (int)s;
       if (cur == kMark) {
         const KT prev = (KT)atomicCAS(reinterpret_cast<UKT*>(&key[s]), (UKT)kMark, (UKT)k);
         if (prev == kMark || prev == k) return (int)s;
       }
-      s = (s + step) & (uint32_t)(L - 1);
-      cur = key[s];
+      h = next_probe(h);
+      s = home_of(h, 0);
     }
     return -1;
+  }
+
+  // Adds the float of bits fb to the windows of entry s; u = its bits << 1
+  // less the pass's first exponent << 24, below kWinSpan << 24.
+  __device__ __forceinline__ void add_window(int s, uint32_t fb, uint32_t u) {
+    const int32_t sign = (int32_t)fb >> 31;
+    const int32_t m = (int32_t)(((fb & 0x7FFFFFu) | 0x800000u) ^ (uint32_t)sign) - sign;
+    const uint32_t w = u >> 28, sh = __builtin_amdgcn_ubfe(u, 24, 4);
+    static_assert(kWinOctaves == 16, "a window is the exponent's upper four bits");
+    // m is never 0, so its sign word is the upper half of the 64-bit value
+    const uint64_t v = (((uint64_t)(uint32_t)sign << 32) | (uint32_t)m) << sh;
+    at_add<true>(reinterpret_cast<unsigned long long*>(&win[__umul24(w, E) + (uint32_t)s]), (unsigned long long)v);
   }
 
   // Folds the rows of the tiles first, first + tile_step, ... (kTile rows
@@ -613,11 +631,17 @@ struct LdsTable {
   // bounds test nor address arithmetic (a uniform base per row and one lane
   // offset), the next tile's loads are in flight while a tile is folded, and
   // the first probes of a batch are read before the first of them is
-  // resolved.
+  // resolved.  A row whose home slot holds its key takes a few straight
+  // instructions; a batch with any other row (a new key, a collision, a float
+  // outside the windows) reads all second probes too, and what neither probe
+  // finds sets a bit for one loop after the batch, which handles one row of
+  // each lane at a time.  (Random keys that fill half a table, 2^28 rows:
+  // int64 SUM of 4096 groups 830 -> 721 us; with the loop right after the
+  // first probes 923.)
   template <int VD, bool ROWS, bool SUB>
-  __device__ __forceinline__ void fold_rows(const Table& t, const void* keys, const void* vals, int64_t first,
+  __device__ __forceinline__ void fold_rows(const Table& t_, const void* keys, const void* vals, int64_t first,
                                             int64_t last, int64_t tile_step, uint32_t skip, uint32_t sub_shift,
-                                            uint32_t sub_mask, uint32_t sub) {
+                                            uint32_t sub_mask, uint32_t sub, const FloatWindows& fw, int pass) {
     constexpr int R = tile_rows_of<VD>();
     constexpr int TR = R * NT;
     constexpr bool kStaged = ROWS && G != G_COUNT;
@@ -632,6 +656,13 @@ struct LdsTable {
       Row x[R];
     };
     const uint32_t tid = threadIdx.x;
+    // a float's exponent is compared in place, as the top byte of its bits << 1
+    // less the pass's first exponent (exponents below it wrap past the span);
+    // no pass takes out_from and up, seen from the first one (zeros, subnormals
+    // and non-finite floats among them)
+    const uint32_t win_off = 0u - (fw.base(pass) << 24), win_span = fw.span(pass) << 24;
+    const uint32_t out_from =
+        pass == 0 ? min((uint32_t)(fw.passes * kWinSpan), 255u - fw.base(0)) << 24 : UINT32_MAX;
     auto load_row = [&](Row& x, int64_t base, uint32_t lane) {  // row base + lane (base uniform)
       x.iv = 0;
       x.fv = 0.0f;
@@ -704,7 +735,7 @@ struct LdsTable {
           else __asm__ volatile("" : "+v"(b.x[r].iv));
         }
       }
-      uint32_t spill = 0;
+      uint32_t rest = 0;  // bit R - 1 - r: row r is for the loop below
       uint32_t home[R];
       KT cur[R];
 #pragma unroll
@@ -712,50 +743,107 @@ struct LdsTable {
         home[r] = home_of(key_hash<KD>(b.x[r].k), skip);
         cur[r] = key[home[r]];
       }
+      // one wait for all of the batch's probes: left alone, each row's check
+      // would also wait for the atomics of the rows before it
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (!full && row_at(r) >= left) continue;
-        const KT k = b.x[r].k;
-        if (SUB && ((key_hash<KD>(k) >> sub_shift) & sub_mask) != sub) continue;  // another pass's row
-        const float fv = b.x[r].fv;
-        int slot = (int)home[r];
-        if (cur[r] != k || k == kMark) slot = slot_of(k, key_hash<KD>(k), home[r], cur[r]);
-        if constexpr (kDig)
-          if (!lds_digits_hold(fv)) slot = -1;  // outside the LDS slot's digits: the global table
-        if (slot >= 0) {
-          const int s = slot * REP + (int)(tid & (REP - 1));  // this lane's copy
-          if constexpr (kDig) {
-            at_add<true>(&cnt[s], 1u);
-            if (!__builtin_isfinite(fv)) {
-              at_or<true>(&flags[s], __builtin_isnan(fv) ? 1 : (fv > 0 ? 2 : 4));
-            } else {  // digit j of the sum sits at dig[s * kLdsDigits + j - 1]
-              int dk;
-              int64_t dlo, dhi;
-              f32_digits(fv, &dk, &dlo, &dhi);
-              // both adds unconditionally (no branch per digit): a float the slot
-              // holds has 1 <= dk <= 6, and a zero (dk = 0, both digits 0) adds 0
-              // to digit slots 0 and 1
-              const int j = dk > 0 ? dk - 1 : 0;
-              const int e0 = (int)mul7_u24((uint32_t)s) + j;
-              at_add<true>(reinterpret_cast<unsigned long long*>(&dig[e0]), (unsigned long long)dlo);
-              at_add<true>(reinterpret_cast<unsigned long long*>(&dig[e0 + 1]), (unsigned long long)dhi);
+      for (int r = 0; r < R; ++r) __asm__ volatile("" : "+v"(cur[r]));
+      const int copy = (int)(tid & (REP - 1));  // this lane's copy of the accumulators
+      if constexpr (!SUB) {
+        // Nearly every batch of a wave: each row of each lane finds its key at
+        // home (and its float in a window), tested for all of them at once, so
+        // a row is its adds and nothing else.
+        KT differ = 0;
+        uint32_t far = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          differ |= cur[r] ^ b.x[r].k;
+          if constexpr (kDig) far = max(far, (__float_as_uint(b.x[r].fv) << 1) + win_off);
+        }
+        if (full && __all(differ == 0 && (!kDig || far < win_span))) {
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const int s = (int)home[r] * REP + copy;
+            if constexpr (kDig) {
+              const uint32_t fb = __float_as_uint(b.x[r].fv);
+              at_add<true>(&cnt[s], 1u);
+              add_window(s, fb, (fb << 1) + win_off);
+            } else {
+              apply<G, true>(&cnt[s], &val[kVal ? s : 0], nullptr, nullptr, (int64_t)b.x[r].iv, b.x[r].fv);
             }
-          } else {
-            apply<G, true>(&cnt[s], &val[kVal ? s : 0], &dig[0], &flags[0], (int64_t)b.x[r].iv, fv);
           }
-        } else {
-          spill |= 1u << r;
+          return;
         }
       }
-      // rows for the global table: rare, so one copy of the code for all of
-      // the batch's rows, which reads them again
-      while (spill) {
-        const uint32_t r = (uint32_t)__builtin_ctz(spill);
-        spill &= spill - 1;
-        Row x;
-        load_row(x, base, row_at((int)r));
-        const int64_t g = global_slot(t, (int64_t)x.k, key_hash<KD>(x.k));
-        if (g >= 0) apply_global<G>(t, g, (int64_t)x.iv, x.fv);
+      // Somewhere a key is not at home: the second probes, four rows' in flight
+      // at once.
+#pragma unroll
+      for (int q = 0; q < R; q += 4) {
+        KT cur2[4];
+        uint32_t second[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          second[c] = home_of(next_probe(key_hash<KD>(b.x[q + c].k)), 0);
+          cur2[c] = key[second[c]];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          __asm__ volatile("" : "+v"(cur2[c]));
+          const bool home_hit = cur[q + c] == b.x[q + c].k;
+          home[q + c] = home_hit ? home[q + c] : second[c];
+          cur[q + c] = home_hit ? cur[q + c] : cur2[c];
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const KT k = b.x[r].k;
+        bool mine = full || row_at(r) < left;
+        if constexpr (SUB) mine = mine && ((key_hash<KD>(k) >> sub_shift) & sub_mask) == sub;
+        const bool hit = cur[r] == k && k != kMark && mine;
+        const int s = (int)home[r] * REP + copy;
+        bool miss = mine && !hit;
+        if constexpr (kDig) {
+          const uint32_t fb = __float_as_uint(b.x[r].fv), u = (fb << 1) + win_off;
+          const bool in = u < win_span, zero = pass == 0 && b.x[r].fv == 0.0f;
+          const bool hot = hit && (in || zero);
+          if (hot) {
+            at_add<true>(&cnt[s], 1u);
+            if (in) add_window(s, fb, u);
+          }
+          miss = mine && !hot && (in || u >= out_from);
+        } else {
+          if (hit) apply<G, true>(&cnt[s], &val[kVal ? s : 0], nullptr, nullptr, (int64_t)b.x[r].iv, b.x[r].fv);
+        }
+        rest = rest + rest + (miss ? 1u : 0u);
+      }
+      while (rest) {
+        const int r = R - 1 - __builtin_ctz(rest);
+        rest &= rest - 1;
+        Row x = b.x[0];
+#pragma unroll
+        for (int j = 1; j < R; ++j) {  // field by field: a struct would go through scratch memory
+          x.k = r == j ? b.x[j].k : x.k;
+          x.iv = r == j ? b.x[j].iv : x.iv;
+          x.fv = r == j ? b.x[j].fv : x.fv;
+        }
+        const uint32_t h = key_hash<KD>(x.k), fb = __float_as_uint(x.fv), u = (fb << 1) + win_off;
+        const bool nonfinite = (fb << 1) >= 0xFF000000u;
+        const bool in = !kDig || u < win_span || x.fv == 0.0f || nonfinite;  // an LDS slot can take it
+        const int slot = in ? slot_of(x.k, h, skip) : -1;
+        if (slot >= 0) {
+          const int s = slot * REP + copy;
+          if constexpr (kDig) {
+            at_add<true>(&cnt[s], 1u);
+            if (u < win_span) add_window(s, fb, u);
+            else if (nonfinite)
+              at_or<true>(reinterpret_cast<int*>(&flags[slot >> 3]),
+                          (__builtin_isnan(x.fv) ? 1 : (x.fv > 0 ? 2 : 4)) << (4 * (slot & 7)));
+          } else {
+            apply<G, true>(&cnt[s], &val[kVal ? s : 0], nullptr, nullptr, (int64_t)x.iv, x.fv);
+          }
+        } else {
+          const int64_t g = global_slot(t_, (int64_t)x.k, h);
+          if (g >= 0) apply_global<G>(t_, g, (int64_t)x.iv, x.fv);
+        }
       }
     };
     int64_t b = first;
@@ -766,7 +854,7 @@ struct LdsTable {
         const int64_t next = b + tile_step;
         const bool more = next + TR <= last;
         Batch B;
-        if (more) load(B, next);
+        load(B, more ? next : b);  // never behind a branch: the fold would wait for it (the last one is not used)
         fold(A, b, true, 0);
         b = next;
         if (!more) break;
@@ -779,7 +867,7 @@ struct LdsTable {
     }
   }
 
-  __device__ __forceinline__ void flush(const Table& t) {
+  __device__ __forceinline__ void flush(const Table& t, uint32_t win_base) {
     // Every workgroup's table holds its keys in about the same slots (same
     // hash), so flushing all tables in slot order would have every workgroup
     // update the same global slots at the same moment, and device-scope
@@ -792,7 +880,7 @@ struct LdsTable {
       const KT k = e < L ? key[e] : kMark;
       uint64_t c = 0;
       for (int r = 0; r < REP; ++r) c += cnt[e * REP + r];
-      if (e < L ? k == kMark : c == 0) continue;
+      if (c == 0) continue;
       const int64_t g = global_slot(t, (int64_t)k, key_hash<KD>(k));
       if (g < 0) continue;
       atomicAdd(reinterpret_cast<unsigned long long*>(t.cnt + g), (unsigned long long)c);
@@ -809,13 +897,26 @@ struct LdsTable {
         if constexpr (G == G_MAX_INT || G == G_MAX_F32) atomicMax(reinterpret_cast<long long*>(t.val + g), (long long)v);
       }
       if constexpr (kDig) {
-        int32_t f = 0;
-        for (int r = 0; r < REP; ++r) f |= flags[e * REP + r];
+        const int32_t f = (int32_t)((flags[e >> 3] >> (4 * (e & 7))) & 7u);
         if (f) atomicOr(t.flags + g, f);
-        for (int d = 0; d < kLdsDigits; ++d) {
-          uint64_t v = 0;  // digits add mod 2^64, as in the global table
-          for (int r = 0; r < REP; ++r) v += (uint64_t)dig[(e * REP + r) * kLdsDigits + d];
-          if (v) atomicAdd(reinterpret_cast<unsigned long long*>(t.dig + g * kDigits + d + 1), (unsigned long long)v);
+        // The windows' total, a whole number of 2^(base - 150), as 32-bit digits
+        // from digit (base - 1) / 32 on: three unsigned ones and a signed top one.
+        // Digit 8 takes all there is from it on (floats end at 2^128, which
+        // keeps that below 2^53 over 2^31 rows).
+        __int128 sum = 0;
+        for (int w = kWindows - 1; w >= 0; --w) {
+          uint64_t v = 0;  // the copies' rows are at most kMaxTableRows in all
+          for (int r = 0; r < REP; ++r) v += (uint64_t)win[w * E + e * REP + r];
+          sum = sum * (1 << kWinOctaves) + (int64_t)v;
+        }
+        const int d = ((int)win_base - 1) >> 5;
+        sum *= (int64_t)1 << (((int)win_base - 1) & 31);
+        unsigned long long* dig = reinterpret_cast<unsigned long long*>(t.dig + g * kDigits + d);
+        for (int i = 0; i < 4; ++i) {
+          const bool top = i == 3 || d + i == kDigits - 1;
+          const int64_t v = top ? (int64_t)(sum >> (32 * i)) : (int64_t)(uint32_t)(sum >> (32 * i));
+          if (v) atomicAdd(dig + i, (unsigned long long)v);
+          if (top) break;
         }
       }
     }
@@ -829,38 +930,49 @@ struct LdsTable {
 // addresses 6).  A small table whose slots carry kFewCopies copies of the
 // accumulators (lane l updates copy l % kFewCopies) cuts the meetings by that
 // factor, and is cleared and flushed in one step.  2^28 rows, int32 keys,
-// full table -> this one: int64 SUM 1056 -> 492 us at 2 groups, 499 -> 495 at
-// 16; COUNT 545 -> 183 and 210 -> 182; float SUM 1580 -> 430 and 620 -> 370.
+// full table -> this one: int64 SUM 1056 -> 478 us at 2 groups, 499 -> 478 at
+// 16; COUNT 545 -> 163 and 210 -> 163; float SUM 1580 -> 348 and 620 -> 343.
 constexpr int kFewGroups = 32;
 constexpr int kFewCopies = 8;
 constexpr int kFewSlots = 128;
+
+__device__ __forceinline__ FloatWindows windows_of(const Table& t) {
+  FloatWindows f;
+  f.first = t.state[4];
+  f.passes = t.state[5];
+  return f;
+}
 
 // Direct path: every workgroup sweeps its share of the rows' tiles into one
 // LDS table, in 2^sub_bits passes (each taking the keys of one sub-partition:
 // the top bits of the key's hash) when the groups need more than one table.
 // Bound by HBM where a row is 12 bytes or more: 2^28 rows, int32 keys, 1024
-// dense keys: int64 SUM 563 -> 499 us (6.45 TB/s), COUNT 367 -> 207 (5.2),
-// float SUM 923 -> 428 (5.0); the loads alone run at 6.6 TB/s.
-// The few-groups table leaves room for two workgroups per CU where the fold
-// fits 64 registers, which rows of up to two words do (8 waves per SIMD
-// instead of 4 hide the LDS and memory latency; wider rows keep 8 rows in
-// flight per thread instead: int64 SUM of 16 groups 495 us against 519).
+// dense keys: int64 SUM 563 -> 490 us (6.5 TB/s), COUNT 367 -> 177 (6.0),
+// float SUM 923 -> 380 (5.7); the loads alone run at 6.6 TB/s.
+// Two workgroups per CU, which the few-groups table would leave room for, ran
+// slower: half the registers are half the rows in flight per thread (16
+// groups: COUNT 177 us against 161, float SUM 367 against 345).
 template <int KD, int VD, int G, bool FEW, bool SUB>
-__global__ void __attribute__((amdgpu_flat_work_group_size(1, kDirectThreads), amdgpu_waves_per_eu(FEW && row_words<KD, VD, G>() <= 2 ? 8 : 1)))
+__global__ void __launch_bounds__(kDirectThreads)
 gb_aggregate_kernel(Args a) {
   
   __shared__ LdsTable<G, KD, FEW ? kFewSlots : lds_slots<G, KD>(), kDirectThreads, FEW ? kFewCopies : 1> tab;
   constexpr int TR = decltype(tab)::template tile_rows_of<VD>() * kDirectThreads;
   const uint32_t sub_mask = (1u << a.pt.sub_bits) - 1u;
   const uint32_t sub_shift = a.pt.sub_bits ? (uint32_t)(32 - a.pt.sub_bits) : 0u;
+  FloatWindows fw;
+  if constexpr (G == G_SUM_F32) fw = windows_of(a.t);
   for (uint32_t sub = 0; sub <= sub_mask; ++sub) {
-    tab.clear();
-    __syncthreads();
-    tab.template fold_rows<VD, false, SUB>(a.t, a.keys, a.vals, (int64_t)blockIdx.x * TR, a.n,
-                                           (int64_t)gridDim.x * TR, (uint32_t)a.pt.sub_bits, sub_shift, sub_mask, sub);
-    __syncthreads();
-    tab.flush(a.t);
-    __syncthreads();
+    for (int pass = 0; pass < fw.passes; ++pass) {
+      tab.clear((uint32_t)a.pt.sub_bits);
+      __syncthreads();
+      tab.template fold_rows<VD, false, SUB>(a.t, a.keys, a.vals, (int64_t)blockIdx.x * TR, a.n,
+                                             (int64_t)gridDim.x * TR, (uint32_t)a.pt.sub_bits, sub_shift, sub_mask, sub,
+                                             fw, pass);
+      __syncthreads();
+      tab.flush(a.t, fw.base(pass));
+      __syncthreads();
+    }
   }
 }
 
@@ -876,6 +988,8 @@ template <int KD, int VD, int G, bool SUB>
 __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a) {
   __shared__ LdsTable<G, KD, lds_slots<G, KD>(), kPartThreads> tab;
   constexpr int TR = decltype(tab)::template tile_rows_of<VD>() * kPartThreads;
+  FloatWindows fw;
+  if constexpr (G == G_SUM_F32) fw = windows_of(a.t);
   const int P = 1 << a.pt.bits;
   int64_t r = a.n * (int64_t)blockIdx.x / gridDim.x;
   const int64_t r1 = a.n * ((int64_t)blockIdx.x + 1) / gridDim.x;
@@ -893,20 +1007,63 @@ __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a)
     while ((int64_t)a.pt.start[p + 1] <= r) ++p;  // skip partitions that end before r
     const int64_t seg_end = std::min<int64_t>(r1, (int64_t)a.pt.start[p + 1]);
     for (uint32_t sub = 0; sub <= sub_mask; ++sub) {
-      tab.clear();
-      __syncthreads();
-      tab.template fold_rows<VD, true, SUB>(a.t, a.pt.pk, a.pt.pv, r, seg_end, TR, (uint32_t)(a.pt.bits + a.pt.sub_bits),
-                                            sub_shift, sub_mask, sub);
-      __syncthreads();
-      tab.flush(a.t);
-      __syncthreads();
+      for (int pass = 0; pass < fw.passes; ++pass) {
+        tab.clear((uint32_t)(a.pt.bits + a.pt.sub_bits));
+        __syncthreads();
+        tab.template fold_rows<VD, true, SUB>(a.t, a.pt.pk, a.pt.pv, r, seg_end, TR,
+                                              (uint32_t)(a.pt.bits + a.pt.sub_bits), sub_shift, sub_mask, sub, fw, pass);
+        __syncthreads();
+        tab.flush(a.t, fw.base(pass));
+        __syncthreads();
+      }
     }
     r = seg_end;
   }
 }
 
+// Where the float-sum windows of a run go, from kSampleRows rows spread evenly
+// over it: the sampled exponents, with most of the slack below them (sums of
+// small parts) and up to 2^8 of room above.  More than kWinSpan exponents take
+// several passes over the rows; a row outside all of them goes to the global
+// table.  One workgroup of the init kernel reads the sample while the others
+// clear the table (every aggregation workgroup reading one of its own took
+// 20 us of page-table misses at 2^28 rows).
+constexpr int kSampleRows = 16 * kThreads;
+__device__ __forceinline__ void place_windows(const Args& a) {
+  __shared__ int range[2];
+  if (threadIdx.x == 0) {
+    range[0] = 255;
+    range[1] = 0;
+  }
+  __syncthreads();
+  int emin = 255, emax = 0;
+  if (a.n > 0) {
+#pragma unroll
+    for (int i = 0; i < kSampleRows / kThreads; ++i) {
+      const uint64_t row = (uint64_t)a.n * (uint32_t)(i * kThreads + threadIdx.x) / (uint32_t)kSampleRows;
+      const int e = (int)((static_cast<const uint32_t*>(a.vals)[row] >> 23) & 0xFFu);
+      const bool placed = e != 0 && e != 255;  // zeros, subnormals and non-finite rows do not place a window
+      emin = min(emin, placed ? e : 255);
+      emax = max(emax, placed ? e : 0);
+    }
+  }
+  atomicMin(&range[0], emin);
+  atomicMax(&range[1], emax);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    emin = range[0];
+    emax = range[1];
+    if (emin > emax) emin = emax = 127;
+    const int passes = (emax - emin + kWinSpan) / kWinSpan;
+    const int slack = passes * kWinSpan - (emax - emin + 1);
+    a.t.state[4] = max(1, emax + min(slack / 2, 8) - passes * kWinSpan + 1);
+    a.t.state[5] = passes;
+  }
+}
+
 template <int G>
-__global__ void __launch_bounds__(kThreads) gb_init_kernel(Table t) {
+__global__ void __launch_bounds__(kThreads) gb_init_kernel(Args a) {
+  const Table& t = a.t;
   const int64_t stride = (int64_t)gridDim.x * kThreads;
   for (int64_t s = (int64_t)blockIdx.x * kThreads + threadIdx.x; s <= t.cap; s += stride) {
     t.key[s] = s == t.cap ? INT64_MIN : kEmpty;
@@ -917,6 +1074,8 @@ __global__ void __launch_bounds__(kThreads) gb_init_kernel(Table t) {
       for (int d = 0; d < kDigits; ++d) t.dig[s * kDigits + d] = 0;
   }
   if (blockIdx.x == 0 && threadIdx.x < 4) t.state[threadIdx.x] = 0;
+  if constexpr (G == G_SUM_F32)
+    if (blockIdx.x == gridDim.x - 1) place_windows(a);
 }
 
 // Workgroup w writes the used slots of its contiguous slot range: it counts
@@ -1252,11 +1411,12 @@ int agg_groupby_run(agg_groupby_t p, const void* keys, const void* vals, int64_t
   a.is_avg = p->op == AGG_AVG;
   a.op = p->op;
   const int64_t table_grid = std::max<int64_t>(1, std::min<int64_t>(ceil_div(p->t.cap + 1, kThreads), (int64_t)cu * 8));
-  rc = launch(init_kernel(p->gop), (int)table_grid, kThreads, &a.t, stream);
+  rc = launch(init_kernel(p->gop), (int)table_grid, kThreads, &a, stream);
   if (rc != AGG_OK) return rc;
   if (n > 0 && p->pt.bits == 0) {
     const int64_t grid =
-        std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, kDirectThreads * 16), (int64_t)cu * p->agg_blocks));
+        std::max<int64_t>(ceil_div(n, kMaxTableRows),
+                          std::min<int64_t>(ceil_div(n, kDirectThreads * 16), (int64_t)cu * p->agg_blocks));
     rc = launch(agg_kernel(p->key_dtype, p->val_dtype, p->gop, p->path), (int)grid, kDirectThreads, &a, stream);
     if (rc != AGG_OK) return rc;
   } else if (n > 0) {
@@ -1285,7 +1445,8 @@ int agg_groupby_run(agg_groupby_t p, const void* keys, const void* vals, int64_t
       if ((rc = launch_lds(scat, a.pt.g1, kTileThreads, 0, &a, stream)) != AGG_OK)
         return rc;
       const int64_t agrid =
-          std::max<int64_t>(1, std::min<int64_t>(ceil_div(m, kPartThreads * 8), (int64_t)cu * p->agg_blocks));
+          std::max<int64_t>(ceil_div(m, kMaxTableRows),
+                            std::min<int64_t>(ceil_div(m, kPartThreads * 8), (int64_t)cu * p->agg_blocks));
       if ((rc = launch_lds(aggk, agrid, kPartThreads, 0, &a, stream)) != AGG_OK) return rc;
     }
     a.keys = keys;

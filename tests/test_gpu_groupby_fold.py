@@ -63,3 +63,41 @@ def test_regular_key_sets(agg, kdt, first, stride):
             for declared in (groups, 3_000_000):
                 run(agg, keys, make_vals(n, vdt, seed=groups), op, declared,
                     f"{kdt} {first}+{stride}i groups={groups} declared={declared} {vdt} {op}")
+
+
+def window_values(kind, n, r):
+    """Float columns that place an LDS table's windows differently (48 exponents
+    a pass, placed by a sample of the column)."""
+    def spread(lo, hi):
+        return (np.where(r.random(n) < 0.5, -1.0, 1.0) * np.ldexp(1.0 + r.random(n), r.integers(lo, hi + 1, size=n)))
+    v = {
+        "one exponent": lambda: 1.0 + r.random(n),
+        "48 exponents": lambda: spread(-20, 27),
+        "49 exponents": lambda: spread(-20, 28),
+        "five passes": lambda: spread(-120, 100),
+        "top": lambda: spread(120, 127),
+        "bottom": lambda: spread(-126, -120),
+        "subnormal": lambda: r.integers(-1000, 1000, size=n) * 2.0**-149,
+        "zeros": lambda: np.where(r.random(n) < 0.5, 0.0, -0.0),
+        "mostly zeros": lambda: np.where(r.random(n) < 0.9, 0.0, r.standard_normal(n)),
+        "non-finite": lambda: np.where(r.random(n) < 0.1, r.choice([np.nan, np.inf, -np.inf], size=n), r.standard_normal(n)),
+        # the sample of 4096 rows spread over the column misses these
+        "rare outliers": lambda: np.where(np.arange(n) % 9973 == 17, r.choice([1e38, -1e-38, 1e-44], size=n), r.random(n)),
+        "ascending": lambda: np.sort(np.abs(spread(-60, 60))),
+    }[kind]()
+    with np.errstate(over="ignore"):
+        x = v.astype(np.float32)
+    return x if kind == "non-finite" else np.where(np.isfinite(x), x, np.float32(3.4e38))
+
+
+@pytest.mark.parametrize("kind", ["one exponent", "48 exponents", "49 exponents", "five passes", "top", "bottom",
+                                  "subnormal", "zeros", "mostly zeros", "non-finite", "rare outliers", "ascending"])
+def test_float_windows(agg, kind):
+    """Float sums of every spread of exponents, exact through every path."""
+    n = 150_001
+    r = np.random.default_rng(len(kind))
+    vals = window_values(kind, n, r)
+    for kdt, groups in (("i32", 3), ("i64", 20), ("i32", 1500), ("i64", 3000), ("i32", 20_000)):
+        keys = r.integers(0, groups, size=n).astype(NP[kdt])
+        for op, declared in (("sum", groups), ("avg", groups), ("sum", 6_000_000)):
+            run(agg, keys, vals, op, declared, f"{kind} {kdt} groups={groups} declared={declared} {op}")
