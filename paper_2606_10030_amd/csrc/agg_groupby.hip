@@ -47,32 +47,29 @@ constexpr int64_t kEmpty = INT64_MIN;
 constexpr int kThreads = 256;
 constexpr int kLdsProbes = 16;
 constexpr int kGlobalProbes = 32;     // hashed probes of the global table, then linear ones
-constexpr int kAggRows = 8;           // rows whose loads a thread keeps in flight
 constexpr int kMaxPartBits = 14;      // at most 16384 (sub-)partitions
 constexpr int kMinPartBits = 5;       // at least 32
 // Rows are partitioned in chunks of up to 2^28: every chunk ends with each
 // aggregation workgroup flushing the groups it holds, so fewer, larger
 // chunks flush less (the staging area holds one chunk: up to 4 GiB).
 constexpr int64_t kChunkRows = (int64_t)1 << 28;
-constexpr int kMaxHistWg = 1024;                   // histogram / scatter workgroups per chunk
+constexpr int kMaxHistWg = 512;                    // histogram / scatter workgroups per chunk
 constexpr int64_t kMinHistRows = 8192;             // rows per such workgroup, at least
 constexpr int kScanThreads = 1024;
 constexpr int kTileThreads = 1024;    // scatter: rows staged in LDS per tile
 constexpr int kTileMaxBits = 11;      // scatter into at most 2048 partitions
-// Rows per scatter tile: as many as LDS holds next to the per-partition
-// counters (at most 152 KiB in all), 16 per thread at most (registers).
-// Longer tiles give longer runs per partition, so fewer partial cache lines.
-// With values, LDS holds keys and values only and the store phase hashes the
-// key again; a tile of keys only (COUNT) keeps each row's partition in LDS,
-// and below 128 partitions, where runs are long anyway, takes 8192 rows
-// (measured: 4% faster there, 3-9% slower above).
-template <int KD, int VD, bool HASV, bool BIG>
+// Rows per tile of the scatter without carried rows: as many as LDS holds next
+// to the per-partition counters (at most 152 KiB in all), 16 per thread at most
+// (registers).  Longer tiles give longer runs per partition, so fewer partial
+// cache lines.  With values, LDS holds keys and values only and the store phase
+// hashes the key again; a tile of keys only (COUNT) keeps each row's partition
+// in LDS.
+template <int KD, int VD, bool HASV>
 constexpr int tile_rows() {
-  return !HASV ? (!BIG ? 8192 : KD == AGG_I32 ? 16384 : 12288)
+  return !HASV ? (KD == AGG_I32 ? 16384 : 12288)
                : (KD == AGG_I32 ? 4 : 8) + (VD == AGG_I64 ? 8 : 4) == 8 ? 16384
                : (KD == AGG_I32 ? 4 : 8) + (VD == AGG_I64 ? 8 : 4) == 12 ? 10240 : 8192;
 }
-constexpr int kBigTileBits = 7;  // key-only tiles grow from 128 partitions on
 // A staged row with a value is stored as one record, the key's 32-bit words
 // then the value's (8, 12 or 16 bytes, over the keys' and the values'
 // staging regions together), so a partition's run in a scatter tile is one
@@ -308,52 +305,66 @@ __device__ __forceinline__ void apply_global(const Table& t, int64_t s, int64_t 
   apply<G, false>(t.cnt + s, t.val + s, t.dig + (G == G_SUM_F32 ? s * kDigits : 0), t.flags + s, iv, fv);
 }
 
+// V consecutive items of a column at base + tid * V, as one vector load (8 or
+// 16 bytes) at any item alignment.  NT: non-temporal (a row is read once).
+template <int V, bool NT, typename T>
+__device__ __forceinline__ void load_items(T (&x)[V], const T* base, uint32_t tid) {
+  typedef uint32_t vec __attribute__((ext_vector_type(V * sizeof(T) / 4), aligned(4)));
+  static_assert(sizeof(vec) == sizeof(x), "a vector of whole items");
+  const vec* p = reinterpret_cast<const vec*>(base) + tid;
+  vec v;
+  if constexpr (NT) v = __builtin_nontemporal_load(p);
+  else v = *p;
+  __builtin_memcpy(x, &v, sizeof(x));
+}
+
 // ---- histogram / prefix sums / scatter of the partitioned path ----
 
+// Bound by HBM: every key is read once, in 16-byte vectors, the next tile's
+// loads in flight while a tile is counted.  2^28 keys: int32 204 -> 160 us (6.7 TB/s),
+// int64 383 -> 325 (6.6).
+constexpr int kHistThreads = 512;
 template <int KD>
-__global__ void __launch_bounds__(kThreads) gb_hist_kernel(Args a) {
-  extern __shared__ uint32_t h[];
+__global__ void __launch_bounds__(kHistThreads) gb_hist_kernel(Args a) {
+  using KT = typename std::conditional<KD == AGG_I32, int32_t, int64_t>::type;
+  constexpr int NT = kHistThreads, V = 16 / (int)sizeof(KT), R = 4 * V, TR = R * NT;
+  __shared__ uint32_t h[1 << kTileMaxBits];
   const int P = 1 << a.pt.bits;
-  for (int e = threadIdx.x; e < P; e += kThreads) h[e] = 0;
+  for (int e = threadIdx.x; e < P; e += NT) h[e] = 0;
   __syncthreads();
   const int64_t lo = (int64_t)blockIdx.x * a.pt.rows_per_wg;
   const int64_t hi = std::min<int64_t>(lo + a.pt.rows_per_wg, a.n);
-  using KT = typename std::conditional<KD == AGG_I32, int32_t, int64_t>::type;
-  // rows base + r * kThreads: one 64-bit clamp per batch, 32-bit offsets per row
-  auto load = [&](KT* kk, int64_t base) {
-    const int64_t b0 = std::min<int64_t>(base, hi - 1);
-    const uint32_t room = (uint32_t)std::min<int64_t>(hi - 1 - b0, (int64_t)kAggRows * kThreads);
-#pragma unroll
-    for (int r = 0; r < kAggRows; ++r)
-      kk[r] = (static_cast<const KT*>(a.keys) + b0)[std::min<uint32_t>((uint32_t)(r * kThreads), room)];
+  const KT* keys = static_cast<const KT*>(a.keys);
+  struct Tile {
+    KT k[R];
   };
-  auto count = [&](KT* kk, int64_t base) {
-    const uint32_t left = (uint32_t)std::max<int64_t>(0, std::min<int64_t>(hi - base, (int64_t)kAggRows * kThreads));
+  auto load = [&](Tile& t, int64_t base) {
 #pragma unroll
-    for (int r = 0; r < kAggRows; ++r) __asm__ volatile("" : "+v"(kk[r]));
+    for (int q = 0; q < R; q += V) {
+      KT kk[V];
+      load_items<V, true>(kk, keys + base + q * NT, threadIdx.x);
 #pragma unroll
-    for (int r = 0; r < kAggRows; ++r)
-      if ((uint32_t)(r * kThreads) < left) atomicAdd(&h[part_of(key_hash<KD>(kk[r]), a.pt.bits)], 1u);
+      for (int c = 0; c < V; ++c) t.k[q + c] = kk[c];
+    }
   };
-  // two batches alternate, so the next batch's loads are in flight while this
-  // one is counted (2^28 rows: 1-3% off the partitioned paths)
-  const int64_t first = lo + threadIdx.x, adv = (int64_t)kThreads * kAggRows;
-  if (first < hi) {
-    KT A[kAggRows], B[kAggRows];
-    load(A, first);
-    for (int64_t base = first;;) {
-      load(B, base + adv);
-      count(A, base);
-      base += adv;
-      if (base >= hi) break;
-      load(A, base + adv);
-      count(B, base);
-      base += adv;
-      if (base >= hi) break;
+  int64_t b = lo;
+  if (b + TR <= hi) {
+    Tile A;
+    load(A, b);
+    for (;;) {
+      const bool more = b + 2 * TR <= hi;
+      Tile B;
+      load(B, more ? b + TR : b);  // never behind a branch: the count would wait for it
+#pragma unroll
+      for (int r = 0; r < R; ++r) atomicAdd(&h[part_of(key_hash<KD>(A.k[r]), a.pt.bits)], 1u);
+      b += TR;
+      if (!more) break;
+      A = B;
     }
   }
+  for (b += threadIdx.x; b < hi; b += NT) atomicAdd(&h[part_of(key_hash<KD>(keys[b]), a.pt.bits)], 1u);
   __syncthreads();
-  for (int e = threadIdx.x; e < P; e += kThreads) a.pt.hist[(int64_t)e * a.pt.g1 + blockIdx.x] = h[e];
+  for (int e = threadIdx.x; e < P; e += NT) a.pt.hist[(int64_t)e * a.pt.g1 + blockIdx.x] = h[e];
 }
 
 // One wave per partition: exclusive prefix of its per-workgroup counts, in place.
@@ -420,11 +431,11 @@ __global__ void __launch_bounds__(kScanThreads) gb_scan_tot_kernel(Args a) {
 // rows of this workgroup.  Each tile of rows is counting-sorted by partition
 // in LDS first, so the rows of one partition leave as one contiguous run
 // (coalesced stores) instead of one scattered store per row.
-template <int KD, int VD, bool HASV, bool BIG>
+template <int KD, int VD, bool HASV>
 __global__ void __launch_bounds__(kTileThreads) gb_scatter_tiled_kernel(Args a) {
   using KT = typename std::conditional<KD == AGG_I32, int32_t, int64_t>::type;
   using VT = typename std::conditional<VD == AGG_I64, int64_t, uint32_t>::type;
-  constexpr int TR = tile_rows<KD, VD, HASV, BIG>();
+  constexpr int TR = tile_rows<KD, VD, HASV>();
   constexpr int R = TR / kTileThreads;
   constexpr int PM = 1 << kTileMaxBits;
   __shared__ KT skey[TR];
@@ -517,17 +528,181 @@ __global__ void __launch_bounds__(kTileThreads) gb_scatter_tiled_kernel(Args a) 
   }
 }
 
-// ---- aggregation into LDS tables, flushed into the global table ----
+// The same scatter, writing whole 64-byte pieces only, for up to PMAX
+// partitions.  A tile's run for one partition is some tens of rows, and the
+// incomplete lines at its ends leave L2 before the next tile completes them;
+// a partial write costs the memory far more than its bytes (2^28 rows of 12
+// bytes, 256 partitions, stores of the same volume: 1636 us with unaligned
+// runs, 1382 with aligned ones).  So a partition's run ends at a multiple of U
+// rows (64 bytes, or 192 for 12-byte rows), and the up to U - 1 rows past it
+// stay: 1024 / P threads per partition carry them in registers and put them
+// back at the head of their partition in the next tile.  2^28 rows: 12 bytes,
+// 256 partitions 1774 -> 1522 us, 32 partitions 1330 -> 1268; 16 bytes, 512
+// partitions 2626 -> 2186; 8 bytes, 512 partitions 1322 -> 1128.  (Loading the
+// next tile during the stores changed nothing: reads and writes share the
+// memory's time.)
+template <int KD, int VD, bool HASV, bool WIDE>
+struct CarryTile {
+  static constexpr int RB = (KD == AGG_I32 ? 4 : 8) + (!HASV ? 0 : VD == AGG_I64 ? 8 : 4);  // bytes of a row
+  static constexpr int U = RB == 16 ? 4 : RB == 8 ? 8 : 16;
+  static constexpr int PMAX = (U == 16 ? 256 : 512) << (WIDE ? 1 : 0);
+  // New rows per thread and tile: what LDS holds next to the carried rows.
+  static constexpr int R = RB == 4 ? (WIDE ? 24 : 32) : RB == 8 ? (WIDE ? 10 : 14) : RB == 12 ? (WIDE ? 4 : 8) : WIDE ? 4 : 6;
+  static constexpr int CR = ((U - 1) * PMAX + kTileThreads - 1) / kTileThreads;  // carried rows per thread
+  static constexpr int CAP = R * kTileThreads + (U - 1) * PMAX;
+};
 
-// V consecutive items of a column at base + tid * V, as one vector load (8 or
-// 16 bytes) at any item alignment; non-temporal, since a row is read once.
-template <int V, typename T>
-__device__ __forceinline__ void load_items(T (&x)[V], const T* base, uint32_t tid) {
-  typedef uint32_t vec __attribute__((ext_vector_type(V * sizeof(T) / 4), aligned(4)));
-  static_assert(sizeof(vec) == sizeof(x), "a vector of whole items");
-  const vec v = __builtin_nontemporal_load(reinterpret_cast<const vec*>(base) + tid);
-  __builtin_memcpy(x, &v, sizeof(x));
+template <int KD, int VD, bool HASV, bool WIDE>
+__global__ void __launch_bounds__(kTileThreads) gb_scatter_carry_kernel(Args a) {
+  using KT = typename std::conditional<KD == AGG_I32, int32_t, int64_t>::type;
+  using VT = typename std::conditional<VD == AGG_I64, int64_t, uint32_t>::type;
+  using SR = StagedRow<KD, VD>;
+  using T = CarryTile<KD, VD, HASV, WIDE>;
+  constexpr int NT = kTileThreads, R = T::R, U = T::U, TR = R * NT;
+  constexpr int V = KD == AGG_I64 || (HASV && VD == AGG_I64) || R % 4 ? 2 : 4;
+  static_assert(R % V == 0, "a thread's rows are whole vectors");
+  __shared__ KT skey[T::CAP];
+  __shared__ VT sval[HASV ? T::CAP : 1];
+  // per partition: rows of the tile (the carried ones first); their first
+  // place in the tile; the place where the stored ones end, and in the upper
+  // bits how many are left; where place j is stored: delta + j; rows stored so far
+  __shared__ uint32_t tcnt[T::PMAX], toff[T::PMAX], tend[T::PMAX], delta[T::PMAX], cur[T::PMAX], total;
+  constexpr int kEndBits = 20;
+  const int P = 1 << a.pt.bits;
+  const uint32_t tid = threadIdx.x;
+  // this thread's carried rows are rows lane, lane + step, ... of partition mine
+  const uint32_t step = (uint32_t)NT >> a.pt.bits, mine = tid / step, lane = tid % step;
+  for (int e = tid; e < P; e += NT) {
+    cur[e] = a.pt.start[e] + a.pt.hist[(int64_t)e * a.pt.g1 + blockIdx.x];
+    tcnt[e] = 0;
+  }
+  __syncthreads();
+  const int64_t lo = (int64_t)blockIdx.x * a.pt.rows_per_wg;
+  const int64_t hi = std::min<int64_t>(lo + a.pt.rows_per_wg, a.n);
+  const uint32_t last_row = (uint32_t)(a.n - 1);
+  KT k[R], ck[T::CR];
+  VT v[R], cv[T::CR];
+  uint32_t pr[R];      // a row's partition in the upper half, its rank there in the lower
+  uint32_t kept = 0;   // rows carried in partition mine
+#pragma unroll
+  for (int c = 0; c < T::CR; ++c) {
+    ck[c] = 0;
+    cv[c] = 0;
+  }
+  auto row_at = [&](int r) -> uint32_t { return (uint32_t)(r / V * V * NT + r % V) + tid * V; };
+  for (int64_t t0 = lo; t0 < hi; t0 += TR) {
+    const bool full = t0 + TR <= hi;
+    const uint32_t rows = full ? (uint32_t)TR : (uint32_t)(hi - t0);
+    if (full) {
+#pragma unroll
+      for (int q = 0; q < R; q += V) {
+        KT kk[V];
+        load_items<V, !HASV>(kk, static_cast<const KT*>(a.keys) + t0 + q * NT, tid);
+#pragma unroll
+        for (int c = 0; c < V; ++c) k[q + c] = kk[c];
+        if constexpr (HASV) {
+          VT vv[V];
+          load_items<V, false>(vv, static_cast<const VT*>(a.vals) + t0 + q * NT, tid);
+#pragma unroll
+          for (int c = 0; c < V; ++c) v[q + c] = vv[c];
+        }
+      }
+    } else {  // rows past the end re-load the last row
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const uint32_t j = std::min<uint32_t>(row_at(r), rows - 1);
+        k[r] = (static_cast<const KT*>(a.keys) + t0)[j];
+        if constexpr (HASV) v[r] = (static_cast<const VT*>(a.vals) + t0)[j];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (full || row_at(r) < rows) {
+        const uint32_t q = part_of(key_hash<KD>(k[r]), a.pt.bits);
+        pr[r] = (q << 16) | atomicAdd(&tcnt[q], 1u);
+      }
+    }
+    __syncthreads();
+    if (tid < 64) {  // one wave: exclusive prefix of the tile's counts
+      const int q = (P + 63) / 64;
+      uint32_t sum = 0;
+      for (int j = 0; j < q; ++j) sum += ((int)tid * q + j < P) ? tcnt[tid * q + j] : 0u;
+      uint32_t incl = sum;
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(incl, off, 64);
+        if ((int)tid >= off) incl += y;
+      }
+      if (tid == 63) total = incl;
+      uint32_t run = incl - sum;
+      for (int j = 0; j < q; ++j) {
+        const int e = tid * q + j;
+        if (e < P) {
+          const uint32_t c = tcnt[e], at = cur[e];
+          // the last tile of the workgroup's rows keeps nothing
+          const uint32_t keep = t0 + TR < hi ? std::min<uint32_t>(c, (at + c) % U) : 0u;
+          toff[e] = run;
+          delta[e] = at - run;
+          tend[e] = (run + c - keep) | (keep << kEndBits);
+          cur[e] = at + c - keep;
+          tcnt[e] = keep;
+          run += c;
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (full || row_at(r) < rows) {
+        const uint32_t d = toff[pr[r] >> 16] + (pr[r] & 0xFFFFu);
+        skey[d] = k[r];
+        if constexpr (HASV) sval[d] = v[r];
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < T::CR; ++c) {
+      const uint32_t i = lane + (uint32_t)c * step;
+      if (i < kept) {
+        const uint32_t d = toff[mine] + i;
+        skey[d] = ck[c];
+        if constexpr (HASV) sval[d] = cv[c];
+      }
+    }
+    __syncthreads();
+    const uint32_t places = total;
+    for (uint32_t j = tid; j < places; j += NT) {
+      const KT kj = skey[j];
+      const uint32_t q = part_of(key_hash<KD>(kj), a.pt.bits);
+      if (j >= (tend[q] & ((1u << kEndBits) - 1))) continue;  // carried over
+      const uint32_t pos = std::min<uint32_t>(delta[q] + j, last_row);  // in bounds whatever the counts say
+      if constexpr (HASV) {
+        SR row;
+        const uint64_t kb = (uint64_t)(int64_t)kj, vb = (uint64_t)sval[j];
+        row.w[0] = (uint32_t)kb;
+        if constexpr (SR::KW == 2) row.w[1] = (uint32_t)(kb >> 32);
+        row.w[SR::KW] = (uint32_t)vb;
+        if constexpr (SR::VW == 2) row.w[SR::KW + 1] = (uint32_t)(vb >> 32);
+        static_cast<SR*>(a.pt.pk)[pos] = row;
+      } else {
+        static_cast<KT*>(a.pt.pk)[pos] = kj;
+      }
+    }
+    const uint32_t end = tend[mine];
+    kept = end >> kEndBits;
+#pragma unroll
+    for (int c = 0; c < T::CR; ++c) {
+      const uint32_t i = lane + (uint32_t)c * step;
+      if (i < kept) {
+        const uint32_t d = (end & ((1u << kEndBits) - 1)) + i;
+        ck[c] = skey[d];
+        if constexpr (HASV) cv[c] = sval[d];
+      }
+    }
+    // no barrier: the next tile's ranks touch only tcnt, which this phase does
+    // not read, and everything else changes past the next two barriers
+  }
 }
+
+// ---- aggregation into LDS tables, flushed into the global table ----
 
 // 32-bit words of a row's key and value.
 template <int KD, int VD, int G>
@@ -698,7 +873,7 @@ struct LdsTable {
 #pragma unroll
         for (int q = 0; q < R; q += V) {
           KT kk[V];
-          load_items(kk, static_cast<const KT*>(keys) + base + q * NT, tid);
+          load_items<V, true>(kk, static_cast<const KT*>(keys) + base + q * NT, tid);
 #pragma unroll
           for (int c = 0; c < V; ++c) {
             b.x[q + c].k = kk[c];
@@ -707,7 +882,7 @@ struct LdsTable {
           }
           if constexpr (G != G_COUNT) {
             IVT vv[V];
-            load_items(vv, static_cast<const IVT*>(vals) + base + q * NT, tid);
+            load_items<V, true>(vv, static_cast<const IVT*>(vals) + base + q * NT, tid);
 #pragma unroll
             for (int c = 0; c < V; ++c) {
               if constexpr (VD == AGG_F32) b.x[q + c].fv = __int_as_float(vv[c]);
@@ -1215,13 +1390,23 @@ const void* agg_kernel(int32_t kd, int32_t vd, int g, int path) {
   return kd == AGG_I32 ? agg_kernel_path<AGG_I32>(vd, g, path) : agg_kernel_path<AGG_I64>(vd, g, path);
 }
 
+template <int KD, int VD, bool HASV>
+const void* scatter_row(int bits) {
+  if ((1 << bits) <= CarryTile<KD, VD, HASV, false>::PMAX)
+    return reinterpret_cast<const void*>(&gb_scatter_carry_kernel<KD, VD, HASV, false>);
+  // Twice as many partitions still gain where a row is 8 or 16 bytes (1577 ->
+  // 1391 us and 2972 -> 2630 at 1024), but not at 12, whose carried rows leave
+  // too little of LDS to new ones (2046 against 2066 at 512).
+  using W = CarryTile<KD, VD, HASV, true>;
+  if constexpr (W::RB != 12)
+    if ((1 << bits) <= W::PMAX) return reinterpret_cast<const void*>(&gb_scatter_carry_kernel<KD, VD, HASV, true>);
+  return reinterpret_cast<const void*>(&gb_scatter_tiled_kernel<KD, VD, HASV>);
+}
+
 template <int KD>
 const void* scatter_kd(int32_t vd, bool hasv, int bits) {
-  if (!hasv)
-    return bits >= kBigTileBits ? reinterpret_cast<const void*>(&gb_scatter_tiled_kernel<KD, AGG_I32, false, true>)
-                                : reinterpret_cast<const void*>(&gb_scatter_tiled_kernel<KD, AGG_I32, false, false>);
-  if (vd == AGG_I64) return reinterpret_cast<const void*>(&gb_scatter_tiled_kernel<KD, AGG_I64, true, true>);
-  return reinterpret_cast<const void*>(&gb_scatter_tiled_kernel<KD, AGG_I32, true, true>);  // 4-byte values move as bits
+  if (!hasv) return scatter_row<KD, AGG_I32, false>(bits);
+  return vd == AGG_I64 ? scatter_row<KD, AGG_I64, true>(bits) : scatter_row<KD, AGG_I32, true>(bits);  // 4-byte values move as bits
 }
 
 const void* init_kernel(int g) {
@@ -1421,7 +1606,6 @@ int agg_groupby_run(agg_groupby_t p, const void* keys, const void* vals, int64_t
     if (rc != AGG_OK) return rc;
   } else if (n > 0) {
     const int64_t P = (int64_t)1 << p->pt.bits;
-    const size_t lds = (size_t)P * 4;
     const bool hasv = p->op != AGG_COUNT;
     const void* hist = p->key_dtype == AGG_I32 ? reinterpret_cast<const void*>(&gb_hist_kernel<AGG_I32>)
                                                : reinterpret_cast<const void*>(&gb_hist_kernel<AGG_I64>);
@@ -1435,7 +1619,7 @@ int agg_groupby_run(agg_groupby_t p, const void* keys, const void* vals, int64_t
       a.n = m;
       a.pt.g1 = (int)std::min<int64_t>(kMaxHistWg, ceil_div(m, kMinHistRows));
       a.pt.rows_per_wg = ceil_div(m, a.pt.g1);
-      if ((rc = launch_lds(hist, a.pt.g1, kThreads, lds, &a, stream)) != AGG_OK) return rc;
+      if ((rc = launch_lds(hist, a.pt.g1, kHistThreads, 0, &a, stream)) != AGG_OK) return rc;
       if ((rc = launch_lds(reinterpret_cast<const void*>(&gb_scan_rows_kernel), ceil_div(P, kThreads / 64), kThreads,
                            0, &a, stream)) != AGG_OK)
         return rc;

@@ -101,3 +101,34 @@ def test_float_windows(agg, kind):
         keys = r.integers(0, groups, size=n).astype(NP[kdt])
         for op, declared in (("sum", groups), ("avg", groups), ("sum", 6_000_000)):
             run(agg, keys, vals, op, declared, f"{kind} {kdt} groups={groups} declared={declared} {op}")
+
+
+@pytest.mark.parametrize("kdt,vdt,op", [("i32", "i32", "count"), ("i64", "i32", "count"), ("i32", "f32", "sum"),
+                                        ("i32", "i64", "sum"), ("i64", "i32", "sum"), ("i64", "i64", "sum")])
+def test_scatter_carries_rows_between_tiles(agg, kdt, vdt, op):
+    """Partitioned plans whose workgroups scatter several tiles each (and a
+    partial last one), with partition counts on both sides of every tile form
+    (32 to 2048), uniform and skewed keys (a partition with nearly all rows,
+    and empty ones), against torch's whole-number sums per key."""
+    import torch
+    n, card = 35_000_011, 19_997
+    idx = torch.arange(n, dtype=torch.int64, device="cuda")
+    spread = (idx * 2654435761) % card
+    vals = (idx % 1001 - 500).to({"i32": torch.int32, "i64": torch.int64, "f32": torch.float32}[vdt])
+    for keys in (spread, torch.where(idx % 10 != 0, 77, spread % 3000)):
+        count = torch.bincount(keys, minlength=card)
+        want = count if op == "count" else torch.zeros(card, dtype=torch.int64, device="cuda").index_add_(0, keys, vals.long())
+        k = keys.to(torch.int32 if kdt == "i32" else torch.int64)
+        for declared in (20_000, 300_000, 900_000, 1_900_000, 3_500_000):
+            g = agg.GroupBy(kdt, vdt, op, max_n=n, max_groups=declared)
+            out = torch.empty(declared, 4, dtype=torch.int64, device="cuda")
+            ng = torch.zeros(1, dtype=torch.int64, device="cuda")
+            g.enqueue(k, vals, out, ng)
+            got = out[:int(ng.item())]
+            got = got[torch.argsort(got[:, 0])]
+            seen = torch.nonzero(count).flatten()
+            ctx = f"{kdt}/{vdt} {op} declared={declared}"
+            assert torch.equal(got[:, 0], seen), ctx
+            assert torch.equal(got[:, 3], count[seen]), ctx
+            assert torch.equal(got.view(torch.float64)[:, 2], want[seen].to(torch.float64)), ctx
+            g.close()
