@@ -199,12 +199,12 @@ bool valid_tune(const agg_tune& t) { return tune_is_valid(t); }
 
 // Launch parameters for a kind: the tuning cache, else the built-in table.
 void tune_for(int kind, int32_t src, int64_t bytes, agg_tune* t) {
-  if (!tune_cache_lookup(kind, src, bytes, t)) builtin_tune_for(kind, t);
+  if (!tune_cache_lookup(kind, src, bytes, t)) builtin_tune_for(kind, src, bytes, t);
 }
 
 // Batches mix kinds; two waves per CU with 16 loads in flight suits all of
 // the plain kinds (agg_batch_autotune refines it).
-void batch_builtin_tune(agg_tune* t) { builtin_tune_for(K_SUM_I32, t); }
+void batch_builtin_tune(agg_tune* t) { builtin_tune_for(K_SUM_I32, AGG_SRC_DEVICE, INT64_MAX, t); }
 
 namespace {
 // The checks of check_pointer on attributes already queried.
@@ -298,6 +298,7 @@ struct agg_plan_s {
   int32_t dtype = 0, op = 0, prec = 0, src = 0;
   int64_t max_n = 0;
   bool tune_given = false;
+  bool tune_builtin = false;      // neither given nor cached: each run's size picks its own
   agg_tune tune{};
   int kind = -1;
   int width = 0;
@@ -357,6 +358,14 @@ void batch_release(agg_batch_s* b) {
 }
 
 int alloc_device(void** p, size_t bytes) { return device_alloc(p, bytes); }
+
+// The launch parameters of a run over `bytes` bytes of the plan's column: its
+// own, or the built-in ones of that size (the staging ring's stay the plan's).
+agg_tune plan_tune(const agg_plan_s* p, int64_t bytes) {
+  agg_tune t = p->tune;
+  if (p->tune_builtin) builtin_tune_for(p->kind, p->src, bytes, &t);
+  return t;
+}
 
 #define RET_IF(x)            \
   do {                       \
@@ -468,10 +477,9 @@ int enqueue_resident(int kind, int32_t dtype, int32_t op, int32_t prec, const ag
   const void* combine_fn = combine_kernel_ptr(kind);
   if (!combine_fn) return AGG_E_INVALID;
   if (s.nseg > 0) {
-    const bool aligned = (reinterpret_cast<uintptr_t>(col) & 15) == 0;
     const int grid = grid_for(t, cu, s.nseg);
     const bool fused = s.nseg <= kFuseMaxPartials && grid <= cu;
-    const void* fn = scan_kernel_ptr(kind, t.unroll, t.nontemporal != 0, aligned, fused);
+    const void* fn = scan_kernel_ptr(kind, t.unroll, t.nontemporal != 0, fused);
     if (!fn) return AGG_E_INVALID;
     ScanArgs a;
     a.base = static_cast<const char*>(col);
@@ -563,11 +571,13 @@ int agg_plan(agg_plan_t* out, int32_t dtype, int32_t op, int32_t prec, int64_t m
   if (kind < 0 || max_n < 0 || max_n > kMaxItems || src < AGG_SRC_DEVICE || src > AGG_SRC_ZEROCOPY)
     return AGG_E_INVALID;
   agg_tune t;
+  bool builtin = false;
   if (tune) {
     t = *tune;
     if (!valid_tune(t)) return AGG_E_INVALID;
-  } else {
-    agg_default_tune(dtype, op, prec, max_n, src, &t);
+  } else if (!tune_cache_lookup(kind, src, max_n * width_of(dtype), &t)) {
+    builtin = true;
+    builtin_tune_for(kind, src, max_n * width_of(dtype), &t);
   }
   int dev = 0;
   RET_IF(current_device(&dev));
@@ -578,6 +588,7 @@ int agg_plan(agg_plan_t* out, int32_t dtype, int32_t op, int32_t prec, int64_t m
   p->max_n = max_n;
   p->tune = t;
   p->tune_given = tune != nullptr;
+  p->tune_builtin = builtin;
   p->kind = kind;
   p->width = width_of(dtype);
   const int rc = plan_create(p);
@@ -592,7 +603,7 @@ int agg_plan(agg_plan_t* out, int32_t dtype, int32_t op, int32_t prec, int64_t m
 int agg_plan_info(agg_plan_t plan, int64_t n, agg_shape* shape, agg_tune* tune) {
   if (!plan || n < 0 || n > plan->max_n) return AGG_E_INVALID;
   if (shape) shape_of(plan->dtype, n, shape);
-  if (tune) *tune = plan->tune;
+  if (tune) *tune = plan_tune(plan, n * plan->width);
   return AGG_OK;
 }
 
@@ -606,7 +617,7 @@ int agg_run(agg_plan_t p, const void* col, int64_t n, agg_result* out, void* str
   if (n > 0) RET_IF(check_pointer(col, bytes, p->src == AGG_SRC_ZEROCOPY ? AGG_SRC_PINNED_HOST : p->src,
                                   p->device));
   RET_IF(check_out_pointer(out, sizeof(agg_result), p->device));
-  const agg_tune& t = p->tune;
+  const agg_tune t = plan_tune(p, bytes);
   const int cu = g_dev[p->device].cu;
   const bool is_float_sum = p->dtype == AGG_F32 && (p->op == AGG_SUM || p->op == AGG_AVG);
 
@@ -629,7 +640,7 @@ int agg_run(agg_plan_t p, const void* col, int64_t n, agg_result* out, void* str
 
   // Pinned host: copy chunks of whole segments into the staging ring on the
   // copy stream while the scan of earlier chunks runs on `stream`.
-  const void* fn = scan_kernel_ptr(p->kind, t.unroll, t.nontemporal != 0, true);
+  const void* fn = scan_kernel_ptr(p->kind, t.unroll, t.nontemporal != 0);
   if (!fn) return AGG_E_INVALID;
   const int64_t cs = std::max<int64_t>(1, p->stage_bytes / s.seg_bytes);
   const int64_t nchunks = ceil_div(s.nseg, cs);
@@ -745,11 +756,14 @@ int agg_run_filtered(agg_plan_t p, const void* col, int64_t n, const agg_filter*
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
   agg_shape s;
   shape_of(p->dtype, n, &s);
-  const bool aligned = ((reinterpret_cast<uintptr_t>(col) | reinterpret_cast<uintptr_t>(filter->col)) & 15) == 0;
-  const void* fn = filter_scan_kernel_ptr(p->kind, filter->dtype, aligned);
-  const void* comb = filter_combine_kernel_ptr(p->kind);
-  if (!fn || !comb) return AGG_E_INVALID;
   uint64_t* cpart = p->part + kSegTarget;
+  FilterCombineArgs c;
+  c.part = p->part;
+  c.cpart = cpart;
+  c.nseg = s.nseg;
+  c.out = out;
+  c.is_avg = p->op == AGG_AVG;
+  c.prec_used = (p->dtype == AGG_F32 && (p->op == AGG_SUM || p->op == AGG_AVG)) ? p->prec : -1;
   if (s.nseg > 0) {
     FilterArgs a;
     a.base = static_cast<const char*>(col);
@@ -759,23 +773,38 @@ int agg_run_filtered(agg_plan_t p, const void* col, int64_t n, const agg_filter*
     a.nseg = s.nseg;
     a.part = p->part;
     a.cpart = cpart;
-    // the predicate and the masking add VALU work: more waves than the plain
-    // scan (4 per CU measured best for 4- and 8-byte value / filter pairs)
+    // The predicate and the masking add VALU work, and a 4-byte value with an
+    // 8-byte filter three loads a round: more waves than the plain scan, 8 per
+    // CU (4 with that pair) past the columns that one launch takes.  Against
+    // 4 waves everywhere: float SUM WHERE int32, 6e6 items 28.4 -> 24.8 us,
+    // 3e7 62.8 -> 52.1, 6e7 102.0 -> 87.1, 2.5e8 341 -> 308; int64 SUM WHERE
+    // int64, 6e7 160 -> 147; int32 MAX WHERE int64, 6e6 20.9 -> 17.7.
     agg_tune t = p->tune;
     if (!p->tune_given) {
-      t.waves_per_block = 4;
-      t.blocks_per_cu = 1;
+      const bool pair48 = p->width == 4 && fw == 8;
+      if (s.nseg <= kFuseMaxPartials) {  // one launch: at most one workgroup per CU
+        t.waves_per_block = s.nseg > 256 ? 8 : pair48 ? 2 : 4;
+        t.blocks_per_cu = 1;
+      } else {
+        t.waves_per_block = 2;
+        t.blocks_per_cu = pair48 ? 2 : 4;
+      }
     }
     a.pred = pred;
-    RET_IF(launch(fn, grid_for(t, g_dev[p->device].cu, s.nseg), 64 * t.waves_per_block, &a, stream));
+    const int cu = g_dev[p->device].cu;
+    const int grid = grid_for(t, cu, s.nseg);
+    const bool fused = s.nseg <= kFuseMaxPartials && grid <= cu;
+    const void* fn = filter_scan_kernel_ptr(p->kind, filter->dtype, fused);
+    if (!fn) return AGG_E_INVALID;
+    if (fused) {
+      a.done = p->done;
+      a.fin = c;
+      return launch(fn, grid, 64 * t.waves_per_block, &a, stream);
+    }
+    RET_IF(launch(fn, grid, 64 * t.waves_per_block, &a, stream));
   }
-  FilterCombineArgs c;
-  c.part = p->part;
-  c.cpart = cpart;
-  c.nseg = s.nseg;
-  c.out = out;
-  c.is_avg = p->op == AGG_AVG;
-  c.prec_used = (p->dtype == AGG_F32 && (p->op == AGG_SUM || p->op == AGG_AVG)) ? p->prec : -1;
+  const void* comb = filter_combine_kernel_ptr(p->kind);
+  if (!comb) return AGG_E_INVALID;
   return launch(comb, 1, kCombineThreads, &c, stream);
 }
 
@@ -814,7 +843,7 @@ int agg_run_packed(agg_plan_t p, const agg_packed* col, agg_result* out, void* s
       a.seg_hi = s.nseg;
       a.base_seg = 0;
       a.part = p->part;
-      const void* fn = scan_kernel_ptr(p->kind, p->tune.unroll, p->tune.nontemporal != 0, true);
+      const void* fn = scan_kernel_ptr(p->kind, p->tune.unroll, p->tune.nontemporal != 0);
       RET_IF(launch(fn, grid_for(p->tune, g_dev[p->device].cu, s.nseg), 64 * p->tune.waves_per_block, &a, stream));
     }
     c.nseg = s.nseg;
@@ -909,7 +938,7 @@ int agg_batch_plan(agg_batch_t* out, const agg_col* cols, int32_t ncols, const a
     d.kind = kind;
     d.is_avg = c.op == AGG_AVG;
     d.prec_used = (c.dtype == AGG_F32 && (c.op == AGG_SUM || c.op == AGG_AVG)) ? c.prec : -1;
-    d.aligned = (reinterpret_cast<uintptr_t>(c.ptr) & 15) == 0;
+    d.reserved = 0;
     slots += s.nseg;
     if (slots > (int64_t)UINT32_MAX) return AGG_E_INVALID;  // partial slots are indexed by 32 bits
     const int64_t per = std::max<int64_t>(1, run_bytes / s.seg_bytes);
@@ -922,7 +951,6 @@ int agg_batch_plan(agg_batch_t* out, const agg_col* cols, int32_t ncols, const a
       it.seg_hi = (uint16_t)std::min<int64_t>(s.nseg, lo + per);
       it.seg_log2 = (uint8_t)__builtin_ctzll((uint64_t)d.seg_bytes);
       it.kind = (uint8_t)d.kind;
-      it.aligned = (uint8_t)d.aligned;
       items.push_back(it);
     }
   }

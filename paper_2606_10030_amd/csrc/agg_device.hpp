@@ -31,43 +31,26 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // Columns live in global memory (device memory, or pinned host memory mapped
 // into the device's address space), and the loads say so: a column address
 // the compiler cannot trace to a kernel argument (one read from a batch work
-// record) would otherwise get flat loads.
-typedef __attribute__((address_space(1))) const u32x4 global_u32x4;
-typedef __attribute__((address_space(1))) const uint32_t global_u32;
-typedef __attribute__((address_space(1))) const uint64_t global_u64;
+// record) would otherwise get flat loads.  A column is aligned to its item
+// width only, and so is the vector type: a 16-byte load takes any 4-byte
+// aligned address on gfx950, so a slice that starts anywhere in an allocation
+// reads like a whole column (6 001 215 int64 items one item past a 16-byte
+// boundary: scan 11.5 us with item-wise loads).
+typedef uint32_t u32x4_item __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_item __attribute__((ext_vector_type(2), aligned(4)));
 
 template <bool NT>
-__device__ __forceinline__ u32x4 load_vec_aligned(const char* p) {
-  global_u32x4* q = (global_u32x4*)p;
+__device__ __forceinline__ u32x4 load_vec(const char* p) {
+  typedef __attribute__((address_space(1))) const u32x4_item global_vec;
+  global_vec* q = (global_vec*)p;
   if constexpr (NT) return __builtin_nontemporal_load(q);
   else return *q;
-}
-
-// 16 bytes at an address aligned only to the item width W (4 or 8).
-template <bool NT, int W>
-__device__ __forceinline__ u32x4 load_vec_unaligned(const char* p) {
-  u32x4 v;
-  if constexpr (W == 4) {
-    global_u32* q = (global_u32*)p;
-    v[0] = q[0]; v[1] = q[1]; v[2] = q[2]; v[3] = q[3];
-  } else {
-    global_u64* q = (global_u64*)p;
-    uint64_t a = q[0], b = q[1];
-    v[0] = (uint32_t)a; v[1] = (uint32_t)(a >> 32); v[2] = (uint32_t)b; v[3] = (uint32_t)(b >> 32);
-  }
-  return v;
 }
 
 // One item of type T (ragged tails).
 template <typename T>
 __device__ __forceinline__ T load_item(const char* p) {
   return *(__attribute__((address_space(1))) const T*)p;
-}
-
-template <bool NT, bool AL, int W>
-__device__ __forceinline__ u32x4 load_vec(const char* p) {
-  if constexpr (AL) return load_vec_aligned<NT>(p);
-  else return load_vec_unaligned<NT, W>(p);
 }
 
 // ------------------------------------------------------------ fold traits
@@ -352,7 +335,7 @@ __device__ __forceinline__ void fold_unrolled(typename Fold<K>::acc* a, int64_t 
 // seg + r * 1024 + 16 * l, r = 0, 1, ..., each component into its own
 // accumulator in order of r.  `valid` is the segment's byte count (a
 // multiple of the item width); U loads are kept in flight per lane.
-template <int K, int U, bool NT, bool AL>
+template <int K, int U, bool NT>
 __device__ __forceinline__ typename Fold<K>::acc fold_segment(const char* __restrict__ seg,
                                                                int64_t valid, int lane) {
   using F = Fold<K>;
@@ -380,11 +363,11 @@ __device__ __forceinline__ typename Fold<K>::acc fold_segment(const char* __rest
     if (U <= full) {
       u32x4 x[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) x[u] = load_vec<NT, AL, F::W>(p + u * kRoundBytes);
+      for (int u = 0; u < U; ++u) x[u] = load_vec<NT>(p + u * kRoundBytes);
       for (; r + 2 * U <= full; r += U) {
         u32x4 y[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) y[u] = load_vec<NT, AL, F::W>(p + (r + U + u) * kRoundBytes);
+        for (int u = 0; u < U; ++u) y[u] = load_vec<NT>(p + (r + U + u) * kRoundBytes);
         fold_unrolled<K, U>(a, r, [&](int u) { F::add_vec(a, x[u]); }, std::make_integer_sequence<int, U>());
 #pragma unroll
         for (int u = 0; u < U; ++u) x[u] = y[u];
@@ -396,12 +379,12 @@ __device__ __forceinline__ typename Fold<K>::acc fold_segment(const char* __rest
     for (; r + U <= full; r += U) {
       u32x4 x[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) x[u] = load_vec<NT, AL, F::W>(p + (r + u) * kRoundBytes);
+      for (int u = 0; u < U; ++u) x[u] = load_vec<NT>(p + (r + u) * kRoundBytes);
       fold_unrolled<K, U>(a, r, [&](int u) { F::add_vec(a, x[u]); }, std::make_integer_sequence<int, U>());
     }
   }
   for (; r < full; ++r) {
-    F::add_vec(a, load_vec<NT, AL, F::W>(p + r * kRoundBytes));
+    F::add_vec(a, load_vec<NT>(p + r * kRoundBytes));
     round_done<K>(a, r);
   }
   const int rem = (int)(valid - full * kRoundBytes);
@@ -409,7 +392,7 @@ __device__ __forceinline__ typename Fold<K>::acc fold_segment(const char* __rest
     const int lo = lane * kVecBytes;
     const char* q = p + full * kRoundBytes;
     if (lo + kVecBytes <= rem) {
-      F::add_vec(a, load_vec<NT, AL, F::W>(q));
+      F::add_vec(a, load_vec<NT>(q));
     } else if (lo < rem) {
       for (int k = 0; k * F::W < rem - lo; ++k) F::add_item(a[k], q + k * F::W);
     }
@@ -529,6 +512,27 @@ __device__ typename Fold<K>::part combine_partials(const typename Fold<K>::part*
   // same workgroup (the filtered merge takes two) must not overwrite it first
   __syncthreads();
   return total;
+}
+
+// Whether this workgroup is the launch's last to finish, which then merges the
+// partials that all of them stored.  The partials are stored with device-scope
+// stores (written through to the level every XCD sees), and each wave waits
+// for its stores to complete before the workgroup counts itself finished;
+// the workgroup whose count completes the grid reads the partials with
+// device-scope loads, merges, and zeroes the counter for the next launch.
+// Fences would cost more than the combine launch they replace: a device-scope
+// release fence in every wave writes back its XCD's whole L2 (2.5% slower at
+// 2^30 items, measured), and an acquire in every wave also invalidates the
+// L2 under the loads other waves still have in flight (4% slower).  Every
+// workgroup reaches this point, so the count always completes.
+__device__ __forceinline__ bool last_to_finish(uint32_t* done) {
+  __shared__ uint32_t last;
+  __builtin_amdgcn_s_waitcnt(0);  // every memory operation of this wave has completed
+  __syncthreads();
+  if (threadIdx.x == 0)
+    last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+  __syncthreads();
+  return last != 0;
 }
 
 // ------------------------------------------------------------ finalise

@@ -38,35 +38,26 @@ __device__ __forceinline__ bool pred_test(uint32_t lo_word, uint32_t hi_word, co
   }
 }
 
-// FB bytes of filter items for one lane and round.
-template <int FB, int FW, bool NT, bool AL>
+// FB bytes of filter items for one lane and round, at any item alignment.
+template <int FB, bool NT>
 __device__ __forceinline__ void load_filter(const char* p, uint32_t (&w)[FB / 4]) {
-  if constexpr (AL && FB == 8) {
-    const uint64_t v = *reinterpret_cast<const uint64_t*>(p);
-    w[0] = (uint32_t)v;
-    w[1] = (uint32_t)(v >> 32);
-  } else if constexpr (AL) {
-#pragma unroll
-    for (int c = 0; c < FB / 16; ++c) {
-      const u32x4 v = load_vec_aligned<NT>(p + 16 * c);
-      w[4 * c] = v[0]; w[4 * c + 1] = v[1]; w[4 * c + 2] = v[2]; w[4 * c + 3] = v[3];
-    }
-  } else if constexpr (FW == 4) {
-#pragma unroll
-    for (int k = 0; k < FB / 4; ++k) w[k] = reinterpret_cast<const uint32_t*>(p)[k];
+  if constexpr (FB == 8) {
+    typedef __attribute__((address_space(1))) const u32x2_item global_vec2;
+    const u32x2_item v = *(global_vec2*)p;
+    w[0] = v[0];
+    w[1] = v[1];
   } else {
 #pragma unroll
-    for (int k = 0; k < FB / 8; ++k) {
-      const uint64_t v = reinterpret_cast<const uint64_t*>(p)[k];
-      w[2 * k] = (uint32_t)v;
-      w[2 * k + 1] = (uint32_t)(v >> 32);
+    for (int c = 0; c < FB / 16; ++c) {
+      const u32x4 v = load_vec<NT>(p + 16 * c);
+      w[4 * c] = v[0]; w[4 * c + 1] = v[1]; w[4 * c + 2] = v[2]; w[4 * c + 3] = v[3];
     }
   }
 }
 
 // One wave folds the selected items of one segment; `cnt` gets this lane's
 // selected count.  Same lane mapping and accumulation order as fold_segment.
-template <int K, int FT, int U, bool NT, bool AL>
+template <int K, int FT, int U, bool NT>
 __device__ __forceinline__ typename Fold<K>::acc fold_segment_filtered(const char* __restrict__ vseg,
                                                                         const char* __restrict__ fseg,
                                                                         int64_t valid, int lane,
@@ -109,8 +100,8 @@ __device__ __forceinline__ typename Fold<K>::acc fold_segment_filtered(const cha
     uint32_t fw[U][FB / 4];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if constexpr (!kCount) x[u] = load_vec<NT, AL, W>(p + (r + u) * kRoundBytes);
-      load_filter<FB, FW, NT, AL>(f + (r + u) * RFB, fw[u]);
+      if constexpr (!kCount) x[u] = load_vec<NT>(p + (r + u) * kRoundBytes);
+      load_filter<FB, NT>(f + (r + u) * RFB, fw[u]);
     }
     fold_unrolled<K, U>(
         a, r, [&](int u) { fold_round(kCount ? u32x4{0, 0, 0, 0} : x[u], fw[u]); },
@@ -118,8 +109,8 @@ __device__ __forceinline__ typename Fold<K>::acc fold_segment_filtered(const cha
   }
   for (; r < full; ++r) {
     uint32_t fw[FB / 4];
-    load_filter<FB, FW, NT, AL>(f + r * RFB, fw);
-    fold_round(kCount ? u32x4{0, 0, 0, 0} : load_vec<NT, AL, W>(p + r * kRoundBytes), fw);
+    load_filter<FB, NT>(f + r * RFB, fw);
+    fold_round(kCount ? u32x4{0, 0, 0, 0} : load_vec<NT>(p + r * kRoundBytes), fw);
     round_done<K>(a, r);
   }
   const int rem = (int)(valid - full * kRoundBytes);
@@ -164,7 +155,21 @@ struct U64Add {
 template <int K, int FT>
 constexpr int filter_unroll() { return (Fold<K>::W == 4 && FT != AGG_I64) ? 8 : 4; }
 
-template <int K, int FT, bool AL>
+template <int K, bool COHERENT>
+__device__ __forceinline__ void filter_combine(const FilterCombineArgs& c) {
+  using P = typename Fold<K>::part;
+  const P total = combine_partials<K, COHERENT>(reinterpret_cast<const P*>(c.part), c.nseg);
+  const uint64_t selected = combine_partials<K_COUNT_4, COHERENT>(c.cpart, c.nseg);
+  if (threadIdx.x == 0) {
+    P t = total;
+    if constexpr (K == K_COUNT_4 || K == K_COUNT_8) t = selected;
+    *c.out = finalize<K>(t, (int64_t)selected, c.is_avg != 0, c.prec_used);
+  }
+}
+
+// FUSED: the single-launch form for small columns (a.done set), as in the
+// plain scan.
+template <int K, int FT, bool FUSED>
 __global__ void __launch_bounds__(1024) filter_scan_kernel(FilterArgs a) {
   using F = Fold<K>;
   using P = typename F::part;
@@ -179,46 +184,46 @@ __global__ void __launch_bounds__(1024) filter_scan_kernel(FilterArgs a) {
     const int64_t begin = j * a.seg_bytes;
     const int64_t valid = a.col_bytes - begin < a.seg_bytes ? a.col_bytes - begin : a.seg_bytes;
     uint64_t cnt = 0;
-    typename F::acc acc = fold_segment_filtered<K, FT, filter_unroll<K, FT>(), true, AL>(
+    typename F::acc acc = fold_segment_filtered<K, FT, filter_unroll<K, FT>(), true>(
         a.base + begin, a.fbase + begin / W * FW, valid, lane, a.pred, cnt);
     acc = wave_reduce(acc, AccMerge<K>());
     cnt = wave_reduce(cnt, U64Add());
     if (lane == 0) {
-      part[j] = F::to_part(acc);
-      a.cpart[j] = cnt;
+      if constexpr (FUSED) {
+        __hip_atomic_store(part + j, F::to_part(acc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(a.cpart + j, cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } else {
+        part[j] = F::to_part(acc);
+        a.cpart[j] = cnt;
+      }
     }
+  }
+  if constexpr (FUSED) {
+    if (!last_to_finish(a.done)) return;
+    filter_combine<K, true>(a.fin);
+    if (threadIdx.x == 0) __hip_atomic_store(a.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
 template <int K>
 __global__ void __launch_bounds__(256) filter_combine_kernel(FilterCombineArgs c) {
-  using P = typename Fold<K>::part;
-  const P total = combine_partials<K>(reinterpret_cast<const P*>(c.part), c.nseg);
-  const uint64_t selected = combine_partials<K_COUNT_4>(c.cpart, c.nseg);
-  if (threadIdx.x == 0) {
-    P t = total;
-    if constexpr (K == K_COUNT_4 || K == K_COUNT_8) t = selected;
-    *c.out = finalize<K>(t, (int64_t)selected, c.is_avg != 0, c.prec_used);
-  }
+  filter_combine<K, false>(c);
 }
 
-template <int K>
-const void* filter_row(int32_t ft, bool al) {
+template <int K, bool FUSED>
+const void* filter_row(int32_t ft) {
   switch (ft) {
-    case AGG_I32: return al ? reinterpret_cast<const void*>(&filter_scan_kernel<K, AGG_I32, true>)
-                            : reinterpret_cast<const void*>(&filter_scan_kernel<K, AGG_I32, false>);
-    case AGG_I64: return al ? reinterpret_cast<const void*>(&filter_scan_kernel<K, AGG_I64, true>)
-                            : reinterpret_cast<const void*>(&filter_scan_kernel<K, AGG_I64, false>);
-    case AGG_F32: return al ? reinterpret_cast<const void*>(&filter_scan_kernel<K, AGG_F32, true>)
-                            : reinterpret_cast<const void*>(&filter_scan_kernel<K, AGG_F32, false>);
+    case AGG_I32: return reinterpret_cast<const void*>(&filter_scan_kernel<K, AGG_I32, FUSED>);
+    case AGG_I64: return reinterpret_cast<const void*>(&filter_scan_kernel<K, AGG_I64, FUSED>);
+    case AGG_F32: return reinterpret_cast<const void*>(&filter_scan_kernel<K, AGG_F32, FUSED>);
     default: return nullptr;
   }
 }
 
 template <int... Ks>
-const void* filter_lookup(int kind, int32_t ft, bool al, std::integer_sequence<int, Ks...>) {
+const void* filter_lookup(int kind, int32_t ft, bool fused, std::integer_sequence<int, Ks...>) {
   const void* r = nullptr;
-  ((kind == Ks ? (r = filter_row<Ks>(ft, al), 0) : 0), ...);
+  ((kind == Ks ? (r = fused ? filter_row<Ks, true>(ft) : filter_row<Ks, false>(ft), 0) : 0), ...);
   return r;
 }
 
@@ -231,9 +236,9 @@ const void* filter_combine_lookup(int kind, std::integer_sequence<int, Ks...>) {
 
 }  // namespace
 
-const void* filter_scan_kernel_ptr(int kind, int32_t filter_dtype, bool aligned) {
+const void* filter_scan_kernel_ptr(int kind, int32_t filter_dtype, bool fused) {
   if (kind < 0 || kind >= K_NUM) return nullptr;
-  return filter_lookup(kind, filter_dtype, aligned, std::make_integer_sequence<int, K_NUM>());
+  return filter_lookup(kind, filter_dtype, fused, std::make_integer_sequence<int, K_NUM>());
 }
 
 const void* filter_combine_kernel_ptr(int kind) {

@@ -67,6 +67,15 @@ struct RangePred {
   float flo, fhi;
 };
 
+struct FilterCombineArgs {
+  const void* part;
+  const uint64_t* cpart;
+  int64_t nseg;
+  agg_result* out;
+  int32_t is_avg;
+  int32_t prec_used;
+};
+
 // One launch of the filtered scan: value partials and selected counts per segment.
 struct FilterArgs {
   const char* base;      // value column
@@ -77,15 +86,9 @@ struct FilterArgs {
   void* part;            // nseg value partials
   uint64_t* cpart;       // nseg selected counts
   RangePred pred;
-};
-
-struct FilterCombineArgs {
-  const void* part;
-  const uint64_t* cpart;
-  int64_t nseg;
-  agg_result* out;
-  int32_t is_avg;
-  int32_t prec_used;
+  // Single-launch form, as in ScanArgs: the finished-workgroup counter and the merge.
+  uint32_t* done = nullptr;
+  FilterCombineArgs fin{};
 };
 
 // One column of a batch, as the device sees it.
@@ -99,7 +102,7 @@ struct BatchColDev {
   int32_t kind;
   int32_t is_avg;
   int32_t prec_used;
-  int32_t aligned;       // ptr is 16-byte aligned
+  int32_t reserved;
 };
 
 // A run of whole segments [seg_lo, seg_hi) of one column: the unit of work
@@ -115,8 +118,7 @@ struct WorkItem {
   uint16_t seg_hi;
   uint8_t seg_log2;      // seg_bytes = 2^seg_log2
   uint8_t kind;
-  uint8_t aligned;       // ptr is 16-byte aligned
-  uint8_t pad[5];
+  uint8_t pad[6];
 };
 
 struct BatchArgs {
@@ -148,13 +150,13 @@ int64_t ceil_div(int64_t a, int64_t b);
 
 bool tune_is_valid(const agg_tune& t);
 bool tune_cache_lookup(int kind, int32_t src, int64_t bytes, agg_tune* out);
-void builtin_tune_for(int kind, agg_tune* out);
+void builtin_tune_for(int kind, int32_t src, int64_t bytes, agg_tune* out);
 
 // fused: the single-launch form (ScanArgs::done set)
-const void* scan_kernel_ptr(int kind, int unroll, bool nontemporal, bool aligned, bool fused = false);
+const void* scan_kernel_ptr(int kind, int unroll, bool nontemporal, bool fused = false);
 const void* combine_kernel_ptr(int kind);
 const void* packed_scan_kernel_ptr(int kind);   // K_SUM_I32, K_MIN_I32, K_MAX_I32
-const void* filter_scan_kernel_ptr(int kind, int32_t filter_dtype, bool aligned);
+const void* filter_scan_kernel_ptr(int kind, int32_t filter_dtype, bool fused);
 const void* filter_combine_kernel_ptr(int kind);
 const void* batch_scan_kernel_ptr(int unroll, bool nontemporal);
 const void* batch_combine_kernel_ptr();

@@ -41,32 +41,17 @@ __device__ __forceinline__ void combine_and_write(const CombineArgs& a) {
   }
 }
 
-// Pass 2 inside the scan launch.  The partials are stored with device-scope
-// stores (written through to the level every XCD sees), and each wave waits
-// for its stores to complete before the workgroup counts itself finished;
-// the workgroup whose count completes the grid reads the partials with
-// device-scope loads, merges, and zeroes the counter for the next launch.
-// Fences would cost more than the combine launch they replace: a device-scope
-// release fence in every wave writes back its XCD's whole L2 (2.5% slower at
-// 2^30 items, measured), and an acquire in every wave also invalidates the
-// L2 under the loads other waves still have in flight (4% slower).  Every
-// workgroup reaches this point, so the count always completes.
+// Pass 2 inside the scan launch (last_to_finish).
 template <int K>
 __device__ __forceinline__ void finish_if_last(const CombineArgs& c, uint32_t* done) {
-  __shared__ uint32_t last;
-  __builtin_amdgcn_s_waitcnt(0);  // every memory operation of this wave has completed
-  __syncthreads();
-  if (threadIdx.x == 0)
-    last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
-  __syncthreads();
-  if (!last) return;
+  if (!last_to_finish(done)) return;
   combine_and_write<K, true>(c);
   if (threadIdx.x == 0) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // FUSED: the single-launch form (a.done set); a separate instance, so the
 // two-launch kernels' fold loop compiles exactly as without the merge.
-template <int K, int U, bool NT, bool AL, bool FUSED>
+template <int K, int U, bool NT, bool FUSED>
 __global__ void __launch_bounds__(1024) scan_kernel(ScanArgs a) {
   using F = Fold<K>;
   using P = typename F::part;
@@ -81,7 +66,7 @@ __global__ void __launch_bounds__(1024) scan_kernel(ScanArgs a) {
     const int64_t begin = j * a.seg_bytes;
     const int64_t valid = a.col_bytes - begin < a.seg_bytes ? a.col_bytes - begin : a.seg_bytes;
     const char* seg = a.base + (j - a.base_seg) * a.seg_bytes;
-    typename F::acc acc = fold_segment<K, U, NT, AL>(seg, valid, lane);
+    typename F::acc acc = fold_segment<K, U, NT>(seg, valid, lane);
     acc = wave_reduce(acc, AccMerge<K>());
     if (lane == 0) {
       if constexpr (FUSED)  // a device-scope store: the in-launch merge reads it from another XCD
@@ -196,8 +181,7 @@ __device__ __forceinline__ void batch_item(const WorkItem& it, uint64_t* slots, 
   for (int64_t j = it.seg_lo; j < it.seg_hi; ++j) {
     const int64_t begin = j * seg_bytes;
     const int64_t valid = it.col_bytes - begin < seg_bytes ? it.col_bytes - begin : seg_bytes;
-    typename F::acc acc = it.aligned ? fold_segment<K, U, NT, true>(it.ptr + begin, valid, lane)
-                                     : fold_segment<K, 4, false, false>(it.ptr + begin, valid, lane);
+    typename F::acc acc = fold_segment<K, U, NT>(it.ptr + begin, valid, lane);
     acc = wave_reduce(acc, AccMerge<K>());
     if (lane == 0) part[j] = F::to_part(acc);
   }
@@ -241,7 +225,6 @@ __global__ void __launch_bounds__(1024) batch_scan_kernel(BatchArgs a) {
       it.seg_hi = (uint16_t)(range >> 16);
       it.seg_log2 = (uint8_t)(meta & 0xFFu);
       it.kind = (uint8_t)((meta >> 8) & 0xFFu);
-      it.aligned = (uint8_t)((meta >> 16) & 0xFFu);
       switch (it.kind) {
         case K_SUM_I32: batch_item<K_SUM_I32, U, NT>(it, a.part, lane); break;
         case K_MIN_I32: batch_item<K_MIN_I32, U, NT>(it, a.part, lane); break;
@@ -298,40 +281,36 @@ namespace {
 
 template <int K>
 struct ScanRow {
-  // [fused][unroll index][nontemporal][aligned]; the unaligned variant is
-  // one (U = 4, temporal) kernel per form, shared by every entry.
+  // [unroll index][nontemporal], one table per form
   template <bool FU>
-  static const void* get_form(int ui, bool nt, bool al) {
-    if (!al) return reinterpret_cast<const void*>(&scan_kernel<K, 4, false, false, FU>);
+  static const void* get_form(int ui, bool nt) {
     static const void* t[4][2] = {
-        {reinterpret_cast<const void*>(&scan_kernel<K, 4, false, true, FU>),
-         reinterpret_cast<const void*>(&scan_kernel<K, 4, true, true, FU>)},
-        {reinterpret_cast<const void*>(&scan_kernel<K, 8, false, true, FU>),
-         reinterpret_cast<const void*>(&scan_kernel<K, 8, true, true, FU>)},
-        {reinterpret_cast<const void*>(&scan_kernel<K, 16, false, true, FU>),
-         reinterpret_cast<const void*>(&scan_kernel<K, 16, true, true, FU>)},
-        {reinterpret_cast<const void*>(&scan_kernel<K, 32, false, true, FU>),
-         reinterpret_cast<const void*>(&scan_kernel<K, 32, true, true, FU>)}};
+        {reinterpret_cast<const void*>(&scan_kernel<K, 4, false, FU>),
+         reinterpret_cast<const void*>(&scan_kernel<K, 4, true, FU>)},
+        {reinterpret_cast<const void*>(&scan_kernel<K, 8, false, FU>),
+         reinterpret_cast<const void*>(&scan_kernel<K, 8, true, FU>)},
+        {reinterpret_cast<const void*>(&scan_kernel<K, 16, false, FU>),
+         reinterpret_cast<const void*>(&scan_kernel<K, 16, true, FU>)},
+        {reinterpret_cast<const void*>(&scan_kernel<K, 32, false, FU>),
+         reinterpret_cast<const void*>(&scan_kernel<K, 32, true, FU>)}};
     return t[ui][nt ? 1 : 0];
   }
-  static const void* get(int ui, bool nt, bool al, bool fused) {
-    return fused ? get_form<true>(ui, nt, al) : get_form<false>(ui, nt, al);
-  }
+  static const void* get(int ui, bool nt, bool fused) { return fused ? get_form<true>(ui, nt) : get_form<false>(ui, nt); }
 };
 
 template <int... Ks>
-const void* scan_lookup(int kind, int ui, bool nt, bool al, bool fused, std::integer_sequence<int, Ks...>) {
+const void* scan_lookup(int kind, int ui, bool nt, bool fused, std::integer_sequence<int, Ks...>) {
   const void* r = nullptr;
-  ((kind == Ks ? (r = ScanRow<Ks>::get(ui, nt, al, fused), 0) : 0), ...);
+  ((kind == Ks ? (r = ScanRow<Ks>::get(ui, nt, fused), 0) : 0), ...);
   return r;
 }
 
 }  // namespace
 
-const void* scan_kernel_ptr(int kind, int unroll, bool nontemporal, bool aligned, bool fused) {
+const void* scan_kernel_ptr(int kind, int unroll, bool nontemporal, bool fused) {
   const int ui = unroll_index(unroll);
   if (kind < 0 || kind >= K_NUM || ui < 0) return nullptr;
-  return scan_lookup(kind, ui, nontemporal, aligned, fused, std::make_integer_sequence<int, K_NUM>());
+  return scan_lookup(kind, ui, nontemporal, fused, std::make_integer_sequence<int, K_NUM>());
 }
 
 namespace {

@@ -514,7 +514,6 @@ int agg::serve::HipExecutor::start(int slot, const agg_request& req, const Job& 
   shape_of(req.dtype, req.n, &sh);
   tune_for(j.kind, AGG_SRC_DEVICE, j.bytes, &r.t);
   const char* col = j.from_arena ? s_->arena + j.off : static_cast<const char*>(req.ptr);
-  const bool aligned = (reinterpret_cast<uintptr_t>(col) & 15) == 0;
   uint64_t* part = s_->part + (size_t)slot * kSegTarget;
   r.a.col_bytes = j.bytes;
   r.a.seg_bytes = sh.seg_bytes;
@@ -527,7 +526,7 @@ int agg::serve::HipExecutor::start(int slot, const agg_request& req, const Job& 
   r.c.n = req.n;
   r.c.is_avg = req.op == AGG_AVG;
   r.c.prec_used = (req.dtype == AGG_F32 && (req.op == AGG_SUM || req.op == AGG_AVG)) ? req.prec : -1;
-  r.scan_fn = scan_kernel_ptr(j.kind, r.t.unroll, r.t.nontemporal != 0, aligned);
+  r.scan_fn = scan_kernel_ptr(j.kind, r.t.unroll, r.t.nontemporal != 0);
   r.comb_fn = combine_kernel_ptr(j.kind);
   if (!r.scan_fn || !r.comb_fn) return AGG_E_INVALID;
   r.nseg = sh.nseg;

@@ -47,26 +47,60 @@ int bucket_of(int64_t bytes) {  // ceil(log2(bytes)), at least 10
   return b;
 }
 
-// Measured bests on MI355X for 2^30-item columns (device source): two waves
-// per CU with 16 outstanding 16-byte loads per lane for most kinds; the
-// compensated float sum has about 4x the VALU work per item and wants more
-// waves to hide it.
-void builtin_for(int kind, agg_tune* t) {
+// Measured bests on MI355X.
+//
+// Columns of 256 MiB and more (segments of 64 KiB and more): two waves per CU
+// with 16 or 32 outstanding 16-byte loads per lane stream best (more waves
+// only make the memory's rows compete); the compensated float sum has about 4x
+// the VALU work per item and wants more waves to hide it.
+//
+// Smaller device columns are latency, not streaming: a 16 KiB segment is 16
+// rounds, which a wave loads in one or two groups before it has to wait, and
+// with two waves per CU little is in flight (and 32 rounds, the min / max
+// shape, are never reached, so every round was waited for by itself).  Per call
+// on the GPU, before -> after: int32 MIN 4 MB 11.1 -> 5.8 us, 48 MB 46 -> 11.8,
+// 100 MB 90 -> 20.4, 500 MB 83.9 -> 78.2; int64 SUM 16 MB 9.6 -> 7.4, 48 MB
+// 15.3 -> 11.5, 100 MB 22.2 -> 20.0, 150 MB 28.6 -> 27.2 (int32); compensated
+// float SUM 4 MB 11.2 -> 10.2, 16 MB 20.3 -> 14.7, 48 MB 25.0 -> 21.8, 130 MB
+// 38.8 -> 34.3, 300 MB 63.1 -> 59.5.  Up to 1024 segments (16 MB) the shapes keep
+// to one workgroup per CU, so that the scan's last workgroup may merge.
+void builtin_for(int kind, int32_t src, int64_t bytes, agg_tune* t) {
   t->nontemporal = 1;
   t->chunk_bytes = 64ll << 20;
   t->staging_depth = 3;
   t->reserved = 0;
-  switch (kind) {
-    case K_SUM_I64: case K_MIN_I64: case K_MAX_I64:
-      t->waves_per_block = 1; t->blocks_per_cu = 2; t->unroll = 16; break;
-    case K_SUM_F32_NEU:
-      t->waves_per_block = 4; t->blocks_per_cu = 1; t->unroll = 8; break;
-    case K_MIN_I32: case K_MAX_I32: case K_MIN_F32: case K_MAX_F32:
-      t->waves_per_block = 2; t->blocks_per_cu = 1; t->unroll = 32; break;
-    case K_COUNT_4: case K_COUNT_8:
-      t->waves_per_block = 4; t->blocks_per_cu = 1; t->unroll = 8; break;
-    default:  // K_SUM_I32, K_SUM_F32_PLAIN, K_SUM_F32_F64C
-      t->waves_per_block = 2; t->blocks_per_cu = 1; t->unroll = 16; break;
+  auto shape = [t](int32_t waves, int32_t blocks, int32_t unroll) {
+    t->waves_per_block = waves;
+    t->blocks_per_cu = blocks;
+    t->unroll = unroll;
+  };
+  const int64_t nseg = bytes / kSegMin;  // 16 KiB segments, below 128 MiB
+  const bool small = src == AGG_SRC_DEVICE && bytes < (128ll << 20), mid = src == AGG_SRC_DEVICE && bytes < (256ll << 20);
+  const bool narrow_minmax = kind == K_MIN_I32 || kind == K_MAX_I32 || kind == K_MIN_F32 || kind == K_MAX_F32;
+  if (kind == K_COUNT_4 || kind == K_COUNT_8) {
+    shape(4, 1, 8);
+  } else if (kind == K_SUM_F32_NEU) {
+    if (small) {
+      if (nseg <= 64) shape(4, 1, 16);
+      else if (nseg <= 512) shape(8, 1, 16);
+      else shape(16, 1, 8);
+    } else if (src == AGG_SRC_DEVICE && bytes < (2ll << 30)) {
+      shape(2, 4, 8);
+    } else {
+      shape(4, 1, 8);
+    }
+  } else if (small) {
+    if (nseg <= 512) shape(4, 1, 16);
+    else if (nseg < 1024) shape(8, 1, 8);
+    else shape(2, 2, 8);
+  } else if (mid || (narrow_minmax && src == AGG_SRC_DEVICE && bytes < (1ll << 30))) {
+    shape(2, 2, 16);
+  } else if (narrow_minmax) {
+    shape(2, 1, 32);
+  } else if (kind == K_SUM_I64 || kind == K_MIN_I64 || kind == K_MAX_I64) {
+    shape(1, 2, 16);
+  } else {  // K_SUM_I32, K_SUM_F32_PLAIN, K_SUM_F32_F64C
+    shape(2, 1, 16);
   }
 }
 
@@ -109,10 +143,10 @@ double time_runs(F fn, hipStream_t stream, int warm, int runs) {
   return ms;
 }
 
-std::vector<agg_tune> kernel_candidates(int kind) {
+std::vector<agg_tune> kernel_candidates(int kind, int32_t src, int64_t bytes) {
   std::vector<agg_tune> v;
   agg_tune base;
-  builtin_for(kind, &base);
+  builtin_for(kind, src, bytes, &base);
   const int wb[][2] = {{1, 2}, {2, 1}, {4, 1}, {1, 3}, {2, 2}, {4, 2}, {8, 1}, {1, 4}};
   for (int u : {8, 16, 32})
     for (auto& p : wb) {
@@ -145,7 +179,7 @@ bool tune_cache_lookup(int kind, int32_t src, int64_t bytes, agg_tune* out) {
   return true;
 }
 
-void builtin_tune_for(int kind, agg_tune* out) { builtin_for(kind, out); }
+void builtin_tune_for(int kind, int32_t src, int64_t bytes, agg_tune* out) { builtin_for(kind, src, bytes, out); }
 
 }  // namespace agg
 
@@ -161,7 +195,7 @@ int agg_autotune(int32_t dtype, int32_t op, int32_t prec, const void* col, int64
   std::vector<agg_tune> cands;
   if (src == AGG_SRC_PINNED_HOST) {
     agg_tune base;
-    builtin_for(kind, &base);
+    builtin_for(kind, src, n * width_of(dtype), &base);
     for (int64_t mb : {16, 32, 64, 128})
       for (int depth : {2, 3, 4}) {
         agg_tune t = base;
@@ -170,7 +204,7 @@ int agg_autotune(int32_t dtype, int32_t op, int32_t prec, const void* col, int64
         cands.push_back(t);
       }
   } else {
-    cands = kernel_candidates(kind);
+    cands = kernel_candidates(kind, src, n * width_of(dtype));
   }
   void* out = nullptr;
   const int arc = device_alloc(&out, sizeof(agg_result));
