@@ -205,26 +205,25 @@ int agg_plan_destroy(agg_plan_t plan);
 /* ---- many columns in one launch (agg_batch) ---- */
 
 /* Build a batch over cols[0..ncols): the work table (runs of whole segments
- * of each column), partial and result buffers, and a HIP graph holding the
- * persistent scan kernel and the per-column combine kernel.  Column memory
- * must stay valid and unchanged in address while the batch is used; its
- * contents may change between runs. */
+ * of each column) and partial buffers.  Column memory must stay valid and
+ * unchanged in address while the batch is used; its contents may change
+ * between runs. */
 int agg_batch_plan(agg_batch_t* out, const agg_col* cols, int32_t ncols, const agg_tune* tune);
 
-/* Launch the batch graph on `stream` and copy the ncols results into
- * out[0..ncols) (device or page-locked host memory). */
+/* Enqueue the persistent scan kernel and the per-column combine kernel on
+ * `stream`; the ncols results are written to out[0..ncols) (device or
+ * page-locked host memory). */
 int agg_batch_run(agg_batch_t batch, agg_result* out, void* stream);
 
 int agg_batch_destroy(agg_batch_t batch);
 
-/* Work items, total segments and the launch parameters the batch graph uses. */
+/* Work items, total segments and the launch parameters the batch uses. */
 int agg_batch_info(agg_batch_t batch, int64_t* nitems, int64_t* nseg_total, agg_tune* tune);
 
-/* Re-capture the batch graph with other launch parameters (results
- * unchanged).  Waits for the batch's previous runs to finish. */
+/* Use other launch parameters from the next run on (results unchanged). */
 int agg_batch_retune(agg_batch_t batch, const agg_tune* tune);
 
-/* Time the batch graph under a fixed set of launch parameters on `stream`
+/* Time the batch under a fixed set of launch parameters on `stream`
  * (waves per block x blocks per CU x loads in flight), keep the fastest and
  * return it with its time per run in milliseconds.  Synchronises `stream`. */
 int agg_batch_autotune(agg_batch_t batch, void* stream, agg_tune* best, double* best_ms);

@@ -3,7 +3,7 @@
 // Plans own their workspaces (segment partials, completion counter, and for
 // pinned-host sources a device staging ring, a copy stream and events), so
 // agg_run only validates, picks a kernel and enqueues.  Batches own a work
-// table, partials, results and a captured HIP graph.
+// table and partials.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -202,9 +202,16 @@ void tune_for(int kind, int32_t src, int64_t bytes, agg_tune* t) {
   if (!tune_cache_lookup(kind, src, bytes, t)) builtin_tune_for(kind, src, bytes, t);
 }
 
-// Batches mix kinds; two waves per CU with 16 loads in flight suits all of
-// the plain kinds (agg_batch_autotune refines it).
-void batch_builtin_tune(agg_tune* t) { builtin_tune_for(K_SUM_I32, AGG_SRC_DEVICE, INT64_MAX, t); }
+// Batches mix kinds and short columns, whose 16 KiB segments a wave folds one
+// after another: 4 waves per CU for a large batch, 8 for a smaller one, 8 loads
+// in flight (2 waves with 16 before): 512 columns of 2.7 GB 461 -> 409 us, of
+// 0.36 GB 98 -> 76, 64 columns of 0.22 GB 64 -> 55.  agg_batch_autotune refines it.
+void batch_builtin_tune(int64_t bytes, agg_tune* t) {
+  builtin_tune_for(K_SUM_I32, AGG_SRC_DEVICE, INT64_MAX, t);
+  t->waves_per_block = bytes >= (1ll << 30) ? 4 : 8;
+  t->blocks_per_cu = 1;
+  t->unroll = 8;
+}
 
 namespace {
 // The checks of check_pointer on attributes already queried.
@@ -328,9 +335,6 @@ struct agg_batch_s {
   WorkItem* ditems = nullptr;
   uint64_t* dpart = nullptr;
   agg_result* dres = nullptr;
-  hipStream_t capture_stream = nullptr;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
 };
 
 namespace {
@@ -350,9 +354,6 @@ void plan_release(agg_plan_s* p) {
 
 void batch_release(agg_batch_s* b) {
   if (!b) return;
-  if (b->exec) (void)hipGraphExecDestroy(b->exec);
-  if (b->graph) (void)hipGraphDestroy(b->graph);
-  if (b->capture_stream) (void)hipStreamDestroy(b->capture_stream);
   if (b->ws) (void)hipFree(b->ws);
   delete b;
 }
@@ -406,45 +407,25 @@ int plan_create(agg_plan_s* p) {
 
 namespace {
 
-// Capture the batch graph for launch parameters t: the persistent scan over
-// the work table, then one combine workgroup per column.  Replaces any
-// previous graph.
-int batch_capture(agg_batch_s* b, const agg_tune& t) {
+// Enqueue a batch under launch parameters t: the persistent scan over the work
+// table, then one combine workgroup per column, which writes the column's
+// result straight to its place in `out`.  Two launches cost the host 5 us; a
+// captured graph of the same two kernels and the copy of the results behind
+// it took 25 (16 short columns 26.7 -> 15.8 us a call).
+int batch_enqueue(agg_batch_s* b, const agg_tune& t, agg_result* out, hipStream_t stream) {
   BatchArgs ba;
   ba.cols = b->dcols;
   ba.items = b->ditems;
   ba.nitems = b->nitems;
   ba.part = b->dpart;
-  ba.results = b->dres;
+  ba.results = out;
   const void* scan_fn = batch_scan_kernel_ptr(t.unroll, t.nontemporal != 0);
   if (!scan_fn) return AGG_E_INVALID;
-  const int grid = grid_for(t, g_dev[b->device].cu, b->nitems);
-  if (b->exec) {
-    (void)hipGraphExecDestroy(b->exec);
-    b->exec = nullptr;
-  }
-  if (b->graph) {
-    (void)hipGraphDestroy(b->graph);
-    b->graph = nullptr;
-  }
-  HIPCHK(hipStreamBeginCapture(b->capture_stream, hipStreamCaptureModeThreadLocal));
-  hipError_t e = hipSuccess;
-  if (b->nitems > 0) {
-    void* kargs[] = {&ba};
-    e = hipLaunchKernel(scan_fn, dim3(grid), dim3(64 * t.waves_per_block), kargs, 0, b->capture_stream);
-  }
-  if (e == hipSuccess && b->ncols > 0) {
-    int64_t nc = b->ncols;
-    void* kargs2[] = {&ba, &nc};
-    e = hipLaunchKernel(batch_combine_kernel_ptr(), dim3(b->ncols), dim3(256), kargs2, 0, b->capture_stream);
-  }
-  hipGraph_t g = nullptr;
-  const hipError_t e2 = hipStreamEndCapture(b->capture_stream, &g);
-  b->graph = g;
-  HIPCHK(e);
-  HIPCHK(e2);
-  HIPCHK(hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0));
-  b->tune = t;
+  if (b->nitems > 0)
+    RET_IF(launch(scan_fn, grid_for(t, g_dev[b->device].cu, b->nitems), 64 * t.waves_per_block, &ba, stream));
+  int64_t nc = b->ncols;
+  void* kargs[] = {&ba, &nc};
+  HIPCHK(hipLaunchKernel(batch_combine_kernel_ptr(), dim3(b->ncols), dim3(256), kargs, 0, stream));
   return AGG_OK;
 }
 
@@ -894,8 +875,6 @@ int agg_batch_plan(agg_batch_t* out, const agg_col* cols, int32_t ncols, const a
   if (tune) {
     t = *tune;
     if (!valid_tune(t)) return AGG_E_INVALID;
-  } else {
-    batch_builtin_tune(&t);
   }
   for (int32_t i = 0; i < ncols; ++i) {  // host-side checks first
     const agg_col& c = cols[i];
@@ -914,6 +893,7 @@ int agg_batch_plan(agg_batch_t* out, const agg_col* cols, int32_t ncols, const a
   // 64 KiB items 0.805 / 0.850 of HBM, 256 KiB 0.795 / 0.853, 1 MiB 0.74 / 0.83).
   int64_t total_bytes = 0;
   for (int32_t i = 0; i < ncols; ++i) total_bytes += cols[i].n * width_of(cols[i].dtype);
+  if (!tune) batch_builtin_tune(total_bytes, &t);
   const int64_t item_target = total_bytes / ((int64_t)std::max(1, g_dev[dev].cu) * 4 * 64);
   int64_t run_bytes = kItemMaxBytes;
   while (run_bytes > kItemMinBytes && run_bytes > item_target) run_bytes >>= 1;
@@ -999,10 +979,6 @@ int agg_batch_plan(agg_batch_t* out, const agg_col* cols, int32_t ncols, const a
   if (b->nitems > 0 && (e = hipMemcpy(b->ditems, items.data(), sizeof(WorkItem) * (size_t)b->nitems,
                                       hipMemcpyHostToDevice)) != hipSuccess)
     return hip_fail(e);
-  if ((e = hipStreamCreateWithFlags(&b->capture_stream, hipStreamNonBlocking)) != hipSuccess) return hip_fail(e);
-
-  const int rc2 = batch_capture(b, t);
-  if (rc2 != AGG_OK) return fail(rc2);
   if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(e);
   *out = b;
   return AGG_OK;
@@ -1013,8 +989,10 @@ int agg_batch_run(agg_batch_t b, agg_result* out, void* stream_v) {
   if (b->ncols == 0) return AGG_OK;
   RET_IF(check_out_pointer(out, (int64_t)sizeof(agg_result) * b->ncols, b->device));
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
-  HIPCHK(hipGraphLaunch(b->exec, stream));
-  HIPCHK(hipMemcpyAsync(out, b->dres, sizeof(agg_result) * (size_t)b->ncols, hipMemcpyDefault, stream));
+  // the kernel writes whole records, so one that is not aligned is copied
+  const bool direct = reinterpret_cast<uintptr_t>(out) % alignof(agg_result) == 0;
+  RET_IF(batch_enqueue(b, b->tune, direct ? out : b->dres, stream));
+  if (!direct) HIPCHK(hipMemcpyAsync(out, b->dres, sizeof(agg_result) * (size_t)b->ncols, hipMemcpyDefault, stream));
   return AGG_OK;
 }
 
@@ -1027,8 +1005,8 @@ int agg_batch_destroy(agg_batch_t b) {
 
 int agg_batch_retune(agg_batch_t b, const agg_tune* tune) {
   if (!b || !tune || !valid_tune(*tune)) return AGG_E_INVALID;
-  HIPCHK(hipStreamSynchronize(b->capture_stream));
-  return batch_capture(b, *tune);
+  b->tune = *tune;
+  return AGG_OK;
 }
 
 int agg_batch_info(agg_batch_t b, int64_t* nitems, int64_t* nseg_total, agg_tune* tune) {
@@ -1064,11 +1042,11 @@ int agg_batch_autotune(agg_batch_t b, void* stream_v, agg_tune* best, double* be
       t.unroll = u;
       t.waves_per_block = p[0];
       t.blocks_per_cu = p[1];
-      rc = batch_capture(b, t);
+      rc = batch_enqueue(b, t, b->dres, stream);
       if (rc != AGG_OK) break;
-      if ((e = hipGraphLaunch(b->exec, stream)) != hipSuccess) { g_last_hip = (int32_t)e; rc = AGG_E_HIP; break; }
       if ((e = hipEventRecord(e0, stream)) != hipSuccess) { g_last_hip = (int32_t)e; rc = AGG_E_HIP; break; }
-      for (int r = 0; r < 3 && e == hipSuccess; ++r) e = hipGraphLaunch(b->exec, stream);
+      for (int r = 0; r < 3 && rc == AGG_OK; ++r) rc = batch_enqueue(b, t, b->dres, stream);
+      if (rc != AGG_OK) break;
       if (e == hipSuccess) e = hipEventRecord(e1, stream);
       if (e == hipSuccess) e = hipEventSynchronize(e1);
       float ms = 0.0f;
@@ -1084,7 +1062,7 @@ int agg_batch_autotune(agg_batch_t b, void* stream_v, agg_tune* best, double* be
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc != AGG_OK) return rc;
-  RET_IF(batch_capture(b, best_t));
+  b->tune = best_t;
   if (best) *best = best_t;
   if (best_ms_out) *best_ms_out = best_ms;
   return AGG_OK;
