@@ -56,6 +56,9 @@ struct PackedArgs {
   int64_t payload_words;
   void* part;            // one partial per wave of the launch
   uint32_t* err;         // set to 1 when a block header is corrupt (the block is not read)
+  // Single-launch form, as in ScanArgs: the finished-workgroup counter and the merge.
+  uint32_t* done = nullptr;
+  CombineArgs fin{};
 };
 
 // The range predicate of a filtered scan, as the device sees it: the host
@@ -155,7 +158,7 @@ void builtin_tune_for(int kind, int32_t src, int64_t bytes, agg_tune* out);
 // fused: the single-launch form (ScanArgs::done set)
 const void* scan_kernel_ptr(int kind, int unroll, bool nontemporal, bool fused = false);
 const void* combine_kernel_ptr(int kind);
-const void* packed_scan_kernel_ptr(int kind);   // K_SUM_I32, K_MIN_I32, K_MAX_I32
+const void* packed_scan_kernel_ptr(int kind, bool fused);   // K_SUM_I32, K_MIN_I32, K_MAX_I32
 const void* filter_scan_kernel_ptr(int kind, int32_t filter_dtype, bool fused);
 const void* filter_combine_kernel_ptr(int kind);
 const void* batch_scan_kernel_ptr(int unroll, bool nontemporal);

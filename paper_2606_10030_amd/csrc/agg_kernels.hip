@@ -96,7 +96,8 @@ __device__ __forceinline__ void decode_lane(const uint32_t* __restrict__ p, int 
   uint32_t w[BITS > 0 ? BITS : 1];
 #pragma unroll
   for (int j = 0; j < BITS; ++j) w[j] = p[j * kWave + lane];
-  uint64_t s = 0;
+  // 32 items of up to 27 bits sum within 32 bits
+  typename std::conditional<BITS <= 27, uint32_t, uint64_t>::type s = 0;
   uint32_t mn = 0xFFFFFFFFu, mx = 0u;
 #pragma unroll
   for (int i = 0; i < kWave / 2; ++i) {
@@ -131,10 +132,15 @@ __device__ __forceinline__ void decode_dispatch(uint32_t bits, bool full, const 
   }
 }
 
-template <int K>
+// A wave's blocks are b = wave, wave + P, wave + 2P, ... (P waves).  It reads
+// their headers 64 at a time, one per lane, and takes each out with readlane:
+// a block then waits for its payload only, not for its header first.
+// FUSED: the single-launch form for small columns (a.done set).
+template <int K, bool FUSED>
 __global__ void __launch_bounds__(1024) packed_scan_kernel(PackedArgs a) {
   using F = Fold<K>;
   using P = typename F::part;
+  static_assert(sizeof(agg_packed_block) == 16, "a header is one 16-byte word");
   const int lane = threadIdx.x & (kWave - 1);
   const int W = blockDim.x / kWave;
   const int64_t nwaves = (int64_t)gridDim.x * W;
@@ -142,33 +148,49 @@ __global__ void __launch_bounds__(1024) packed_scan_kernel(PackedArgs a) {
   constexpr int kPerLane = AGG_PACK_BLOCK / kWave;
   uint64_t sum = 0;              // sum of items mod 2^64 (SUM)
   int32_t ext = K == K_MIN_I32 ? INT32_MAX : INT32_MIN;  // running MIN / MAX
-  for (int64_t b = wave; b < a.nblocks; b += nwaves) {
-    const agg_packed_block h = a.blocks[b];
-    // a block whose payload would lie outside the buffer is never read; the
-    // result is marked invalid (the combine reads the flag)
-    if (h.bits > 32 || h.word_off < 0 || h.word_off + (int64_t)kWave * h.bits > a.payload_words) {
-      if (lane == 0) __hip_atomic_fetch_or(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      continue;
-    }
-    const int64_t left = a.n - b * AGG_PACK_BLOCK;
-    const bool full = left >= AGG_PACK_BLOCK;
-    int valid = (int)(left - (int64_t)lane * kPerLane);
-    valid = valid < 0 ? 0 : (valid > kPerLane ? kPerLane : valid);
-    uint64_t dsum = 0;
-    uint32_t dmin = 0xFFFFFFFFu, dmax = 0u;
-    decode_dispatch(h.bits, full, a.payload + h.word_off, lane, valid, dsum, dmin, dmax);
-    if constexpr (K == K_SUM_I32) {
-      sum += dsum + (uint64_t)((int64_t)valid * (int64_t)h.base);
-    } else if (valid > 0) {
-      const int32_t lo = (int32_t)((uint32_t)h.base + dmin), hi = (int32_t)((uint32_t)h.base + dmax);
-      ext = K == K_MIN_I32 ? min(ext, lo) : max(ext, hi);
+  for (int64_t first = wave; first < a.nblocks; first += kWave * nwaves) {
+    u32x4 head = {0, 0, 0, 0};
+    if (first + lane * nwaves < a.nblocks) head = *reinterpret_cast<const u32x4*>(a.blocks + first + lane * nwaves);
+    __asm__ volatile("" : "+v"(head));  // one wait, here (see the batch kernel)
+    const int64_t left_blocks = (a.nblocks - first + nwaves - 1) / nwaves;
+    const int cnt = left_blocks < kWave ? (int)left_blocks : kWave;
+    for (int l = 0; l < cnt; ++l) {
+      auto rd = [l](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+      const int64_t b = first + l * nwaves;
+      const int32_t base = (int32_t)rd(head[0]);
+      const uint32_t bits = rd(head[1]);
+      const int64_t word_off = (int64_t)(((uint64_t)rd(head[3]) << 32) | rd(head[2]));
+      // a block whose payload would lie outside the buffer is never read; the
+      // result is marked invalid (the combine reads the flag)
+      if (bits > 32 || word_off < 0 || word_off > a.payload_words - (int64_t)kWave * bits) {
+        if (lane == 0) __hip_atomic_fetch_or(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        continue;
+      }
+      const int64_t left = a.n - b * AGG_PACK_BLOCK;
+      const bool full = left >= AGG_PACK_BLOCK;
+      int valid = (int)(left - (int64_t)lane * kPerLane);
+      valid = valid < 0 ? 0 : (valid > kPerLane ? kPerLane : valid);
+      uint64_t dsum = 0;
+      uint32_t dmin = 0xFFFFFFFFu, dmax = 0u;
+      decode_dispatch(bits, full, a.payload + word_off, lane, valid, dsum, dmin, dmax);
+      if constexpr (K == K_SUM_I32) {
+        sum += dsum + (uint64_t)((int64_t)valid * (int64_t)base);
+      } else if (valid > 0) {
+        const int32_t lo = (int32_t)((uint32_t)base + dmin), hi = (int32_t)((uint32_t)base + dmax);
+        ext = K == K_MIN_I32 ? min(ext, lo) : max(ext, hi);
+      }
     }
   }
   P partial;
   if constexpr (K == K_SUM_I32) partial = sum;
   else partial = (int64_t)ext;
   partial = wave_reduce(partial, PartMerge<K>());
-  if (lane == 0) reinterpret_cast<P*>(a.part)[wave] = partial;
+  if (lane == 0) {
+    P* part = reinterpret_cast<P*>(a.part) + wave;
+    if constexpr (FUSED) __hip_atomic_store(part, partial, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *part = partial;
+  }
+  if constexpr (FUSED) finish_if_last<K>(a.fin, a.done);
 }
 
 // ------------------------------------------------------------ batch
@@ -327,11 +349,14 @@ const void* combine_kernel_ptr(int kind) {
   return combine_lookup(kind, std::make_integer_sequence<int, K_NUM>());
 }
 
-const void* packed_scan_kernel_ptr(int kind) {
+const void* packed_scan_kernel_ptr(int kind, bool fused) {
   switch (kind) {
-    case K_SUM_I32: return reinterpret_cast<const void*>(&packed_scan_kernel<K_SUM_I32>);
-    case K_MIN_I32: return reinterpret_cast<const void*>(&packed_scan_kernel<K_MIN_I32>);
-    case K_MAX_I32: return reinterpret_cast<const void*>(&packed_scan_kernel<K_MAX_I32>);
+    case K_SUM_I32: return fused ? reinterpret_cast<const void*>(&packed_scan_kernel<K_SUM_I32, true>)
+                                 : reinterpret_cast<const void*>(&packed_scan_kernel<K_SUM_I32, false>);
+    case K_MIN_I32: return fused ? reinterpret_cast<const void*>(&packed_scan_kernel<K_MIN_I32, true>)
+                                 : reinterpret_cast<const void*>(&packed_scan_kernel<K_MIN_I32, false>);
+    case K_MAX_I32: return fused ? reinterpret_cast<const void*>(&packed_scan_kernel<K_MAX_I32, true>)
+                                 : reinterpret_cast<const void*>(&packed_scan_kernel<K_MAX_I32, false>);
     default: return nullptr;
   }
 }
