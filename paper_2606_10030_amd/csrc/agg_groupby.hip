@@ -37,6 +37,7 @@
 #include <type_traits>
 
 #include "agg.h"
+#include "agg_device.hpp"
 #include "agg_digits.hpp"
 #include "agg_internal.hpp"
 
@@ -55,7 +56,6 @@ constexpr int kMinPartBits = 5;       // at least 32
 constexpr int64_t kChunkRows = (int64_t)1 << 28;
 constexpr int kMaxHistWg = 512;                    // histogram / scatter workgroups per chunk
 constexpr int64_t kMinHistRows = 8192;             // rows per such workgroup, at least
-constexpr int kScanThreads = 1024;
 constexpr int kTileThreads = 1024;    // scatter: rows staged in LDS per tile
 constexpr int kTileMaxBits = 11;      // scatter into at most 2048 partitions
 // Rows per tile of the scatter without carried rows: as many as LDS holds next
@@ -89,6 +89,16 @@ enum GOp { G_COUNT = 0, G_SUM_INT, G_MIN_INT, G_MAX_INT, G_SUM_F32, G_MIN_F32, G
 // workgroups per CU with half the slots: fewer, larger tables hold 2x the
 // groups at the same load and fold faster.
 constexpr int kDirectThreads = 1024;
+// Tables up to this many slots are emitted by the aggregation launch's last
+// workgroup, larger ones by a launch of their own.  With the table clean from
+// the call before and the group count written by the emission, a call of 1e5
+// rows and 25 groups is one launch instead of four (22.4 -> 12.9 us).  The one
+// workgroup reads past its L2 and a float slot has nine digits, so the line
+// lies lower there.  1e5 rows, int32 keys, one launch against two: 25 groups
+// 12.8 us (14.1); int32 SUM of 1000 groups, 2048 slots 33.6 (34.8), of 2000,
+// 4096 slots 42.2 (40.8); float SUM of 25 groups 17.8 (18.9), of 300, 1024
+// slots 36.1 (35.0), of 2000 72.9 (56.1).
+constexpr int64_t fuse_slots_of(int g) { return (g == G_SUM_F32 ? 256 : 2048) + 1; }
 constexpr int lds_slots_of(int g, int kd) {
   return g == G_SUM_F32 ? 4096 : (g == G_COUNT ? 2 : 1) * (kd == AGG_I32 ? 8192 : 4096);
 }
@@ -125,7 +135,9 @@ struct Table {
   int64_t* val;        // integer SUM / MIN / MAX; float MIN / MAX as order-preserving ints
   int64_t* dig;        // float SUM: kDigits per slot
   int32_t* flags;      // float SUM: 1 NaN, 2 +Inf, 4 -Inf seen
-  int32_t* state;      // [0] slot cap used, [1] overflow, [2..3] emitted count (uint64), [4..5] float-sum windows
+  // [0] overflow (more distinct keys than slots), [2..3] groups emitted (uint64), [4] finished
+  // workgroups.  State and slots are clean between calls: each call's emission clears what it reads.
+  int32_t* state;
   int64_t cap;         // slots, a power of two >= 64
   int32_t cap_log2;
 };
@@ -154,11 +166,23 @@ struct Args {
   int64_t* ngroups;
   int32_t is_avg;
   int32_t op;
+  int32_t emit;        // direct path: the launch's last workgroup emits (fuse_slots_of)
 };
 
 template <int G>
 constexpr int64_t val_identity() {
   return (G == G_MIN_INT || G == G_MIN_F32) ? INT64_MAX : (G == G_MAX_INT || G == G_MAX_F32) ? INT64_MIN : 0;
+}
+
+template <int G>
+__device__ __forceinline__ void clear_slot(const Table& t, int64_t s) {
+  t.key[s] = kEmpty;  // slot cap's key is the marker key itself
+  t.cnt[s] = 0;
+  t.val[s] = val_identity<G>();
+  if constexpr (G == G_SUM_F32) {
+    t.flags[s] = 0;
+    for (int d = 0; d < kDigits; ++d) t.dig[s * kDigits + d] = 0;
+  }
 }
 
 __device__ __forceinline__ int64_t ceil_div_dev(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -278,10 +302,7 @@ __device__ __forceinline__ void apply(CT* cnt, int64_t* val, int64_t* dig, int32
 // The global slot of key k with hash h, claiming an empty one; -1 when the
 // table is full.  The home is the top bits of the hash (see key_hash).
 __device__ __forceinline__ int64_t global_slot(const Table& t, int64_t k, uint32_t h) {
-  if (k == kEmpty) {
-    t.state[0] = 1;
-    return t.cap;
-  }
+  if (k == kEmpty) return t.cap;
   const uint64_t mask = (uint64_t)t.cap - 1;
   uint64_t s = 0;
   for (int64_t p = 0; p < t.cap + kGlobalProbes; ++p) {
@@ -296,7 +317,7 @@ __device__ __forceinline__ int64_t global_slot(const Table& t, int64_t k, uint32
       if (prev == kEmpty || prev == k) return (int64_t)s;
     }
   }
-  t.state[1] = 1;  // overflow: more distinct keys than the table holds
+  __hip_atomic_store(&t.state[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // overflow
   return -1;
 }
 
@@ -367,63 +388,63 @@ __global__ void __launch_bounds__(kHistThreads) gb_hist_kernel(Args a) {
   for (int e = threadIdx.x; e < P; e += NT) a.pt.hist[(int64_t)e * a.pt.g1 + blockIdx.x] = h[e];
 }
 
-// One wave per partition: exclusive prefix of its per-workgroup counts, in place.
-__global__ void __launch_bounds__(kThreads) gb_scan_rows_kernel(Args a) {
-  const int lane = threadIdx.x & 63;
-  const int64_t p = (int64_t)blockIdx.x * (kThreads / 64) + threadIdx.x / 64;
-  if (p >= ((int64_t)1 << a.pt.bits)) return;  // whole waves leave together
-  uint32_t* row = a.pt.hist + p * a.pt.g1;
-  const int q = (a.pt.g1 + 63) / 64;
-  uint32_t s = 0;
-  for (int j = 0; j < q; ++j) {
-    const int idx = lane * q + j;
-    if (idx < a.pt.g1) s += row[idx];
-  }
-  uint32_t incl = s;
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += y;
-  }
-  uint32_t run = incl - s;
-  for (int j = 0; j < q; ++j) {
-    const int idx = lane * q + j;
-    if (idx < a.pt.g1) {
-      const uint32_t v = row[idx];
-      row[idx] = run;
-      run += v;
-    }
-  }
-  if (lane == 63) a.pt.tot[p] = incl;
-}
-
-// One workgroup: partition starts, the exclusive prefix of the totals.
-__global__ void __launch_bounds__(kScanThreads) gb_scan_tot_kernel(Args a) {
-  __shared__ uint32_t wsum[kScanThreads / 64];
+// One wave per partition: exclusive prefix of its per-workgroup counts, in
+// place; then, in the last workgroup, the partition starts: the exclusive
+// prefix of the totals.
+__global__ void __launch_bounds__(kThreads) gb_scan_kernel(Args a) {
+  __shared__ uint32_t wsum[kThreads / 64];
   const int P = 1 << a.pt.bits;
-  const int q = (P + kScanThreads - 1) / kScanThreads;
   const int lane = threadIdx.x & 63, w = threadIdx.x / 64;
-  uint32_t sum = 0;
-  for (int j = 0; j < q; ++j) {
-    const int idx = threadIdx.x * q + j;
-    if (idx < P) sum += a.pt.tot[idx];
+  const int64_t p = (int64_t)blockIdx.x * (kThreads / 64) + w;
+  auto prefix = [lane](uint32_t s) {  // inclusive, over the wave
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t y = __shfl_up(s, off, 64);
+      if (lane >= off) s += y;
+    }
+    return s;
+  };
+  if (p < P) {
+    uint32_t* row = a.pt.hist + p * a.pt.g1;
+    const int q = (a.pt.g1 + 63) / 64;
+    uint32_t s = 0;
+    for (int j = 0; j < q; ++j) {
+      const int idx = lane * q + j;
+      if (idx < a.pt.g1) s += row[idx];
+    }
+    const uint32_t incl = prefix(s);
+    uint32_t run = incl - s;
+    for (int j = 0; j < q; ++j) {
+      const int idx = lane * q + j;
+      if (idx < a.pt.g1) {
+        const uint32_t v = row[idx];
+        row[idx] = run;
+        run += v;
+      }
+    }
+    if (lane == 63) __hip_atomic_store(a.pt.tot + p, incl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  uint32_t incl = sum;
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += y;
+  if (!last_to_finish(reinterpret_cast<uint32_t*>(a.t.state + 4))) return;
+  constexpr int Q = (1 << kTileMaxBits) / kThreads;  // totals per thread, at most
+  uint32_t tot[Q], sum = 0;
+#pragma unroll
+  for (int j = 0; j < Q; ++j) {
+    const int idx = (int)threadIdx.x * Q + j;
+    tot[j] = idx < P ? __hip_atomic_load(a.pt.tot + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    sum += tot[j];
   }
+  const uint32_t incl = prefix(sum);
   if (lane == 63) wsum[w] = incl;
   __syncthreads();
   uint32_t run = incl - sum;
   for (int v = 0; v < w; ++v) run += wsum[v];
-  for (int j = 0; j < q; ++j) {
-    const int idx = threadIdx.x * q + j;
-    if (idx < P) {
-      a.pt.start[idx] = run;
-      run += a.pt.tot[idx];
-    }
+#pragma unroll
+  for (int j = 0; j < Q; ++j) {
+    const int idx = (int)threadIdx.x * Q + j;
+    if (idx < P) a.pt.start[idx] = run;
+    run += tot[j];
   }
-  if (threadIdx.x == kScanThreads - 1) a.pt.start[P] = run;  // the last thread ends on the total
+  if (threadIdx.x == kThreads - 1) a.pt.start[P] = run;  // the last thread ends on the total
+  if (threadIdx.x == 0) __hip_atomic_store(&a.t.state[4], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Each row lands at its partition's start + this workgroup's prefix (the
@@ -1111,11 +1132,140 @@ constexpr int kFewGroups = 32;
 constexpr int kFewCopies = 8;
 constexpr int kFewSlots = 128;
 
-__device__ __forceinline__ FloatWindows windows_of(const Table& t) {
+// Where a launch's float-sum windows go, from one row per thread, spread evenly
+// over the launch's n rows (word `at` of every `stride`): the sampled
+// exponents, with most of the slack below them (sums of small parts) and up to
+// 2^8 of room above.  More than kWinSpan exponents take several passes over the
+// rows; a row outside all of them goes to the global table.  Every workgroup
+// reads the same rows and gets the same answer.  (1024 rows:
+// a sample is bound by page-table misses, 4096 rows took 13 to 20 us at 2^28;
+// reduced by shuffles, 2 us: LDS min / max of one address by every lane took 8.)
+__device__ __forceinline__ FloatWindows sample_windows(const uint32_t* words, int stride, int at, int64_t n) {
+  __shared__ int range[2][16];
+  const int64_t row = (int64_t)((uint64_t)n * threadIdx.x / blockDim.x);
+  const int e = (int)((words[row * stride + at] >> 23) & 0xFFu);
+  const bool placed = e != 0 && e != 255;  // zeros, subnormals and non-finite rows do not place a window
+  int emin = placed ? e : 255, emax = placed ? e : 0;
+  for (int off = 32; off >= 1; off >>= 1) {
+    emin = std::min(emin, __shfl_xor(emin, off, 64));
+    emax = std::max(emax, __shfl_xor(emax, off, 64));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    range[0][threadIdx.x / 64] = emin;
+    range[1][threadIdx.x / 64] = emax;
+  }
+  __syncthreads();
+  for (int w = 0; w < (int)blockDim.x / 64; ++w) {
+    emin = std::min(emin, range[0][w]);
+    emax = std::max(emax, range[1][w]);
+  }
+  if (emin > emax) emin = emax = 127;
   FloatWindows f;
-  f.first = t.state[4];
-  f.passes = t.state[5];
+  f.passes = (emax - emin + kWinSpan) / kWinSpan;
+  const int slack = f.passes * kWinSpan - (emax - emin + 1);
+  f.first = std::max(1, emax + std::min(slack / 2, 8) - f.passes * kWinSpan + 1);
   return f;
+}
+
+// ---- emission: the global table's groups to the caller's array ----
+
+template <bool COHERENT, typename T>
+__device__ __forceinline__ T table_load(const T* p) {  // COHERENT: written by this launch's other workgroups
+  return load_partial<COHERENT>(p);
+}
+
+// Writes the used slots of [lo, hi) as groups and clears them (and so leaves
+// the table as the next call needs it: no launch clears it first).  A workgroup
+// takes kEmitSlots slots at a time, the keys in registers; it counts the used
+// ones, takes one output range with a single atomic (updates of one address
+// serialise), and writes each group at its slot's rank, so that a wave's
+// groups leave as one contiguous piece.
+constexpr int kEmitPer = 4;  // slots per thread at a time
+template <int G, bool COHERENT, int NT>
+__device__ __forceinline__ void emit_slots(const Args& a, int64_t lo, int64_t hi) {
+  constexpr int NW = NT / 64, CELLS = kEmitPer * NW;
+  static_assert(CELLS <= 64, "one wave scans the counts");
+  __shared__ uint32_t cell[CELLS];
+  __shared__ unsigned long long base_sh;
+  const Table& t = a.t;
+  const int lane = threadIdx.x & 63, w = threadIdx.x / 64;
+  for (int64_t c0 = lo; c0 < hi; c0 += kEmitPer * NT) {
+    int64_t key[kEmitPer];
+    uint64_t cnt[kEmitPer];
+    uint32_t before[kEmitPer];
+#pragma unroll
+    for (int i = 0; i < kEmitPer; ++i) {
+      const int64_t s = c0 + i * NT + threadIdx.x;
+      key[i] = s < hi && s < t.cap ? table_load<COHERENT>(t.key + s) : kEmpty;
+      // the extra slot's key marks an empty one: its rows tell
+      cnt[i] = s < hi && s == t.cap ? table_load<COHERENT>(t.cnt + s) : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < kEmitPer; ++i) {
+      const uint64_t m = __ballot(key[i] != kEmpty || cnt[i] != 0);
+      before[i] = (uint32_t)__popcll(m & ((1ull << lane) - 1));
+      if (lane == 0) cell[i * NW + w] = (uint32_t)__popcll(m);
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {
+      const uint32_t c = lane < CELLS ? cell[lane] : 0;
+      uint32_t incl = c;
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += y;
+      }
+      if (lane < CELLS) cell[lane] = incl - c;
+      if (lane == 63)
+        base_sh = incl ? atomicAdd(reinterpret_cast<unsigned long long*>(t.state + 2), (unsigned long long)incl) : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kEmitPer; ++i) {
+      const int64_t s = c0 + i * NT + threadIdx.x;
+      if (key[i] == kEmpty && cnt[i] == 0) continue;
+      const unsigned long long my = base_sh + cell[i * NW + w] + before[i];
+      agg_group g;
+      g.key = key[i];
+      g.count = (int64_t)table_load<COHERENT>(t.cnt + s);
+      g.i64 = 0;
+      g.f64 = 0.0;
+      if constexpr (G == G_COUNT) {
+        g.i64 = g.count;
+        g.f64 = (double)g.count;
+      } else if constexpr (G == G_SUM_INT) {
+        g.i64 = table_load<COHERENT>(t.val + s);
+        g.f64 = a.is_avg ? (double)g.i64 / (double)g.count : (double)g.i64;
+      } else if constexpr (G == G_MIN_INT || G == G_MAX_INT) {
+        g.i64 = table_load<COHERENT>(t.val + s);
+        g.f64 = (double)g.i64;
+      } else if constexpr (G == G_SUM_F32) {
+        int64_t d[kDigits];
+#pragma unroll
+        for (int k = 0; k < kDigits; ++k) d[k] = table_load<COHERENT>(t.dig + s * kDigits + k);
+        const double sum = digits_to_double(d, table_load<COHERENT>(t.flags + s));
+        g.f64 = a.is_avg ? sum / (double)g.count : sum;
+      } else {  // float MIN / MAX: NaN when every row of the group is NaN
+        const int64_t v = table_load<COHERENT>(t.val + s);
+        g.f64 = v == val_identity<G>() ? (double)__builtin_nanf("") : (double)f32_unorder((int32_t)v);
+      }
+      clear_slot<G>(t, s);
+      if ((int64_t)my < a.max_groups) a.out[my] = g;
+    }
+    __syncthreads();  // cell and base_sh are free again
+  }
+}
+
+// By the last workgroup to emit, once its groups are written: the number of
+// groups, and a clean state for the next call.
+__device__ __forceinline__ void finish_emission(const Args& a) {
+  if (threadIdx.x != 0) return;
+  unsigned long long* emitted = reinterpret_cast<unsigned long long*>(a.t.state + 2);
+  const unsigned long long e = __hip_atomic_load(emitted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int32_t over = __hip_atomic_load(&a.t.state[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  *a.ngroups = (over || (int64_t)e > a.max_groups) ? -1 : (int64_t)e;
+  __hip_atomic_store(emitted, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(&a.t.state[0], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(&a.t.state[4], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Direct path: every workgroup sweeps its share of the rows' tiles into one
@@ -1136,7 +1286,7 @@ gb_aggregate_kernel(Args a) {
   const uint32_t sub_mask = (1u << a.pt.sub_bits) - 1u;
   const uint32_t sub_shift = a.pt.sub_bits ? (uint32_t)(32 - a.pt.sub_bits) : 0u;
   FloatWindows fw;
-  if constexpr (G == G_SUM_F32) fw = windows_of(a.t);
+  if constexpr (G == G_SUM_F32) fw = sample_windows(static_cast<const uint32_t*>(a.vals), 1, 0, a.n);
   for (uint32_t sub = 0; sub <= sub_mask; ++sub) {
     for (int pass = 0; pass < fw.passes; ++pass) {
       tab.clear((uint32_t)a.pt.sub_bits);
@@ -1148,6 +1298,10 @@ gb_aggregate_kernel(Args a) {
       tab.flush(a.t, fw.base(pass));
       __syncthreads();
     }
+  }
+  if (a.emit && last_to_finish(reinterpret_cast<uint32_t*>(a.t.state + 4))) {
+    emit_slots<G, true, kDirectThreads>(a, 0, a.t.cap + 1);
+    finish_emission(a);
   }
 }
 
@@ -1164,7 +1318,10 @@ __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a)
   __shared__ LdsTable<G, KD, lds_slots<G, KD>(), kPartThreads> tab;
   constexpr int TR = decltype(tab)::template tile_rows_of<VD>() * kPartThreads;
   FloatWindows fw;
-  if constexpr (G == G_SUM_F32) fw = windows_of(a.t);
+  if constexpr (G == G_SUM_F32) {
+    using SR = StagedRow<KD, AGG_F32>;
+    fw = sample_windows(static_cast<const uint32_t*>(a.pt.pk), SR::KW + SR::VW, SR::KW, a.n);
+  }
   const int P = 1 << a.pt.bits;
   int64_t r = a.n * (int64_t)blockIdx.x / gridDim.x;
   const int64_t r1 = a.n * ((int64_t)blockIdx.x + 1) / gridDim.x;
@@ -1196,131 +1353,27 @@ __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a)
   }
 }
 
-// Where the float-sum windows of a run go, from kSampleRows rows spread evenly
-// over it: the sampled exponents, with most of the slack below them (sums of
-// small parts) and up to 2^8 of room above.  More than kWinSpan exponents take
-// several passes over the rows; a row outside all of them goes to the global
-// table.  One workgroup of the init kernel reads the sample while the others
-// clear the table (every aggregation workgroup reading one of its own took
-// 20 us of page-table misses at 2^28 rows).
-constexpr int kSampleRows = 16 * kThreads;
-__device__ __forceinline__ void place_windows(const Args& a) {
-  __shared__ int range[2];
-  if (threadIdx.x == 0) {
-    range[0] = 255;
-    range[1] = 0;
-  }
-  __syncthreads();
-  int emin = 255, emax = 0;
-  if (a.n > 0) {
-#pragma unroll
-    for (int i = 0; i < kSampleRows / kThreads; ++i) {
-      const uint64_t row = (uint64_t)a.n * (uint32_t)(i * kThreads + threadIdx.x) / (uint32_t)kSampleRows;
-      const int e = (int)((static_cast<const uint32_t*>(a.vals)[row] >> 23) & 0xFFu);
-      const bool placed = e != 0 && e != 255;  // zeros, subnormals and non-finite rows do not place a window
-      emin = min(emin, placed ? e : 255);
-      emax = max(emax, placed ? e : 0);
-    }
-  }
-  atomicMin(&range[0], emin);
-  atomicMax(&range[1], emax);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    emin = range[0];
-    emax = range[1];
-    if (emin > emax) emin = emax = 127;
-    const int passes = (emax - emin + kWinSpan) / kWinSpan;
-    const int slack = passes * kWinSpan - (emax - emin + 1);
-    a.t.state[4] = max(1, emax + min(slack / 2, 8) - passes * kWinSpan + 1);
-    a.t.state[5] = passes;
-  }
-}
-
+// Clears the whole table: once, before a plan's first call.
 template <int G>
 __global__ void __launch_bounds__(kThreads) gb_init_kernel(Args a) {
-  const Table& t = a.t;
   const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t s = (int64_t)blockIdx.x * kThreads + threadIdx.x; s <= t.cap; s += stride) {
-    t.key[s] = s == t.cap ? INT64_MIN : kEmpty;
-    t.cnt[s] = 0;
-    t.val[s] = val_identity<G>();
-    t.flags[s] = 0;
-    if constexpr (G == G_SUM_F32)
-      for (int d = 0; d < kDigits; ++d) t.dig[s * kDigits + d] = 0;
+  for (int64_t s = (int64_t)blockIdx.x * kThreads + threadIdx.x; s <= a.t.cap; s += stride) {
+    clear_slot<G>(a.t, s);
+    a.t.flags[s] = 0;
   }
-  if (blockIdx.x == 0 && threadIdx.x < 4) t.state[threadIdx.x] = 0;
-  if constexpr (G == G_SUM_F32)
-    if (blockIdx.x == gridDim.x - 1) place_windows(a);
+  if (blockIdx.x == 0 && threadIdx.x < 8) a.t.state[threadIdx.x] = 0;
 }
 
-// Workgroup w writes the used slots of its contiguous slot range: it counts
-// them, takes one output range with a single atomic, and each thread writes
-// its slots at its prefix within that range (one counter update per
-// workgroup: updates of one address serialise).
+// Each workgroup emits a contiguous slot range; the last one to finish writes
+// the number of groups.
+constexpr int kEmitThreads = 1024;
 template <int G>
-__global__ void __launch_bounds__(kThreads) gb_emit_kernel(Args a) {
-  __shared__ uint32_t wsum[kThreads / 64];
-  __shared__ unsigned long long base_sh;
-  const Table& t = a.t;
-  const int64_t slots = t.cap + 1;
+__global__ void __launch_bounds__(kEmitThreads) gb_emit_kernel(Args a) {
+  const int64_t slots = a.t.cap + 1;
   const int64_t per = ceil_div_dev(slots, gridDim.x);
   const int64_t lo = (int64_t)blockIdx.x * per;
-  const int64_t hi = std::min<int64_t>(lo + per, slots);
-  auto used = [&](int64_t s) { return s < t.cap ? t.key[s] != kEmpty : t.state[0] != 0; };
-  uint32_t mine = 0;
-  for (int64_t s = lo + threadIdx.x; s < hi; s += kThreads) mine += used(s) ? 1u : 0u;
-  // exclusive prefix of the per-thread counts over the workgroup
-  const int lane = threadIdx.x & 63, w = threadIdx.x / 64;
-  uint32_t incl = mine;
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += y;
-  }
-  if (lane == 63) wsum[w] = incl;
-  __syncthreads();
-  uint32_t before = incl - mine, total = 0;
-  for (int v = 0; v < kThreads / 64; ++v) {
-    if (v < w) before += wsum[v];
-    total += wsum[v];
-  }
-  if (threadIdx.x == 0)
-    base_sh = total ? atomicAdd(reinterpret_cast<unsigned long long*>(t.state + 2), (unsigned long long)total) : 0;
-  __syncthreads();
-  unsigned long long idx = base_sh + before;
-  for (int64_t s = lo + threadIdx.x; s < hi; s += kThreads) {
-    if (!used(s)) continue;
-    const unsigned long long my = idx++;
-    if ((int64_t)my >= a.max_groups) continue;
-    agg_group g;
-    g.key = t.key[s];
-    g.count = (int64_t)t.cnt[s];
-    g.i64 = 0;
-    g.f64 = 0.0;
-    if constexpr (G == G_COUNT) {
-      g.i64 = g.count;
-      g.f64 = (double)g.count;
-    } else if constexpr (G == G_SUM_INT) {
-      g.i64 = t.val[s];
-      g.f64 = a.is_avg ? (double)g.i64 / (double)g.count : (double)g.i64;
-    } else if constexpr (G == G_MIN_INT || G == G_MAX_INT) {
-      g.i64 = t.val[s];
-      g.f64 = (double)g.i64;
-    } else if constexpr (G == G_SUM_F32) {
-      const double sum = digits_to_double(t.dig + s * kDigits, t.flags[s]);
-      g.f64 = a.is_avg ? sum / (double)g.count : sum;
-    } else {  // float MIN / MAX: NaN when every row of the group is NaN
-      const int64_t v = t.val[s];
-      g.f64 = v == val_identity<G>() ? (double)__builtin_nanf("") : (double)f32_unorder((int32_t)v);
-    }
-    a.out[my] = g;
-  }
-}
-
-__global__ void gb_finish_kernel(Args a) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    const unsigned long long e = *reinterpret_cast<const unsigned long long*>(a.t.state + 2);
-    *a.ngroups = (a.t.state[1] || (int64_t)e > a.max_groups) ? -1 : (int64_t)e;
-  }
+  emit_slots<G, false, kEmitThreads>(a, lo, std::min<int64_t>(lo + per, slots));
+  if (last_to_finish(reinterpret_cast<uint32_t*>(a.t.state + 4))) finish_emission(a);
 }
 
 // ---- kernel tables ----
@@ -1462,6 +1515,7 @@ struct agg_groupby_s {
   Part pt{};           // bits == 0: the direct path
   int path = 0;        // 0 direct, 1 partitioned, 2 few groups, 3 / 4: 0 / 1 in sub-partition passes
   int agg_blocks = 1;  // aggregation workgroups resident per CU
+  bool clean = false;  // the table and its state are as a call needs them
 };
 
 extern "C" {
@@ -1595,13 +1649,30 @@ int agg_groupby_run(agg_groupby_t p, const void* keys, const void* vals, int64_t
   a.ngroups = ngroups;
   a.is_avg = p->op == AGG_AVG;
   a.op = p->op;
-  const int64_t table_grid = std::max<int64_t>(1, std::min<int64_t>(ceil_div(p->t.cap + 1, kThreads), (int64_t)cu * 8));
-  rc = launch(init_kernel(p->gop), (int)table_grid, kThreads, &a, stream);
-  if (rc != AGG_OK) return rc;
+  // The table is clean between calls (each clears what it emits); a plan's
+  // first call clears it, and so does one after a launch that failed.  A call
+  // recorded into a graph with the clearing in it leaves it to the replays.
+  const bool first = !p->clean;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (first && hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    cap = hipStreamCaptureStatusActive;
+  }
+  p->clean = false;
+  const int64_t slots = p->t.cap + 1;
+  if (first) {
+    rc = launch(init_kernel(p->gop), (int)std::min<int64_t>(ceil_div(slots, kThreads), (int64_t)cu * 8), kThreads, &a, stream);
+    if (rc != AGG_OK) return rc;
+  }
   if (n > 0 && p->pt.bits == 0) {
-    const int64_t grid =
-        std::max<int64_t>(ceil_div(n, kMaxTableRows),
-                          std::min<int64_t>(ceil_div(n, kDirectThreads * 16), (int64_t)cu * p->agg_blocks));
+    // Two tiles per workgroup at least, so that its table's flush serves more
+    // rows (1e6 rows, int32 keys and values: 1000 groups 37.4 us, 38.5 with one
+    // tile; float SUM 53.1, 64.6).  The few-groups table's flush is nothing, so
+    // one tile (25 groups 15.1 us either way).
+    const int64_t wg_rows = kDirectThreads * (p->path == 2 ? 8 : 16);
+    const int64_t grid = std::max<int64_t>(ceil_div(n, kMaxTableRows),
+                                           std::min<int64_t>(ceil_div(n, wg_rows), (int64_t)cu * p->agg_blocks));
+    a.emit = slots <= fuse_slots_of(p->gop);
     rc = launch(agg_kernel(p->key_dtype, p->val_dtype, p->gop, p->path), (int)grid, kDirectThreads, &a, stream);
     if (rc != AGG_OK) return rc;
   } else if (n > 0) {
@@ -1620,11 +1691,8 @@ int agg_groupby_run(agg_groupby_t p, const void* keys, const void* vals, int64_t
       a.pt.g1 = (int)std::min<int64_t>(kMaxHistWg, ceil_div(m, kMinHistRows));
       a.pt.rows_per_wg = ceil_div(m, a.pt.g1);
       if ((rc = launch_lds(hist, a.pt.g1, kHistThreads, 0, &a, stream)) != AGG_OK) return rc;
-      if ((rc = launch_lds(reinterpret_cast<const void*>(&gb_scan_rows_kernel), ceil_div(P, kThreads / 64), kThreads,
-                           0, &a, stream)) != AGG_OK)
-        return rc;
-      if ((rc = launch_lds(reinterpret_cast<const void*>(&gb_scan_tot_kernel), 1, kScanThreads, 0, &a, stream)) !=
-          AGG_OK)
+      if ((rc = launch_lds(reinterpret_cast<const void*>(&gb_scan_kernel), ceil_div(P, kThreads / 64), kThreads, 0, &a,
+                           stream)) != AGG_OK)
         return rc;
       if ((rc = launch_lds(scat, a.pt.g1, kTileThreads, 0, &a, stream)) != AGG_OK)
         return rc;
@@ -1637,9 +1705,12 @@ int agg_groupby_run(agg_groupby_t p, const void* keys, const void* vals, int64_t
     a.vals = vals;
     a.n = n;
   }
-  rc = launch(emit_kernel(p->gop), (int)table_grid, kThreads, &a, stream);
-  if (rc != AGG_OK) return rc;
-  return launch(reinterpret_cast<const void*>(&gb_finish_kernel), 1, 64, &a, stream);
+  if (!a.emit) {
+    const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(ceil_div(slots, kEmitPer * kEmitThreads), (int64_t)cu * 2));
+    if ((rc = launch(emit_kernel(p->gop), (int)grid, kEmitThreads, &a, stream)) != AGG_OK) return rc;
+  }
+  p->clean = !(first && cap != hipStreamCaptureStatusNone);
+  return AGG_OK;
 }
 
 int agg_groupby_destroy(agg_groupby_t p) {

@@ -1,0 +1,71 @@
+"""GPU: a group-by plan's calls one after another, against the oracle.
+
+A call leaves the plan's table clean for the next (the emission clears the
+slots it reads), so each kind of call is followed by others on the same plan:
+no rows, more keys than the plan allows, a call recorded into a graph and
+replayed.  Table sizes either side of the one-launch limit and the partitioned
+path.  All results are exact."""
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_groupby import agg, compare, make_vals  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("groups", [3, 30, 200, 1000, 3000, 40_000])
+@pytest.mark.parametrize("vdt,op", [("i32", "sum"), ("f32", "sum"), ("i64", "max"), ("f32", "min"), ("i32", "count")])
+def test_calls_of_one_plan(agg, groups, vdt, op):
+    import torch
+    r = np.random.default_rng(groups)
+    n = 60_000
+    g = agg.GroupBy("i32", vdt, op, max_n=4 * n, max_groups=groups)
+
+    def call(m, keyset, seed):
+        keys = r.choice(keyset, size=m).astype(np.int32)
+        keys[:min(m, 1)] = np.iinfo(np.int32).min
+        vals = make_vals(m, vdt, seed=seed)
+        return keys, vals, torch.from_numpy(keys).cuda(), torch.from_numpy(vals).cuda()
+
+    def check(m, keyset, seed, what):
+        keys, vals, dk, dv = call(m, keyset, seed)
+        compare(g.run(dk, dv), oracle.groupby(keys, vals, op), f"{what} {vdt} {op} groups={groups}")
+
+    a = r.integers(-2**31, 2**31, size=max(1, groups // 2), dtype=np.int64)
+    b = r.integers(-2**31, 2**31, size=max(1, groups // 3), dtype=np.int64)
+    many = np.arange(min(4 * n, 3 * groups + 100), dtype=np.int32)  # more than the plan allows
+    dk, dv = torch.from_numpy(many).cuda(), torch.from_numpy(make_vals(many.size, vdt, seed=9)).cuda()
+    check(n, a, 1, "first")
+    check(n, b, 2, "second")
+    assert g.run(dk[:0], dv[:0]) == []
+    check(1, b, 3, "one row")
+    assert g.run(dk, dv) is None
+    check(n, a, 4, "after too many keys")
+
+    # recorded and replayed: by a plan that has run, and by one whose first call is the recorded one
+    for fresh in (False, True):
+        if fresh:
+            g.close()
+            g = agg.GroupBy("i32", vdt, op, max_n=4 * n, max_groups=groups)
+        out = torch.empty(groups * agg.GROUP_BYTES, dtype=torch.uint8, device="cuda")
+        ng = torch.zeros(1, dtype=torch.int64, device="cuda")
+        _, _, sk, sv = call(n, a, 5)
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            g.enqueue(sk, sv, out, ng, stream=s)
+        for rep in range(3):
+            keys, vals, tk, tv = call(n, b if rep == 1 else a, 6 + rep)
+            sk.copy_(tk)
+            sv.copy_(tv)
+            graph.replay()
+            torch.cuda.synchronize()
+            m = int(ng.item())
+            raw = out[:m * agg.GROUP_BYTES].cpu().numpy().tobytes()
+            gs = [agg.Group.from_buffer_copy(raw, i * agg.GROUP_BYTES) for i in range(m)]
+            got = sorted(((x.key, x.i64, x.f64, x.count) for x in gs), key=lambda t: t[0])
+            compare(got, oracle.groupby(keys, vals, op), f"replay {rep} fresh={fresh} {vdt} {op} groups={groups}")
+            check(n, b, 20 + rep, "between replays")
+    g.close()
