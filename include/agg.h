@@ -98,7 +98,9 @@ typedef struct agg_tune {
                                  capped by the work available */
     int32_t unroll;           /* 4, 8, 16 or 32 outstanding 16-byte loads per lane */
     int32_t nontemporal;      /* 1: streaming (non-temporal) loads */
-    int64_t chunk_bytes;      /* PINNED_HOST: bytes per staged chunk */
+    int64_t chunk_bytes;      /* PINNED_HOST: bytes per staged chunk (plans without
+                                 given or cached parameters read the column
+                                 over the link instead of staging it) */
     int32_t staging_depth;    /* PINNED_HOST: chunks in flight, 2..4 */
     int32_t reserved;
 } agg_tune;

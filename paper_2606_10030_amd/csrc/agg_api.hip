@@ -619,7 +619,26 @@ int agg_run(agg_plan_t p, const void* col, int64_t n, agg_result* out, void* str
   if (p->src != AGG_SRC_PINNED_HOST || n == 0)
     return enqueue_resident(p->kind, p->dtype, p->op, p->prec, t, cu, col, n, out, p->part, p->done, stream);
 
-  // Pinned host: copy chunks of whole segments into the staging ring on the
+  // Pinned host, without given or cached parameters: the scan reads the column
+  // over the link itself, if the device can address it.  It does so at the
+  // link's rate (57.4 GB/s; the staged copies 55.5, and 33 to 43 for a second
+  // after device memory is freed, when the copy engines are busy) and has no
+  // copies to wait for: int32 SUM 256 MiB 4834 -> 4675 us, 4 MiB 121 -> 82,
+  // float 1 MiB 66 -> 25.
+  void* mapped = nullptr;
+  if (p->tune_builtin) {
+    if (hipHostGetDevicePointer(&mapped, const_cast<void*>(col), 0) != hipSuccess) {
+      (void)hipGetLastError();
+      mapped = nullptr;
+    }
+    if (mapped) {
+      agg_tune z;
+      builtin_tune_for(p->kind, AGG_SRC_ZEROCOPY, bytes, &z);
+      return enqueue_resident(p->kind, p->dtype, p->op, p->prec, z, cu, mapped, n, out, p->part, p->done, stream);
+    }
+  }
+
+  // Otherwise: copy chunks of whole segments into the staging ring on the
   // copy stream while the scan of earlier chunks runs on `stream`.
   const void* fn = scan_kernel_ptr(p->kind, t.unroll, t.nontemporal != 0);
   if (!fn) return AGG_E_INVALID;

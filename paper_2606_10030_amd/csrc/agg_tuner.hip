@@ -64,6 +64,11 @@ int bucket_of(int64_t bytes) {  // ceil(log2(bytes)), at least 10
 // float SUM 4 MB 11.2 -> 10.2, 16 MB 20.3 -> 14.7, 48 MB 25.0 -> 21.8, 130 MB
 // 38.8 -> 34.3, 300 MB 63.1 -> 59.5.  Up to 1024 segments (16 MB) the shapes keep
 // to one workgroup per CU, so that the scan's last workgroup may merge.
+//
+// Columns read from host memory are bound by the link (57.4 GB/s), which one
+// wave per CU with 4 loads in flight (1 MiB in all) fills; more of them queue at
+// it and leave an uneven end: int32 SUM 256 MiB 4675 us, with 4 waves and 8
+// loads 4807; float 64 MiB 1180 and 1245; int64 MIN 32 MiB 594 and 659.
 void builtin_for(int kind, int32_t src, int64_t bytes, agg_tune* t) {
   t->nontemporal = 1;
   t->chunk_bytes = 64ll << 20;
@@ -74,6 +79,10 @@ void builtin_for(int kind, int32_t src, int64_t bytes, agg_tune* t) {
     t->blocks_per_cu = blocks;
     t->unroll = unroll;
   };
+  if (src == AGG_SRC_ZEROCOPY) {
+    shape(1, 1, 4);
+    return;
+  }
   const int64_t nseg = bytes / kSegMin;  // 16 KiB segments, below 128 MiB
   const bool small = src == AGG_SRC_DEVICE && bytes < (128ll << 20), mid = src == AGG_SRC_DEVICE && bytes < (256ll << 20);
   const bool narrow_minmax = kind == K_MIN_I32 || kind == K_MAX_I32 || kind == K_MIN_F32 || kind == K_MAX_F32;
@@ -148,6 +157,7 @@ std::vector<agg_tune> kernel_candidates(int kind, int32_t src, int64_t bytes) {
   agg_tune base;
   builtin_for(kind, src, bytes, &base);
   const int wb[][2] = {{1, 2}, {2, 1}, {4, 1}, {1, 3}, {2, 2}, {4, 2}, {8, 1}, {1, 4}};
+  if (src == AGG_SRC_ZEROCOPY) v.push_back(base);
   for (int u : {8, 16, 32})
     for (auto& p : wb) {
       agg_tune t = base;
