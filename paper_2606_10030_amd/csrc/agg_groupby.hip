@@ -738,17 +738,24 @@ constexpr int row_words() {
 // wave instruction whose rows share a key spread over REP addresses (LDS
 // atomics on one address serialise), and the flush merges the copies (exact
 // integer merges: the results do not depend on REP).
-template <int G, int KD, int L_, int NT, int REP = 1>
+// HOT: the table finds a key that most of its rows have, and gives each lane an
+// entry for it (find_hot).
+template <int G, int KD, int L_, int NT, int REP = 1, bool HOT = false>
 struct LdsTable {
   using KT = typename std::conditional<KD == AGG_I32, int32_t, int64_t>::type;
   using UKT = typename std::conditional<KD == AGG_I32, unsigned int, unsigned long long>::type;
   static constexpr KT kMark = std::numeric_limits<KT>::min();  // empty hashed slot
   static constexpr int L = L_;
   static constexpr int kLog2L = __builtin_ctz((unsigned)L_);
-  static constexpr int E = (L + 1) * REP;  // accumulator entries: slot s, copy c at s * REP + c
+  // Accumulator entries: slot s, copy c at s * REP + c; then one per lane for
+  // the hot slot's rows (find_hot).
+  static constexpr int kHotLanes = HOT ? 64 : 0;
+  static constexpr int E = (L + 1) * REP + kHotLanes;
+  static constexpr uint32_t kNoHot = ~0u;
   static constexpr bool kDig = G == G_SUM_F32;
   static constexpr bool kVal = !kDig && G != G_COUNT;
   static_assert((REP & (REP - 1)) == 0 && REP <= 64, "copies: a power of two, at most a wave");
+  static_assert(!HOT || REP == 1, "one kind of copies");
   static_assert((L & (L - 1)) == 0, "home_of takes log2(L) hash bits");
   // Rows a thread folds at a time (two batches are in registers: the next
   // one's loads are in flight): 8, or 4 where a row has four 32-bit words (8
@@ -760,6 +767,7 @@ struct LdsTable {
   int64_t val[kVal ? E : 1];
   int64_t win[kDig ? kWindows * E : 1];    // float sum: window w of entry e at w * E + e
   uint32_t flags[kDig ? L / 8 + 1 : 1];    // float sum: non-finite rows seen, four bits a slot
+  uint32_t hot_sh;                         // the hot slot + 1; 0: there is none
 
   __device__ __forceinline__ void clear(uint32_t skip) {
     // The marker key's home holds key 0 from the start: a row of the marker key
@@ -776,6 +784,69 @@ struct LdsTable {
     }
     if constexpr (kDig)
       for (int e = threadIdx.x; e <= L / 8; e += NT) flags[e] = 0;
+    if (HOT && threadIdx.x == 0) hot_sh = 0;
+  }
+
+  // The table's hot slot, if the home slots of its first batch show one to this
+  // wave (or an earlier one to another wave), else kNoHot.  LDS atomics of a wave
+  // on one address serialise, so a table whose rows are mostly one key's (one
+  // partition of a skewed column) was bound by them: each lane adds the hot
+  // slot's rows to an entry of its own instead, and merge_hot adds those to the
+  // slot.  A wave proposes the slot that the most lanes share in any of its rows
+  // (eight lanes or more); the table takes the first one proposed, which is
+  // mostly the hottest.  Which it is, and which waves know of it, does not show
+  // in the sums.  Partitioned path only: there a skewed column's few hottest
+  // keys fill whole partitions, and the workgroups on those ended last (the
+  // direct path spreads them over all tables, and lost more by the extra
+  // instructions than it won: 4096 groups 219 -> 226 us).  60M rows, 50 000
+  // keys of probability ~ 1/rank (uniform ones in brackets): int32 SUM 587 ->
+  // 454 us (439 -> 444), COUNT 388 -> 330 (322 -> 328), float SUM 612 -> 522
+  // (518 -> 519), int64 SUM 875 -> 764 (767 -> 761); 2^20 keys: int32 SUM 749 ->
+  // 609 (615 -> 618).
+  template <int R>
+  __device__ __forceinline__ uint32_t find_hot(const uint32_t (&home)[R]) {
+    uint32_t best = 0;  // lanes << 16 | slot
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)home[r]);
+      best = max(best, (uint32_t)__popcll(__ballot(home[r] == s)) << 16 | s);
+    }
+    if (best < 8u << 16) return kNoHot;
+    const uint32_t cand = best & 0xFFFFu;
+    uint32_t prev = 0;
+    if ((threadIdx.x & 63) == 0) prev = atomicCAS(&hot_sh, 0u, cand + 1);
+    prev = (uint32_t)__builtin_amdgcn_readfirstlane((int)prev);
+    return prev ? prev - 1 : cand;
+  }
+  __device__ __forceinline__ uint32_t hot_slot() const {
+    const uint32_t h = (uint32_t)__builtin_amdgcn_readfirstlane((int)hot_sh);
+    return h - 1;  // 0: none
+  }
+  // The entry that this lane's row of slot s goes to.
+  static __device__ __forceinline__ int entry_of(uint32_t s, uint32_t hot) {
+    if constexpr (HOT) return (int)(s == hot ? L + 1 + (threadIdx.x & 63) : s);
+    else return (int)(s * REP + (threadIdx.x & (REP - 1)));
+  }
+  // Between the fold's barrier and the flush.
+  __device__ __forceinline__ void merge_hot() {
+    if constexpr (kHotLanes != 0) {
+      const uint32_t hot = hot_slot();
+      if (hot == kNoHot) return;  // the whole workgroup
+      if (threadIdx.x < 64) {
+        const int e = L + 1 + threadIdx.x;
+        at_add<true>(&cnt[hot], cnt[e]);
+        if constexpr (kVal) {
+          if constexpr (G == G_SUM_INT)
+            at_add<true>(reinterpret_cast<unsigned long long*>(&val[hot]), (unsigned long long)val[e]);
+          else if constexpr (G == G_MIN_INT || G == G_MIN_F32) atomicMin(reinterpret_cast<long long*>(&val[hot]), (long long)val[e]);
+          else atomicMax(reinterpret_cast<long long*>(&val[hot]), (long long)val[e]);
+        }
+        if constexpr (kDig)
+          for (int w = 0; w < kWindows; ++w)
+            at_add<true>(reinterpret_cast<unsigned long long*>(&win[w * E + hot]), (unsigned long long)win[w * E + e]);
+      }
+      __syncthreads();
+    }
   }
 
   // The home slot of a key with hash h: the log2(L) hash bits below the
@@ -852,6 +923,7 @@ struct LdsTable {
       Row x[R];
     };
     const uint32_t tid = threadIdx.x;
+    uint32_t hot = kNoHot;
     // a float's exponent is compared in place, as the top byte of its bits << 1
     // less the pass's first exponent (exponents below it wrap past the span);
     // no pass takes out_from and up, seen from the first one (zeros, subnormals
@@ -943,7 +1015,6 @@ struct LdsTable {
       // would also wait for the atomics of the rows before it
 #pragma unroll
       for (int r = 0; r < R; ++r) __asm__ volatile("" : "+v"(cur[r]));
-      const int copy = (int)(tid & (REP - 1));  // this lane's copy of the accumulators
       if constexpr (!SUB) {
         // Nearly every batch of a wave: each row of each lane finds its key at
         // home (and its float in a window), tested for all of them at once, so
@@ -958,7 +1029,7 @@ struct LdsTable {
         if (full && __all(differ == 0 && (!kDig || far < win_span))) {
 #pragma unroll
           for (int r = 0; r < R; ++r) {
-            const int s = (int)home[r] * REP + copy;
+            const int s = entry_of(home[r], hot);
             if constexpr (kDig) {
               const uint32_t fb = __float_as_uint(b.x[r].fv);
               at_add<true>(&cnt[s], 1u);
@@ -995,7 +1066,7 @@ struct LdsTable {
         bool mine = full || row_at(r) < left;
         if constexpr (SUB) mine = mine && ((key_hash<KD>(k) >> sub_shift) & sub_mask) == sub;
         const bool hit = cur[r] == k && k != kMark && mine;
-        const int s = (int)home[r] * REP + copy;
+        const int s = entry_of(home[r], hot);
         bool miss = mine && !hit;
         if constexpr (kDig) {
           const uint32_t fb = __float_as_uint(b.x[r].fv), u = (fb << 1) + win_off;
@@ -1026,7 +1097,7 @@ struct LdsTable {
         const bool in = !kDig || u < win_span || x.fv == 0.0f || nonfinite;  // an LDS slot can take it
         const int slot = in ? slot_of(x.k, h, skip) : -1;
         if (slot >= 0) {
-          const int s = slot * REP + copy;
+          const int s = entry_of((uint32_t)slot, hot);
           if constexpr (kDig) {
             at_add<true>(&cnt[s], 1u);
             if (u < win_span) add_window(s, fb, u);
@@ -1046,6 +1117,12 @@ struct LdsTable {
     Batch A;
     if (b + TR <= last) {
       load(A, b);
+      if constexpr (kHotLanes != 0 && !SUB) {
+        uint32_t home[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) home[r] = home_of(key_hash<KD>(A.x[r].k), skip);
+        hot = find_hot<R>(home);
+      }
       for (;;) {
         const int64_t next = b + tile_step;
         const bool more = next + TR <= last;
@@ -1295,6 +1372,7 @@ gb_aggregate_kernel(Args a) {
                                              (int64_t)gridDim.x * TR, (uint32_t)a.pt.sub_bits, sub_shift, sub_mask, sub,
                                              fw, pass);
       __syncthreads();
+      tab.merge_hot();
       tab.flush(a.t, fw.base(pass));
       __syncthreads();
     }
@@ -1315,7 +1393,7 @@ gb_aggregate_kernel(Args a) {
 // the key's hash) and flushing the table after it.
 template <int KD, int VD, int G, bool SUB>
 __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a) {
-  __shared__ LdsTable<G, KD, lds_slots<G, KD>(), kPartThreads> tab;
+  __shared__ LdsTable<G, KD, lds_slots<G, KD>(), kPartThreads, 1, !SUB> tab;
   constexpr int TR = decltype(tab)::template tile_rows_of<VD>() * kPartThreads;
   FloatWindows fw;
   if constexpr (G == G_SUM_F32) {
@@ -1345,7 +1423,8 @@ __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a)
         tab.template fold_rows<VD, true, SUB>(a.t, a.pt.pk, a.pt.pv, r, seg_end, TR,
                                               (uint32_t)(a.pt.bits + a.pt.sub_bits), sub_shift, sub_mask, sub, fw, pass);
         __syncthreads();
-        tab.flush(a.t, fw.base(pass));
+        tab.merge_hot();
+      tab.flush(a.t, fw.base(pass));
         __syncthreads();
       }
     }
