@@ -49,7 +49,14 @@ constexpr int kThreads = 256;
 constexpr int kLdsProbes = 16;
 constexpr int kGlobalProbes = 32;     // hashed probes of the global table, then linear ones
 constexpr int kMaxPartBits = 14;      // at most 16384 (sub-)partitions
-constexpr int kMinPartBits = 5;       // at least 32
+// At least 128 partitions (64 for 2^25 rows and more): with fewer than there are
+// aggregation workgroups, several flush the same keys, and their device-scope
+// atomics meet on the same addresses; more shorten the scatter's runs.  32 / 64
+// / 128 / 256 partitions, 50 000 groups: float SUM of 1.7M rows 111 / 83 / 69 / 72
+// us, int32 SUM 75 / 62 / 57 / 63, of 6M rows 106 / 90 / 83 / 83, of 60M rows
+// 420 / 411 / 422 / 439.
+constexpr int kMinPartBits = 7, kMinPartBitsLarge = 6;
+constexpr int64_t kLargeRows = (int64_t)1 << 25;
 // Rows are partitioned in chunks of up to 2^28: every chunk ends with each
 // aggregation workgroup flushing the groups it holds, so fewer, larger
 // chunks flush less (the staging area holds one chunk: up to 4 GiB).
@@ -767,6 +774,7 @@ struct LdsTable {
   int64_t val[kVal ? E : 1];
   int64_t win[kDig ? kWindows * E : 1];    // float sum: window w of entry e at w * E + e
   uint32_t flags[kDig ? L / 8 + 1 : 1];    // float sum: non-finite rows seen, four bits a slot
+  uint16_t list[NT / 64][128];             // per wave: slots to flush
   uint32_t hot_sh;                         // the hot slot + 1; 0: there is none
 
   __device__ __forceinline__ void clear(uint32_t skip) {
@@ -1140,58 +1148,92 @@ struct LdsTable {
     }
   }
 
-  __device__ __forceinline__ void flush(const Table& t, uint32_t win_base) {
+  // Adds entry e (which has rows) to the global table.
+  __device__ __forceinline__ void flush_entry(const Table& t, int e, uint32_t win_base) {
+    const KT k = e < L ? key[e] : kMark;
+    uint64_t c = 0;
+    for (int r = 0; r < REP; ++r) c += cnt[e * REP + r];
+    const int64_t g = global_slot(t, (int64_t)k, key_hash<KD>(k));
+    if (g < 0) return;
+    atomicAdd(reinterpret_cast<unsigned long long*>(t.cnt + g), (unsigned long long)c);
+    if constexpr (kVal) {
+      int64_t v = val[e * REP];
+      for (int r = 1; r < REP; ++r) {
+        const int64_t w = val[e * REP + r];
+        if constexpr (G == G_SUM_INT) v = (int64_t)((uint64_t)v + (uint64_t)w);
+        else if constexpr (G == G_MIN_INT || G == G_MIN_F32) v = w < v ? w : v;
+        else v = w > v ? w : v;
+      }
+      if constexpr (G == G_SUM_INT) atomicAdd(reinterpret_cast<unsigned long long*>(t.val + g), (unsigned long long)v);
+      if constexpr (G == G_MIN_INT || G == G_MIN_F32) atomicMin(reinterpret_cast<long long*>(t.val + g), (long long)v);
+      if constexpr (G == G_MAX_INT || G == G_MAX_F32) atomicMax(reinterpret_cast<long long*>(t.val + g), (long long)v);
+    }
+    if constexpr (kDig) {
+      const int32_t f = (int32_t)((flags[e >> 3] >> (4 * (e & 7))) & 7u);
+      if (f) atomicOr(t.flags + g, f);
+      // The windows' total, a whole number of 2^(base - 150), as 32-bit digits
+      // from digit (base - 1) / 32 on: three unsigned ones and a signed top one.
+      // Digit 8 takes all there is from it on (floats end at 2^128, which
+      // keeps that below 2^53 over 2^31 rows).
+      __int128 sum = 0;
+      for (int w = kWindows - 1; w >= 0; --w) {
+        uint64_t v = 0;  // the copies' rows are at most kMaxTableRows in all
+        for (int r = 0; r < REP; ++r) v += (uint64_t)win[w * E + e * REP + r];
+        sum = sum * (1 << kWinOctaves) + (int64_t)v;
+      }
+      const int d = ((int)win_base - 1) >> 5;
+      sum *= (int64_t)1 << (((int)win_base - 1) & 31);
+      unsigned long long* dig = reinterpret_cast<unsigned long long*>(t.dig + g * kDigits + d);
+      for (int i = 0; i < 4; ++i) {
+        const bool top = i == 3 || d + i == kDigits - 1;
+        const int64_t v = top ? (int64_t)(sum >> (32 * i)) : (int64_t)(uint32_t)(sum >> (32 * i));
+        if (v) atomicAdd(dig + i, (unsigned long long)v);
+        if (top) break;
+      }
+    }
+  }
+
+  // A slot's flush is a chain of device-scope accesses (read the global home,
+  // claim it, add: 2 us), so a wave first lists its slots with rows, and flushes
+  // 64 listed ones at a time: a table of few keys takes one such chain per wave
+  // instead of one for every 64 slots.  1e5 rows, int32 keys: COUNT of 2000
+  // groups 55.6 -> 31.5 us, of 50 000 159 -> 85, int32 SUM 122 -> 80.
+  // Not where many workgroups have the same keys (direct path): more of them
+  // would claim a key at the same moment (6M rows, 2000 groups, 256 workgroups:
+  // COUNT 56.5 -> 72.4 us; 31 workgroups 54.9 -> 34.6).
+  __device__ __forceinline__ void flush(const Table& t, uint32_t win_base, bool listed) {
     // Every workgroup's table holds its keys in about the same slots (same
     // hash), so flushing all tables in slot order would have every workgroup
     // update the same global slots at the same moment, and device-scope
     // atomics on one address serialise.  Each workgroup starts its pass at
     // its own offset instead (2^28 rows, 1024 groups: COUNT 0.43 -> 0.39 ms;
     // the other cases within noise).
-    const int off = (int)(((uint32_t)blockIdx.x * 2654435761u) % (uint32_t)(L + 1));
-    for (int i = threadIdx.x; i <= L; i += NT) {
-      const int e = i + off <= L ? i + off : i + off - (L + 1);
-      const KT k = e < L ? key[e] : kMark;
-      uint64_t c = 0;
-      for (int r = 0; r < REP; ++r) c += cnt[e * REP + r];
-      if (c == 0) continue;
-      const int64_t g = global_slot(t, (int64_t)k, key_hash<KD>(k));
-      if (g < 0) continue;
-      atomicAdd(reinterpret_cast<unsigned long long*>(t.cnt + g), (unsigned long long)c);
-      if constexpr (kVal) {
-        int64_t v = val[e * REP];
-        for (int r = 1; r < REP; ++r) {
-          const int64_t w = val[e * REP + r];
-          if constexpr (G == G_SUM_INT) v = (int64_t)((uint64_t)v + (uint64_t)w);
-          else if constexpr (G == G_MIN_INT || G == G_MIN_F32) v = w < v ? w : v;
-          else v = w > v ? w : v;
-        }
-        if constexpr (G == G_SUM_INT) atomicAdd(reinterpret_cast<unsigned long long*>(t.val + g), (unsigned long long)v);
-        if constexpr (G == G_MIN_INT || G == G_MIN_F32) atomicMin(reinterpret_cast<long long*>(t.val + g), (long long)v);
-        if constexpr (G == G_MAX_INT || G == G_MAX_F32) atomicMax(reinterpret_cast<long long*>(t.val + g), (long long)v);
-      }
-      if constexpr (kDig) {
-        const int32_t f = (int32_t)((flags[e >> 3] >> (4 * (e & 7))) & 7u);
-        if (f) atomicOr(t.flags + g, f);
-        // The windows' total, a whole number of 2^(base - 150), as 32-bit digits
-        // from digit (base - 1) / 32 on: three unsigned ones and a signed top one.
-        // Digit 8 takes all there is from it on (floats end at 2^128, which
-        // keeps that below 2^53 over 2^31 rows).
-        __int128 sum = 0;
-        for (int w = kWindows - 1; w >= 0; --w) {
-          uint64_t v = 0;  // the copies' rows are at most kMaxTableRows in all
-          for (int r = 0; r < REP; ++r) v += (uint64_t)win[w * E + e * REP + r];
-          sum = sum * (1 << kWinOctaves) + (int64_t)v;
-        }
-        const int d = ((int)win_base - 1) >> 5;
-        sum *= (int64_t)1 << (((int)win_base - 1) & 31);
-        unsigned long long* dig = reinterpret_cast<unsigned long long*>(t.dig + g * kDigits + d);
-        for (int i = 0; i < 4; ++i) {
-          const bool top = i == 3 || d + i == kDigits - 1;
-          const int64_t v = top ? (int64_t)(sum >> (32 * i)) : (int64_t)(uint32_t)(sum >> (32 * i));
-          if (v) atomicAdd(dig + i, (unsigned long long)v);
-          if (top) break;
+    const int off = (int)(blockIdx.x * 2654435761u >> 16);
+    const int lane = threadIdx.x & 63;
+    volatile uint16_t* mine = list[threadIdx.x / 64];
+    uint32_t pending = 0;  // listed slots, the same in all lanes
+    for (int i = threadIdx.x; i < L; i += NT) {
+      const int e = (i + off) & (L - 1);
+      uint32_t c = 0;
+      for (int r = 0; r < REP; ++r) c |= cnt[e * REP + r];
+      int take = c != 0 ? e : -1;  // the slot this lane flushes
+      if (listed) {
+        const uint64_t used = __ballot(c != 0);
+        if (c != 0) mine[pending + __popcll(used & ((1ull << lane) - 1))] = (uint16_t)e;
+        pending += (uint32_t)__popcll(used);
+        take = -1;
+        if (pending >= 64) {
+          pending -= 64;
+          take = mine[pending + lane];
         }
       }
+      if (take >= 0) flush_entry(t, take, win_base);
+    }
+    if ((uint32_t)lane < pending) flush_entry(t, mine[lane], win_base);
+    if (threadIdx.x == NT - 1) {  // slot L
+      uint32_t c = 0;
+      for (int r = 0; r < REP; ++r) c |= cnt[L * REP + r];
+      if (c != 0) flush_entry(t, L, win_base);
     }
   }
 };
@@ -1253,7 +1295,7 @@ __device__ __forceinline__ T table_load(const T* p) {  // COHERENT: written by t
 
 // Writes the used slots of [lo, hi) as groups and clears them (and so leaves
 // the table as the next call needs it: no launch clears it first).  A workgroup
-// takes kEmitSlots slots at a time, the keys in registers; it counts the used
+// takes kEmitPer x NT slots at a time, the keys in registers; it counts the used
 // ones, takes one output range with a single atomic (updates of one address
 // serialise), and writes each group at its slot's rank, so that a wave's
 // groups leave as one contiguous piece.
@@ -1373,7 +1415,7 @@ gb_aggregate_kernel(Args a) {
                                              fw, pass);
       __syncthreads();
       tab.merge_hot();
-      tab.flush(a.t, fw.base(pass));
+      tab.flush(a.t, fw.base(pass), gridDim.x <= 64);
       __syncthreads();
     }
   }
@@ -1424,7 +1466,7 @@ __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a)
                                               (uint32_t)(a.pt.bits + a.pt.sub_bits), sub_shift, sub_mask, sub, fw, pass);
         __syncthreads();
         tab.merge_hot();
-      tab.flush(a.t, fw.base(pass));
+      tab.flush(a.t, fw.base(pass), true);
         __syncthreads();
       }
     }
@@ -1634,7 +1676,7 @@ int agg_groupby_plan(agg_groupby_t* out, int32_t key_dtype, int32_t val_dtype, i
       return b;
     };
     bits = bits_for(half_table);
-    bits = std::max(bits, kMinPartBits);  // few partitions would serialise the counting atomics
+    bits = std::max(bits, max_n >= kLargeRows ? kMinPartBitsLarge : kMinPartBits);
   }
   // The scatter takes at most 2^kTileMaxBits partitions (its per-partition
   // counters live in LDS, and more would shorten the coalesced runs); past
@@ -1775,9 +1817,12 @@ int agg_groupby_run(agg_groupby_t p, const void* keys, const void* vals, int64_t
         return rc;
       if ((rc = launch_lds(scat, a.pt.g1, kTileThreads, 0, &a, stream)) != AGG_OK)
         return rc;
+      // a workgroup for each tile of rows, or for each partition if those are
+      // more: every partition costs its workgroup a table to clear and flush
+      // (1e5 rows, 50 000 groups: int32 SUM 80 us with 12 workgroups, 53 with 32)
+      const int64_t awg = std::max(ceil_div(m, kPartThreads * 8), std::min(P, ceil_div(m, 64)));
       const int64_t agrid =
-          std::max<int64_t>(ceil_div(m, kMaxTableRows),
-                            std::min<int64_t>(ceil_div(m, kPartThreads * 8), (int64_t)cu * p->agg_blocks));
+          std::max<int64_t>(ceil_div(m, kMaxTableRows), std::min<int64_t>(awg, (int64_t)cu * p->agg_blocks));
       if ((rc = launch_lds(aggk, agrid, kPartThreads, 0, &a, stream)) != AGG_OK) return rc;
     }
     a.keys = keys;
@@ -1785,7 +1830,7 @@ int agg_groupby_run(agg_groupby_t p, const void* keys, const void* vals, int64_t
     a.n = n;
   }
   if (!a.emit) {
-    const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(ceil_div(slots, kEmitPer * kEmitThreads), (int64_t)cu * 2));
+    const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(ceil_div(slots, kEmitThreads), (int64_t)cu * 2));
     if ((rc = launch(emit_kernel(p->gop), (int)grid, kEmitThreads, &a, stream)) != AGG_OK) return rc;
   }
   p->clean = !(first && cap != hipStreamCaptureStatusNone);

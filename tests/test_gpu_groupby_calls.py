@@ -69,3 +69,21 @@ def test_calls_of_one_plan(agg, groups, vdt, op):
             compare(got, oracle.groupby(keys, vals, op), f"replay {rep} fresh={fresh} {vdt} {op} groups={groups}")
             check(n, b, 20 + rep, "between replays")
     g.close()
+
+
+@pytest.mark.parametrize("kdt", ["i32", "i64"])
+@pytest.mark.parametrize("vdt,op", [("i32", "sum"), ("f32", "sum"), ("i32", "count")])
+def test_plan_for_many_rows_run_on_few(agg, kdt, vdt, op):
+    """A plan for 2^25 rows has fewer partitions than one for the rows it is run
+    on; from one row to a few partitions' worth, its workgroups get parts of
+    one partition, one, or several."""
+    import torch
+    groups = 30_000
+    g = agg.GroupBy(kdt, vdt, op, max_n=1 << 25, max_groups=groups)
+    r = np.random.default_rng(7)
+    for n in (1, 63, 65, 4097, 70_001, 700_001):
+        keys = r.integers(-groups // 2, groups // 2, size=n).astype(np.int32 if kdt == "i32" else np.int64)
+        vals = make_vals(n, vdt, seed=n)
+        compare(g.run(torch.from_numpy(keys).cuda(), torch.from_numpy(vals).cuda()), oracle.groupby(keys, vals, op),
+                f"{kdt}/{vdt} {op} n={n}")
+    g.close()
