@@ -55,7 +55,15 @@ constexpr int kMaxPartBits = 14;      // at most 16384 (sub-)partitions
 // / 128 / 256 partitions, 50 000 groups: float SUM of 1.7M rows 111 / 83 / 69 / 72
 // us, int32 SUM 75 / 62 / 57 / 63, of 6M rows 106 / 90 / 83 / 83, of 60M rows
 // 420 / 411 / 422 / 439.
-constexpr int kMinPartBits = 7, kMinPartBitsLarge = 6;
+// With 2^17 groups and more, at least 256: then most partitions are one
+// workgroup's, and their groups leave from LDS (emit_all).  Partitions of few
+// keys are too uneven for that, and 16-byte rows pay more for short runs.  128
+// (64) / 256 partitions, 200 000 groups: COUNT of 6M rows 108 / 96 us, float SUM
+// 174 / 115, of 2^28 rows 1881 / 1812, int64 SUM 3075 / 3261; 90 000 groups:
+// int32 SUM of 6M rows 95 / 89, of 2^28 rows 1575 / 1716; 10^6 groups, COUNT of
+// 60M rows 474 / 321.
+constexpr int kMinPartBits = 7, kMinPartBitsLarge = 6, kMinPartBitsMany = 8;
+constexpr int64_t kManyGroups = (int64_t)1 << 17;
 constexpr int64_t kLargeRows = (int64_t)1 << 25;
 // Rows are partitioned in chunks of up to 2^28: every chunk ends with each
 // aggregation workgroup flushing the groups it holds, so fewer, larger
@@ -174,6 +182,7 @@ struct Args {
   int32_t is_avg;
   int32_t op;
   int32_t emit;        // direct path: the launch's last workgroup emits (fuse_slots_of)
+  int32_t whole;       // partitioned path: all rows are in this launch (a table may emit its groups itself)
 };
 
 template <int G>
@@ -331,6 +340,33 @@ __device__ __forceinline__ int64_t global_slot(const Table& t, int64_t k, uint32
 template <int G>
 __device__ __forceinline__ void apply_global(const Table& t, int64_t s, int64_t iv, float fv) {
   apply<G, false>(t.cnt + s, t.val + s, t.dig + (G == G_SUM_F32 ? s * kDigits : 0), t.flags + s, iv, fv);
+}
+
+// A group's record, from its rows and its value (float sum: digits and flags).
+template <int G>
+__device__ __forceinline__ agg_group make_group(int64_t key, int64_t count, int64_t v, const int64_t* d, int32_t flags,
+                                                int32_t is_avg) {
+  agg_group g;
+  g.key = key;
+  g.count = count;
+  g.i64 = 0;
+  g.f64 = 0.0;
+  if constexpr (G == G_COUNT) {
+    g.i64 = count;
+    g.f64 = (double)count;
+  } else if constexpr (G == G_SUM_INT) {
+    g.i64 = v;
+    g.f64 = is_avg ? (double)v / (double)count : (double)v;
+  } else if constexpr (G == G_MIN_INT || G == G_MAX_INT) {
+    g.i64 = v;
+    g.f64 = (double)v;
+  } else if constexpr (G == G_SUM_F32) {
+    const double sum = digits_to_double(d, flags);
+    g.f64 = is_avg ? sum / (double)count : sum;
+  } else {  // float MIN / MAX: NaN when every row of the group is NaN
+    g.f64 = v == val_identity<G>() ? (double)__builtin_nanf("") : (double)f32_unorder((int32_t)v);
+  }
+  return g;
 }
 
 // V consecutive items of a column at base + tid * V, as one vector load (8 or
@@ -775,6 +811,9 @@ struct LdsTable {
   int64_t win[kDig ? kWindows * E : 1];    // float sum: window w of entry e at w * E + e
   uint32_t flags[kDig ? L / 8 + 1 : 1];    // float sum: non-finite rows seen, four bits a slot
   uint16_t list[NT / 64][128];             // per wave: slots to flush
+  uint32_t spilled;                        // a row went to the global table
+  uint32_t emit_base[2];                   // emit_all: the output range's first group
+  uint32_t wave_groups[NT / 64];           // emit_all: groups per wave
   uint32_t hot_sh;                         // the hot slot + 1; 0: there is none
 
   __device__ __forceinline__ void clear(uint32_t skip) {
@@ -792,7 +831,10 @@ struct LdsTable {
     }
     if constexpr (kDig)
       for (int e = threadIdx.x; e <= L / 8; e += NT) flags[e] = 0;
-    if (HOT && threadIdx.x == 0) hot_sh = 0;
+    if (threadIdx.x == 0) {
+      hot_sh = 0;
+      spilled = 0;
+    }
   }
 
   // The table's hot slot, if the home slots of its first batch show one to this
@@ -1116,6 +1158,7 @@ struct LdsTable {
             apply<G, true>(&cnt[s], &val[kVal ? s : 0], nullptr, nullptr, (int64_t)x.iv, x.fv);
           }
         } else {
+          spilled = 1;
           const int64_t g = global_slot(t_, (int64_t)x.k, h);
           if (g >= 0) apply_global<G>(t_, g, (int64_t)x.iv, x.fv);
         }
@@ -1148,6 +1191,91 @@ struct LdsTable {
     }
   }
 
+  // Entry e's windows as a whole number of 2^(32 d - 149), d = (win_base - 1) / 32.
+  __device__ __forceinline__ __int128 window_total(int e, uint32_t win_base) const {
+    __int128 sum = 0;
+    for (int w = kWindows - 1; w >= 0; --w) {
+      uint64_t v = 0;  // the copies' rows are at most kMaxTableRows in all
+      for (int r = 0; r < REP; ++r) v += (uint64_t)win[w * E + e * REP + r];
+      sum = sum * (1 << kWinOctaves) + (int64_t)v;
+    }
+    return sum * ((int64_t)1 << (((int)win_base - 1) & 31));
+  }
+
+  // The group of entry e, which holds all of its rows.
+  __device__ __forceinline__ agg_group group_of(int e, uint32_t win_base, int32_t is_avg) const {
+    static_assert(REP == 1, "one entry per slot");
+    int64_t v = 0, d[kDig ? kDigits : 1] = {};
+    int32_t f = 0;
+    if constexpr (kVal) v = val[e];
+    if constexpr (kDig) {
+      f = (int32_t)((flags[e >> 3] >> (4 * (e & 7))) & 7u);
+      const __int128 sum = window_total(e, win_base);
+      const int first = ((int)win_base - 1) >> 5;
+#pragma unroll
+      for (int k = 0; k < kDigits; ++k) {  // digit 8 takes all there is from it on
+        const int i = k - first;
+        if (i < 0 || i > 3) continue;
+        const __int128 up = sum >> (32 * i);
+        d[k] = i == 3 || k == kDigits - 1 ? (int64_t)up : (int64_t)(uint32_t)up;
+      }
+    }
+    return make_group<G>(e < L ? (int64_t)key[e] : (int64_t)kMark, (int64_t)cnt[e], v, d, f, is_avg);
+  }
+
+  // Lists the wave's slots with rows, 64 at a time: fn(slot, rank among the
+  // wave's listed slots), or slot -1 for a lane with none.
+  template <class F>
+  __device__ __forceinline__ void each_listed(int off, F fn) {
+    const int lane = threadIdx.x & 63;
+    volatile uint16_t* mine = list[threadIdx.x / 64];
+    uint32_t pending = 0, done = 0;  // the same in all lanes
+    for (int i = threadIdx.x; i < L + NT; i += NT) {
+      const bool end = i >= L;  // the whole wave's last step
+      const int e = (i + off) & (L - 1);
+      bool has = false;
+      if (!end)
+        for (int r = 0; r < REP; ++r) has |= cnt[e * REP + r] != 0;
+      const uint64_t used = __ballot(has);
+      if (has) mine[pending + __popcll(used & ((1ull << lane) - 1))] = (uint16_t)e;
+      pending += (uint32_t)__popcll(used);
+      if (pending >= 64 || end) {
+        const uint32_t take = min(pending, 64u);
+        pending -= take;
+        if ((uint32_t)lane < take) fn((int)mine[pending + lane], done + lane);
+        done += take;
+      }
+    }
+  }
+
+  // Writes the table's groups straight to the caller's array: for a table that
+  // holds all rows of its keys.  One range of the output per table, one
+  // contiguous piece per 64 groups.
+  __device__ __forceinline__ void emit_all(const Args& a, uint32_t win_base) {
+    const int w = threadIdx.x / 64;
+    uint32_t mine = 0;
+    for (int i = threadIdx.x; i < L; i += NT) mine += (uint32_t)__popcll(__ballot(cnt[i] != 0));
+    const bool marker = cnt[L] != 0;
+    if ((threadIdx.x & 63) == 0) wave_groups[w] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t total = marker ? 1 : 0;
+      for (int v = 0; v < NT / 64; ++v) total += wave_groups[v];
+      const unsigned long long at =
+          total ? atomicAdd(reinterpret_cast<unsigned long long*>(a.t.state + 2), (unsigned long long)total) : 0;
+      emit_base[0] = (uint32_t)at;
+      emit_base[1] = (uint32_t)(at >> 32);
+    }
+    __syncthreads();
+    int64_t base = (int64_t)((uint64_t)emit_base[1] << 32 | emit_base[0]);
+    if (marker && threadIdx.x == NT - 1 && base < a.max_groups) a.out[base] = group_of(L, win_base, a.is_avg);
+    base += marker ? 1 : 0;
+    for (int v = 0; v < w; ++v) base += wave_groups[v];
+    each_listed(0, [&](int e, uint32_t rank) {
+      if (base + rank < a.max_groups) a.out[base + rank] = group_of(e, win_base, a.is_avg);
+    });
+  }
+
   // Adds entry e (which has rows) to the global table.
   __device__ __forceinline__ void flush_entry(const Table& t, int e, uint32_t win_base) {
     const KT k = e < L ? key[e] : kMark;
@@ -1175,14 +1303,8 @@ struct LdsTable {
       // from digit (base - 1) / 32 on: three unsigned ones and a signed top one.
       // Digit 8 takes all there is from it on (floats end at 2^128, which
       // keeps that below 2^53 over 2^31 rows).
-      __int128 sum = 0;
-      for (int w = kWindows - 1; w >= 0; --w) {
-        uint64_t v = 0;  // the copies' rows are at most kMaxTableRows in all
-        for (int r = 0; r < REP; ++r) v += (uint64_t)win[w * E + e * REP + r];
-        sum = sum * (1 << kWinOctaves) + (int64_t)v;
-      }
+      const __int128 sum = window_total(e, win_base);
       const int d = ((int)win_base - 1) >> 5;
-      sum *= (int64_t)1 << (((int)win_base - 1) & 31);
       unsigned long long* dig = reinterpret_cast<unsigned long long*>(t.dig + g * kDigits + d);
       for (int i = 0; i < 4; ++i) {
         const bool top = i == 3 || d + i == kDigits - 1;
@@ -1209,27 +1331,16 @@ struct LdsTable {
     // its own offset instead (2^28 rows, 1024 groups: COUNT 0.43 -> 0.39 ms;
     // the other cases within noise).
     const int off = (int)(blockIdx.x * 2654435761u >> 16);
-    const int lane = threadIdx.x & 63;
-    volatile uint16_t* mine = list[threadIdx.x / 64];
-    uint32_t pending = 0;  // listed slots, the same in all lanes
-    for (int i = threadIdx.x; i < L; i += NT) {
-      const int e = (i + off) & (L - 1);
-      uint32_t c = 0;
-      for (int r = 0; r < REP; ++r) c |= cnt[e * REP + r];
-      int take = c != 0 ? e : -1;  // the slot this lane flushes
-      if (listed) {
-        const uint64_t used = __ballot(c != 0);
-        if (c != 0) mine[pending + __popcll(used & ((1ull << lane) - 1))] = (uint16_t)e;
-        pending += (uint32_t)__popcll(used);
-        take = -1;
-        if (pending >= 64) {
-          pending -= 64;
-          take = mine[pending + lane];
-        }
+    if (listed) {
+      each_listed(off & (L - 1), [&](int e, uint32_t) { flush_entry(t, e, win_base); });
+    } else {
+      for (int i = threadIdx.x; i < L; i += NT) {
+        const int e = (i + off) & (L - 1);
+        uint32_t c = 0;
+        for (int r = 0; r < REP; ++r) c |= cnt[e * REP + r];
+        if (c != 0) flush_entry(t, e, win_base);
       }
-      if (take >= 0) flush_entry(t, take, win_base);
     }
-    if ((uint32_t)lane < pending) flush_entry(t, mine[lane], win_base);
     if (threadIdx.x == NT - 1) {  // slot L
       uint32_t c = 0;
       for (int r = 0; r < REP; ++r) c |= cnt[L * REP + r];
@@ -1343,30 +1454,16 @@ __device__ __forceinline__ void emit_slots(const Args& a, int64_t lo, int64_t hi
       const int64_t s = c0 + i * NT + threadIdx.x;
       if (key[i] == kEmpty && cnt[i] == 0) continue;
       const unsigned long long my = base_sh + cell[i * NW + w] + before[i];
-      agg_group g;
-      g.key = key[i];
-      g.count = (int64_t)table_load<COHERENT>(t.cnt + s);
-      g.i64 = 0;
-      g.f64 = 0.0;
-      if constexpr (G == G_COUNT) {
-        g.i64 = g.count;
-        g.f64 = (double)g.count;
-      } else if constexpr (G == G_SUM_INT) {
-        g.i64 = table_load<COHERENT>(t.val + s);
-        g.f64 = a.is_avg ? (double)g.i64 / (double)g.count : (double)g.i64;
-      } else if constexpr (G == G_MIN_INT || G == G_MAX_INT) {
-        g.i64 = table_load<COHERENT>(t.val + s);
-        g.f64 = (double)g.i64;
-      } else if constexpr (G == G_SUM_F32) {
-        int64_t d[kDigits];
+      int64_t v = 0, d[G == G_SUM_F32 ? kDigits : 1] = {};
+      int32_t f = 0;
+      if constexpr (G == G_SUM_F32) {
 #pragma unroll
         for (int k = 0; k < kDigits; ++k) d[k] = table_load<COHERENT>(t.dig + s * kDigits + k);
-        const double sum = digits_to_double(d, table_load<COHERENT>(t.flags + s));
-        g.f64 = a.is_avg ? sum / (double)g.count : sum;
-      } else {  // float MIN / MAX: NaN when every row of the group is NaN
-        const int64_t v = table_load<COHERENT>(t.val + s);
-        g.f64 = v == val_identity<G>() ? (double)__builtin_nanf("") : (double)f32_unorder((int32_t)v);
+        f = table_load<COHERENT>(t.flags + s);
+      } else if constexpr (G != G_COUNT) {
+        v = table_load<COHERENT>(t.val + s);
       }
+      const agg_group g = make_group<G>(key[i], (int64_t)table_load<COHERENT>(t.cnt + s), v, d, f, a.is_avg);
       clear_slot<G>(t, s);
       if ((int64_t)my < a.max_groups) a.out[my] = g;
     }
@@ -1443,21 +1540,41 @@ __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a)
     fw = sample_windows(static_cast<const uint32_t*>(a.pt.pk), SR::KW + SR::VW, SR::KW, a.n);
   }
   const int P = 1 << a.pt.bits;
-  int64_t r = a.n * (int64_t)blockIdx.x / gridDim.x;
-  const int64_t r1 = a.n * ((int64_t)blockIdx.x + 1) / gridDim.x;
+  // The workgroup's rows: an equal share.  Where there are as many partitions as
+  // workgroups, each end is moved to the nearest partition start within a quarter
+  // of a share: the partitions between are wholly this workgroup's, and their
+  // groups need no global table.  (2^20 groups, 256 partitions and more: COUNT
+  // of 6M rows 181 -> 85 us, of 2^28 rows 1425 -> 1157; float SUM of 6M rows 362
+  // -> 144.  With fewer partitions it gains nothing and makes the shares
+  // uneven: 2^28 rows, 50 000 groups, COUNT 951 -> 984.)
+  uint32_t* start = tab.cnt;  // the partition starts, until the table is cleared
+  for (int i = threadIdx.x; i <= P; i += kPartThreads) start[i] = a.pt.start[i];
+  __syncthreads();
+  int p = 0;  // the last partition that starts at or before the row last asked for
+  auto snap = [&](int64_t row) -> int64_t {
+    int lo = 0, hi = P;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) / 2;
+      if ((int64_t)start[mid] <= row) lo = mid;
+      else hi = mid - 1;
+    }
+    p = lo;
+    const int64_t down = row - (int64_t)start[lo], up = lo < P ? (int64_t)start[lo + 1] - row : down;
+    const int64_t most = P >= (int)gridDim.x ? a.n / gridDim.x / 4 : 0;
+    return down <= up ? (down <= most ? row - down : row) : (up <= most ? row + up : row);
+  };
+  const int64_t r1 = snap(a.n * ((int64_t)blockIdx.x + 1) / gridDim.x);
+  int64_t r = snap(a.n * (int64_t)blockIdx.x / gridDim.x);
+  __syncthreads();
   if (r >= r1) return;  // the whole workgroup leaves together
-  int lo = 0, hi = P - 1;  // the partition holding row r: the last p with start[p] <= r
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) / 2;
-    if ((int64_t)a.pt.start[mid] <= r) lo = mid;
-    else hi = mid - 1;
-  }
-  int p = lo;
   const uint32_t sub_mask = (1u << a.pt.sub_bits) - 1u;
   const uint32_t sub_shift = a.pt.sub_bits ? (uint32_t)(32 - a.pt.bits - a.pt.sub_bits) : 0u;
   while (r < r1) {
     while ((int64_t)a.pt.start[p + 1] <= r) ++p;  // skip partitions that end before r
     const int64_t seg_end = std::min<int64_t>(r1, (int64_t)a.pt.start[p + 1]);
+    // the workgroup has all rows of the partition's keys, folded in one pass
+    const bool whole =
+        a.whole && fw.passes == 1 && r == (int64_t)a.pt.start[p] && seg_end == (int64_t)a.pt.start[p + 1];
     for (uint32_t sub = 0; sub <= sub_mask; ++sub) {
       for (int pass = 0; pass < fw.passes; ++pass) {
         tab.clear((uint32_t)(a.pt.bits + a.pt.sub_bits));
@@ -1466,7 +1583,8 @@ __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a)
                                               (uint32_t)(a.pt.bits + a.pt.sub_bits), sub_shift, sub_mask, sub, fw, pass);
         __syncthreads();
         tab.merge_hot();
-      tab.flush(a.t, fw.base(pass), true);
+        if (whole && tab.spilled == 0) tab.emit_all(a, fw.base(pass));
+        else tab.flush(a.t, fw.base(pass), true);
         __syncthreads();
       }
     }
@@ -1676,7 +1794,11 @@ int agg_groupby_plan(agg_groupby_t* out, int32_t key_dtype, int32_t val_dtype, i
       return b;
     };
     bits = bits_for(half_table);
-    bits = std::max(bits, max_n >= kLargeRows ? kMinPartBitsLarge : kMinPartBits);
+    const bool large = max_n >= kLargeRows;
+    const bool wide = width_of(key_dtype) + (op == AGG_COUNT ? 0 : width_of(val_dtype)) >= 16;
+    bits = std::max(bits, max_groups >= kManyGroups && !(large && wide) ? kMinPartBitsMany
+                          : large                                      ? kMinPartBitsLarge
+                                                                       : kMinPartBits);
   }
   // The scatter takes at most 2^kTileMaxBits partitions (its per-partition
   // counters live in LDS, and more would shorten the coalesced runs); past
@@ -1809,6 +1931,7 @@ int agg_groupby_run(agg_groupby_t p, const void* keys, const void* vals, int64_t
       a.keys = static_cast<const char*>(keys) + c0 * kw;
       a.vals = static_cast<const char*>(vals) + c0 * vw;
       a.n = m;
+      a.whole = m == n;
       a.pt.g1 = (int)std::min<int64_t>(kMaxHistWg, ceil_div(m, kMinHistRows));
       a.pt.rows_per_wg = ceil_div(m, a.pt.g1);
       if ((rc = launch_lds(hist, a.pt.g1, kHistThreads, 0, &a, stream)) != AGG_OK) return rc;
