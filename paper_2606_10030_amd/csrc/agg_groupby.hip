@@ -46,7 +46,11 @@ namespace gb {
 
 constexpr int64_t kEmpty = INT64_MIN;
 constexpr int kThreads = 256;
-constexpr int kLdsProbes = 16;
+// Probes of an LDS table.  At half load a key finds none of 16 free once in 2^16:
+// with 4096 keys in 256 tables that was a row in the global table every few runs,
+// and merged tables (gb_merge_kernel) then went there too: 6M rows, float SUM of
+// 4096 groups 99 us, or 156.
+constexpr int kLdsProbes = 32;
 constexpr int kGlobalProbes = 32;     // hashed probes of the global table, then linear ones
 constexpr int kMaxPartBits = 14;      // at most 16384 (sub-)partitions
 // At least 128 partitions (64 for 2^25 rows and more): with fewer than there are
@@ -114,6 +118,25 @@ constexpr int kDirectThreads = 1024;
 // 4096 slots 42.2 (40.8); float SUM of 25 groups 17.8 (18.9), of 300, 1024
 // slots 36.1 (35.0), of 2000 72.9 (56.1).
 constexpr int64_t fuse_slots_of(int g) { return (g == G_SUM_F32 ? 256 : 2048) + 1; }
+// Direct path with many workgroups: a table's flush is bound by device-scope
+// atomics (about 1.4e10 a second for the chip; 256 workgroups x 2000 groups x 2
+// of them are 70 us), so the tables are written out instead, by sections of the
+// hash, and a second launch merges each section's records in LDS.  6M rows (366
+// workgroups' worth, 256): COUNT of 2000 groups 52 -> 38 us, int32 SUM of 4096 95
+// -> 73, float SUM of 4096 223 -> 99, int64 SUM of 100 38 -> 27; 60M rows: COUNT of
+// 300 76 -> 73, int32 SUM of 2000 133 -> 122; 2^28 rows within 2%.  The line, where
+// the flush would be about 16 000 updates: 5e5 rows, 31 workgroups, COUNT of 2000
+// groups 35 -> 28, int64 SUM of 300 19.0 -> 21.5.
+constexpr int kSectionBits = 7, kSections = 1 << kSectionBits;
+constexpr int kMergeSlots = 512;      // a section holds 128 keys at most, on average (1/128 of 16384)
+constexpr int64_t kDirectRows = 16 * kDirectThreads;  // rows per workgroup, at least
+constexpr int64_t kMergeMinWg = 16, kMergeMaxWg = 1024;
+constexpr int64_t kMergeMinUpdates = 16'000;  // workgroups x groups
+constexpr int64_t kMergeMaxRows = (int64_t)1 << 31;  // 32-bit row counts
+constexpr int dump_words_of(int g, int kd) {  // a record: key, rows, value (float sum: windows, flags)
+  return (kd == AGG_I32 ? 1 : 2) + 1 + (g == G_COUNT ? 0 : g == G_SUM_F32 ? 7 : 2);
+}
+constexpr int64_t dump_region_of(int g, int kd, int64_t most) { return kSections + 1 + most * dump_words_of(g, kd); }
 constexpr int lds_slots_of(int g, int kd) {
   return g == G_SUM_F32 ? 4096 : (g == G_COUNT ? 2 : 1) * (kd == AGG_I32 ? 8192 : 4096);
 }
@@ -151,7 +174,7 @@ struct Table {
   int64_t* dig;        // float SUM: kDigits per slot
   int32_t* flags;      // float SUM: 1 NaN, 2 +Inf, 4 -Inf seen
   // [0] overflow (more distinct keys than slots), [2..3] groups emitted (uint64), [4] finished
-  // workgroups.  State and slots are clean between calls: each call's emission clears what it reads.
+  // workgroups, [5] merged runs: the global table holds rows, [6] merged float sums: the windows' base.  State and slots are clean between calls: each call's emission clears what it reads.
   int32_t* state;
   int64_t cap;         // slots, a power of two >= 64
   int32_t cap_log2;
@@ -182,6 +205,9 @@ struct Args {
   int32_t is_avg;
   int32_t op;
   int32_t emit;        // direct path: the launch's last workgroup emits (fuse_slots_of)
+  uint32_t* dump;      // direct path, merged: the workgroups' tables, a region each (gb_merge_kernel)
+  int32_t dumps;       // workgroups that wrote one; 0: tables are flushed into the global one
+  int32_t dump_max;    // records a region holds
   int32_t whole;       // partitioned path: all rows are in this launch (a table may emit its groups itself)
 };
 
@@ -1303,16 +1329,119 @@ struct LdsTable {
       // from digit (base - 1) / 32 on: three unsigned ones and a signed top one.
       // Digit 8 takes all there is from it on (floats end at 2^128, which
       // keeps that below 2^53 over 2^31 rows).
-      const __int128 sum = window_total(e, win_base);
-      const int d = ((int)win_base - 1) >> 5;
-      unsigned long long* dig = reinterpret_cast<unsigned long long*>(t.dig + g * kDigits + d);
-      for (int i = 0; i < 4; ++i) {
-        const bool top = i == 3 || d + i == kDigits - 1;
-        const int64_t v = top ? (int64_t)(sum >> (32 * i)) : (int64_t)(uint32_t)(sum >> (32 * i));
-        if (v) atomicAdd(dig + i, (unsigned long long)v);
-        if (top) break;
+      add_digits(t, g, window_total(e, win_base), win_base);
+    }
+  }
+
+  // Adds a float sum's window total to the global slot g.
+  static __device__ __forceinline__ void add_digits(const Table& t, int64_t g, __int128 sum, uint32_t win_base) {
+    const int d = ((int)win_base - 1) >> 5;
+    unsigned long long* dig = reinterpret_cast<unsigned long long*>(t.dig + g * kDigits + d);
+    for (int i = 0; i < 4; ++i) {
+      const bool top = i == 3 || d + i == kDigits - 1;
+      const int64_t v = top ? (int64_t)(sum >> (32 * i)) : (int64_t)(uint32_t)(sum >> (32 * i));
+      if (v) atomicAdd(dig + i, (unsigned long long)v);
+      if (top) break;
+    }
+  }
+
+  // ---- merged tables: records of key, rows and value, by section of the hash ----
+  static constexpr int kKeyWords = KD == AGG_I32 ? 1 : 2;
+  static constexpr int kRecWords = dump_words_of(G, KD);
+
+  // Writes the table to its region: the sections' starts, then the records by
+  // section (a counting sort).  False, with nothing written but the empty
+  // sections, if the region is too small: more keys than the plan allows.
+  __device__ __forceinline__ bool dump(uint32_t* region, int most) {
+    static_assert(sizeof(list) >= 2 * kSections * 4, "the counters lie over the list");
+    uint32_t* count = reinterpret_cast<uint32_t*>(&list[0][0]);
+    if (threadIdx.x <= kSections) count[threadIdx.x] = 0;
+    __syncthreads();
+    auto section_of = [&](int e) { return key_hash<KD>(e < L ? key[e] : kMark) >> (32 - kSectionBits); };
+    for (int e = threadIdx.x; e <= L; e += NT)
+      if (cnt[e] != 0) at_add<true>(&count[section_of(e)], 1u);
+    __syncthreads();
+    if (threadIdx.x < 64) {  // exclusive prefix, two sections a lane
+      const uint32_t c0 = count[2 * threadIdx.x], c1 = count[2 * threadIdx.x + 1];
+      uint32_t incl = c0 + c1;
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(incl, off, 64);
+        if ((int)threadIdx.x >= off) incl += y;
+      }
+      count[2 * threadIdx.x] = incl - c0 - c1;
+      count[2 * threadIdx.x + 1] = incl - c1;
+      if (threadIdx.x == 63) count[kSections] = incl;
+    }
+    __syncthreads();
+    const bool fits = (int64_t)count[kSections] <= most;
+    if (threadIdx.x <= kSections) region[threadIdx.x] = fits ? count[threadIdx.x] : 0;
+    __syncthreads();
+    if (!fits) return false;
+    for (int e = threadIdx.x; e <= L; e += NT) {
+      if (cnt[e] == 0) continue;
+      const KT k = e < L ? key[e] : kMark;
+      uint32_t* r = region + kSections + 1 + (int64_t)at_fetch_add(&count[section_of(e)], 1u) * kRecWords;
+      r[0] = (uint32_t)k;
+      if constexpr (kKeyWords == 2) r[1] = (uint32_t)((uint64_t)k >> 32);
+      r[kKeyWords] = cnt[e];
+      if constexpr (kVal) put64(r + kKeyWords + 1, val[e]);
+      if constexpr (kDig) {
+        for (int w = 0; w < kWindows; ++w) put64(r + kKeyWords + 1 + 2 * w, win[w * E + e]);
+        r[kKeyWords + 1 + 2 * kWindows] = (flags[e >> 3] >> (4 * (e & 7))) & 7u;
       }
     }
+    return true;
+  }
+  static __device__ __forceinline__ void put64(uint32_t* p, int64_t v) {
+    p[0] = (uint32_t)v;
+    p[1] = (uint32_t)((uint64_t)v >> 32);
+  }
+  static __device__ __forceinline__ int64_t get64(const uint32_t* p) { return (int64_t)((uint64_t)p[1] << 32 | p[0]); }
+  static __device__ __forceinline__ uint32_t at_fetch_add(uint32_t* p, uint32_t v) {
+    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+
+  // Adds a record; to the global table if its key finds no slot (as any other
+  // record of the key then does too).
+  __device__ __forceinline__ void add_record(const Table& t, const uint32_t* r, uint32_t skip, uint32_t win_base) {
+    const KT k = kKeyWords == 2 ? (KT)get64(r) : (KT)(int32_t)r[0];
+    const uint32_t rows = r[kKeyWords], h = key_hash<KD>(k);
+    const uint32_t* x = r + kKeyWords + 1;
+    const int s = slot_of(k, h, skip);
+    if (s >= 0) {
+      at_add<true>(&cnt[s], rows);
+      if constexpr (G == G_SUM_INT)
+        at_add<true>(reinterpret_cast<unsigned long long*>(&val[s]), (unsigned long long)get64(x));
+      else if constexpr (G == G_MIN_INT || G == G_MIN_F32)
+        atomicMin(reinterpret_cast<long long*>(&val[s]), (long long)get64(x));
+      else if constexpr (kVal)
+        atomicMax(reinterpret_cast<long long*>(&val[s]), (long long)get64(x));
+      if constexpr (kDig) {
+        for (int w = 0; w < kWindows; ++w)
+          at_add<true>(reinterpret_cast<unsigned long long*>(&win[w * E + s]), (unsigned long long)get64(x + 2 * w));
+        const uint32_t f = x[2 * kWindows];
+        if (f) at_or<true>(reinterpret_cast<int*>(&flags[s >> 3]), (int)(f << (4 * (s & 7))));
+      }
+      return;
+    }
+    mark_global(t);
+    const int64_t g = global_slot(t, (int64_t)k, h);
+    if (g < 0) return;
+    atomicAdd(reinterpret_cast<unsigned long long*>(t.cnt + g), (unsigned long long)rows);
+    if constexpr (G == G_SUM_INT) atomicAdd(reinterpret_cast<unsigned long long*>(t.val + g), (unsigned long long)get64(x));
+    else if constexpr (G == G_MIN_INT || G == G_MIN_F32)
+      atomicMin(reinterpret_cast<long long*>(t.val + g), (long long)get64(x));
+    else if constexpr (kVal) atomicMax(reinterpret_cast<long long*>(t.val + g), (long long)get64(x));
+    if constexpr (kDig) {
+      __int128 sum = 0;
+      for (int w = kWindows - 1; w >= 0; --w) sum = sum * (1 << kWinOctaves) + get64(x + 2 * w);
+      add_digits(t, g, sum * ((int64_t)1 << (((int)win_base - 1) & 31)), win_base);
+      if (x[2 * kWindows]) atomicOr(t.flags + g, (int32_t)x[2 * kWindows]);
+    }
+  }
+  // Merged runs: the global table holds rows, so the merge's last workgroup emits it too.
+  static __device__ __forceinline__ void mark_global(const Table& t) {
+    __hip_atomic_store(&t.state[5], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 
   // A slot's flush is a chain of device-scope accesses (read the global home,
@@ -1505,14 +1634,27 @@ gb_aggregate_kernel(Args a) {
   if constexpr (G == G_SUM_F32) fw = sample_windows(static_cast<const uint32_t*>(a.vals), 1, 0, a.n);
   for (uint32_t sub = 0; sub <= sub_mask; ++sub) {
     for (int pass = 0; pass < fw.passes; ++pass) {
+      bool written = false;
       tab.clear((uint32_t)a.pt.sub_bits);
       __syncthreads();
       tab.template fold_rows<VD, false, SUB>(a.t, a.keys, a.vals, (int64_t)blockIdx.x * TR, a.n,
                                              (int64_t)gridDim.x * TR, (uint32_t)a.pt.sub_bits, sub_shift, sub_mask, sub,
                                              fw, pass);
       __syncthreads();
-      tab.merge_hot();
-      tab.flush(a.t, fw.base(pass), gridDim.x <= 64);
+      if constexpr (!FEW)
+        if (a.dumps) {
+          // one region per workgroup and hash half; its rows may be in the global
+          // table as well (spilled), and several windows' passes all are
+          uint32_t* region = a.dump + ((int64_t)blockIdx.x * (sub_mask + 1) + sub) * dump_region_of(G, KD, a.dump_max);
+          const bool dumped = fw.passes == 1 && tab.dump(region, a.dump_max);
+          if (fw.passes > 1 && threadIdx.x <= kSections) region[threadIdx.x] = 0;
+          if (threadIdx.x == 0) {
+            if (!dumped || tab.spilled) decltype(tab)::mark_global(a.t);
+            if (blockIdx.x == 0) a.t.state[6] = (int32_t)fw.base(0);
+          }
+          if (dumped) written = true;
+        }
+      if (!written) tab.flush(a.t, fw.base(pass), gridDim.x <= 64);
       __syncthreads();
     }
   }
@@ -1590,6 +1732,63 @@ __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a)
     }
     r = seg_end;
   }
+}
+
+// Merges the direct path's tables: workgroup s adds the records of section s of
+// every region in an LDS table and writes its groups.  If rows are in the
+// global table too, the tables go there instead and the last workgroup emits it.
+template <int KD, int G>
+__global__ void __launch_bounds__(kDirectThreads) gb_merge_kernel(Args a) {
+  __shared__ LdsTable<G, KD, kMergeSlots, kDirectThreads> tab;
+  __shared__ uint32_t first[kMergeMaxWg], upto[kMergeMaxWg];  // a region's records of the section; their running total
+  __shared__ uint32_t wave_sum[kDirectThreads / 64];
+  const uint32_t section = blockIdx.x;
+  const uint32_t subs = 1u << a.pt.sub_bits, sub = section >> (kSectionBits - a.pt.sub_bits);
+  const int64_t region = dump_region_of(G, KD, a.dump_max);
+  const int tid = threadIdx.x, lane = tid & 63, w = tid / 64;
+  const uint32_t* mine = a.dump + ((int64_t)tid * subs + sub) * region;
+  uint32_t n = 0;
+  if (tid < a.dumps) {
+    first[tid] = mine[section];
+    n = mine[section + 1] - first[tid];
+  }
+  tab.clear((uint32_t)kSectionBits);
+  uint32_t incl = n;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t y = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += y;
+  }
+  if (lane == 63) wave_sum[w] = incl;
+  __syncthreads();
+  for (int v = 0; v < w; ++v) incl += wave_sum[v];
+  upto[tid] = incl;
+  __syncthreads();
+  const uint32_t total = upto[kDirectThreads - 1];
+  const uint32_t win_base = G == G_SUM_F32 ? (uint32_t)a.t.state[6] : 0u;
+  const bool global = __hip_atomic_load(&a.t.state[5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+  __syncthreads();  // (below, other workgroups may mark it)
+  for (uint32_t i = tid; i < total; i += kDirectThreads) {
+    int lo = 0, hi = a.dumps - 1;  // the first region that ends after record i
+    while (lo < hi) {
+      const int mid = (lo + hi) / 2;
+      if (upto[mid] > i) hi = mid;
+      else lo = mid + 1;
+    }
+    const uint32_t at = first[lo] + i - (lo ? upto[lo - 1] : 0u);
+    const uint32_t* r = a.dump + ((int64_t)lo * subs + sub) * region + kSections + 1 + (int64_t)at * decltype(tab)::kRecWords;
+    tab.add_record(a.t, r, (uint32_t)kSectionBits, win_base);
+  }
+  __syncthreads();
+  // (all workgroups read the mark before this launch's own marks count: a key
+  // that found no slot here is in no table here)
+  if (global) tab.flush(a.t, win_base, true);
+  else tab.emit_all(a, win_base);
+  if (!last_to_finish(reinterpret_cast<uint32_t*>(a.t.state + 4))) return;
+  if (__hip_atomic_load(&a.t.state[5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
+    emit_slots<G, true, kDirectThreads>(a, 0, a.t.cap + 1);
+  __syncthreads();
+  if (tid == 0) __hip_atomic_store(&a.t.state[5], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  finish_emission(a);
 }
 
 // Clears the whole table: once, before a plan's first call.
@@ -1727,6 +1926,20 @@ const void* emit_kernel(int g) {
   }
 }
 
+template <int KD>
+const void* merge_kernel(int g) {
+  switch (g) {
+    case G_COUNT: return reinterpret_cast<const void*>(&gb_merge_kernel<KD, G_COUNT>);
+    case G_SUM_INT: return reinterpret_cast<const void*>(&gb_merge_kernel<KD, G_SUM_INT>);
+    case G_MIN_INT: return reinterpret_cast<const void*>(&gb_merge_kernel<KD, G_MIN_INT>);
+    case G_MAX_INT: return reinterpret_cast<const void*>(&gb_merge_kernel<KD, G_MAX_INT>);
+    case G_SUM_F32: return reinterpret_cast<const void*>(&gb_merge_kernel<KD, G_SUM_F32>);
+    case G_MIN_F32: return reinterpret_cast<const void*>(&gb_merge_kernel<KD, G_MIN_F32>);
+    case G_MAX_F32: return reinterpret_cast<const void*>(&gb_merge_kernel<KD, G_MAX_F32>);
+    default: return nullptr;
+  }
+}
+
 int launch_lds(const void* fn, int64_t grid, int block, size_t lds, Args* args, hipStream_t stream) {
   void* kargs[] = {args};
   const hipError_t e = hipLaunchKernel(fn, dim3((unsigned)grid), dim3(block), kargs, lds, stream);
@@ -1755,6 +1968,8 @@ struct agg_groupby_s {
   int path = 0;        // 0 direct, 1 partitioned, 2 few groups, 3 / 4: 0 / 1 in sub-partition passes
   int agg_blocks = 1;  // aggregation workgroups resident per CU
   bool clean = false;  // the table and its state are as a call needs them
+  uint32_t* dump = nullptr;  // direct path: regions for dump_wgs workgroups' tables
+  int dump_wgs = 0, dump_max = 0;
 };
 
 extern "C" {
@@ -1813,8 +2028,14 @@ int agg_groupby_plan(agg_groupby_t* out, int32_t key_dtype, int32_t val_dtype, i
   const int64_t b_dig = dig ? up(slots * 8 * kDigits) : 256, b_flags = up(slots * 4), b_state = 256;
   const int64_t b_hist = up(P * kMaxHistWg * 4), b_tot = up(P * 4 + 4), b_start = up(P * 4 + 4),
                 b_pk = up(crow * kw), b_pv = up(crow * vw);
+  // Regions for one table per CU and hash half, if a run can have enough
+  // workgroups to merge them: room for the groups (for a half of them, half and
+  // a quarter more; a table with more than that is flushed as usual).
+  const int wgs = bits || max_groups <= kFewGroups || max_n <= kMergeMinWg * kDirectRows ? 0 : device_cu(dev);
+  const int64_t dump_max = sub_bits ? max_groups / 2 + max_groups / 8 + 64 : max_groups + 1;
+  const int64_t b_dump = up(wgs * (dump_region_of(g, key_dtype, dump_max) << sub_bits) * 4);
   const int64_t total = b_key + b_cnt + b_val + b_dig + b_flags + b_state + b_hist + b_tot + b_start +
-                        b_pk + b_pv;
+                        b_pk + b_pv + b_dump;
   agg_groupby_s* p = new (std::nothrow) agg_groupby_s();
   if (!p) return AGG_E_NOMEM;
   const int arc = device_alloc(&p->ws, (size_t)total);
@@ -1841,6 +2062,9 @@ int agg_groupby_plan(agg_groupby_t* out, int32_t key_dtype, int32_t val_dtype, i
   p->pt.start = reinterpret_cast<uint32_t*>(take(b_start));
   p->pt.pk = take(b_pk);
   p->pt.pv = vw ? take(b_pv) : nullptr;  // right after pk: staged (key, value) records span both
+  p->dump = wgs ? reinterpret_cast<uint32_t*>(take(b_dump)) : nullptr;
+  p->dump_wgs = wgs;
+  p->dump_max = (int)dump_max;
   p->pt.bits = bits;
   p->pt.sub_bits = sub_bits;
   p->device = dev;
@@ -1912,11 +2136,22 @@ int agg_groupby_run(agg_groupby_t p, const void* keys, const void* vals, int64_t
     // rows (1e6 rows, int32 keys and values: 1000 groups 37.4 us, 38.5 with one
     // tile; float SUM 53.1, 64.6).  The few-groups table's flush is nothing, so
     // one tile (25 groups 15.1 us either way).
-    const int64_t wg_rows = kDirectThreads * (p->path == 2 ? 8 : 16);
+    const int64_t wg_rows = p->path == 2 ? kDirectRows / 2 : kDirectRows;
     const int64_t grid = std::max<int64_t>(ceil_div(n, kMaxTableRows),
                                            std::min<int64_t>(ceil_div(n, wg_rows), (int64_t)cu * p->agg_blocks));
-    a.emit = slots <= fuse_slots_of(p->gop);
-    rc = launch(agg_kernel(p->key_dtype, p->val_dtype, p->gop, p->path), (int)grid, kDirectThreads, &a, stream);
+    // (a float sum's windows take the rows of one table, merged or not)
+    const bool merge = grid > kMergeMinWg && grid <= p->dump_wgs && grid * p->max_groups >= kMergeMinUpdates &&
+                       n <= (p->gop == G_SUM_F32 ? kMaxTableRows : kMergeMaxRows);
+    a.dump = p->dump;
+    a.dump_max = p->dump_max;
+    a.dumps = merge ? (int)grid : 0;
+    a.emit = merge || slots <= fuse_slots_of(p->gop);
+    Args fold = a;
+    fold.emit = !merge && a.emit;
+    rc = launch(agg_kernel(p->key_dtype, p->val_dtype, p->gop, p->path), (int)grid, kDirectThreads, &fold, stream);
+    if (rc == AGG_OK && merge)
+      rc = launch_lds(p->key_dtype == AGG_I32 ? merge_kernel<AGG_I32>(p->gop) : merge_kernel<AGG_I64>(p->gop), kSections,
+                      kDirectThreads, 0, &a, stream);
     if (rc != AGG_OK) return rc;
   } else if (n > 0) {
     const int64_t P = (int64_t)1 << p->pt.bits;
