@@ -431,12 +431,14 @@ int batch_enqueue(agg_batch_s* b, const agg_tune& t, agg_result* out, hipStream_
 
 // Small columns take one launch: the scan's last workgroup merges, which
 // saves the host one kernel launch (about 3 us of the call).  Only where the
-// merge is one round trip of device-scope loads (at most 1024 partials: 16
-// loads in flight per lane on a one-wave workgroup) and the finished-
-// workgroup counter sees at most one increment per CU; beyond that the
-// coherent merge rounds and the contended counter cost the GPU more than the
-// separate merge launch (measured up to 2^26 items).
-constexpr int64_t kFuseMaxPartials = 1024;
+// merge is one round trip of device-scope loads (16 loads in flight per lane:
+// at most 1024 partials on a one-wave workgroup, 4096 on one of four waves or
+// more) and the finished-workgroup counter sees at most one increment per CU;
+// beyond that the coherent merge rounds and the contended counter cost the GPU
+// more than the separate merge launch (measured up to 2^26 items).  The plain
+// scan, one launch against two: int64 AVG 17 MB 6.2 us (6.8), 32 MB 6.7 (7.2);
+// compensated float SUM 17 MB 12.0 (13.0), 48 MB 19.9 (20.9), 66 MB 22.4 (23.2).
+constexpr int64_t kFuseMaxPartials = 1024, kFuseMaxPartialsWide = 4096;
 
 // The scan of a column the kernels can read directly (device memory, or
 // page-locked host memory read over PCIe) and the combine (in the same
@@ -459,7 +461,7 @@ int enqueue_resident(int kind, int32_t dtype, int32_t op, int32_t prec, const ag
   if (!combine_fn) return AGG_E_INVALID;
   if (s.nseg > 0) {
     const int grid = grid_for(t, cu, s.nseg);
-    const bool fused = s.nseg <= kFuseMaxPartials && grid <= cu;
+    const bool fused = grid <= cu && s.nseg <= (t.waves_per_block >= 8 ? kFuseMaxPartialsWide : kFuseMaxPartials);
     const void* fn = scan_kernel_ptr(kind, t.unroll, t.nontemporal != 0, fused);
     if (!fn) return AGG_E_INVALID;
     ScanArgs a;

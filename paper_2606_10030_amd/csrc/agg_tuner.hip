@@ -62,8 +62,10 @@ int bucket_of(int64_t bytes) {  // ceil(log2(bytes)), at least 10
 // 100 MB 90 -> 20.4, 500 MB 83.9 -> 78.2; int64 SUM 16 MB 9.6 -> 7.4, 48 MB
 // 15.3 -> 11.5, 100 MB 22.2 -> 20.0, 150 MB 28.6 -> 27.2 (int32); compensated
 // float SUM 4 MB 11.2 -> 10.2, 16 MB 20.3 -> 14.7, 48 MB 25.0 -> 21.8, 130 MB
-// 38.8 -> 34.3, 300 MB 63.1 -> 59.5.  Up to 1024 segments (16 MB) the shapes keep
-// to one workgroup per CU, so that the scan's last workgroup may merge.
+// 38.8 -> 34.3, 300 MB 63.1 -> 59.5.  Up to 2560 segments (40 MB; compensated float
+// 128 MB) the shapes keep to one workgroup per CU, so that the scan's last
+// workgroup may merge: int32 SUM 17 MB 7.2 us in two launches, 6.2 in one, 32 MB
+// 7.2 and 6.9, but 48 MB 9.9 either way and int64 AVG 9.3 and 9.9.
 //
 // Columns read from host memory are bound by the link (57.4 GB/s), which one
 // wave per CU with 4 loads in flight (1 MiB in all) fills; more of them queue at
@@ -101,6 +103,7 @@ void builtin_for(int kind, int32_t src, int64_t bytes, agg_tune* t) {
   } else if (small) {
     if (nseg <= 512) shape(4, 1, 16);
     else if (nseg < 1024) shape(8, 1, 8);
+    else if (nseg <= 2560) shape(16, 1, 8);
     else shape(2, 2, 8);
   } else if (mid || (narrow_minmax && src == AGG_SRC_DEVICE && bytes < (1ll << 30))) {
     shape(2, 2, 16);

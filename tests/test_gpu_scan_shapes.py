@@ -50,3 +50,21 @@ def test_shapes_by_size(agg, dtype, segs):
         sel = x[off:off + n][mask]
         assert got["count"] == sel.size
         assert got["value"] == (None if sel.size == 0 else oracle.value(sel, "max"))
+
+
+@pytest.mark.parametrize("dtype", ["i32", "i64", "f32"])
+@pytest.mark.parametrize("segs", [2048, 2559, 2560, 2561, 4095, 4096, 4097])
+def test_one_launch_or_two(agg, dtype, segs):
+    """Where the scan's last workgroup merges, and where a launch of its own does:
+    the bits of both, call after call (the counter is clear again)."""
+    import torch
+    n = segs * SEG // T[dtype] - 3
+    x = datagen.column(n, dtype, "uniform", seed=segs)
+    d = torch.from_numpy(x).to("cuda")
+    for op in ("sum", "min"):
+        two = agg.Plan(dtype, op, max_n=n, tune=agg.make_tune(waves_per_block=4, blocks_per_cu=2)).run(d)
+        check(x, dtype, op, "neumaier", two, ctx=f"{dtype} {op} segs={segs}")
+        for plan in (agg.Plan(dtype, op, max_n=n),
+                     agg.Plan(dtype, op, max_n=n, tune=agg.make_tune(waves_per_block=8, blocks_per_cu=1))):
+            for _ in range(3):
+                assert same_bits(plan.run(d), two), f"{dtype} {op} segs={segs}"
