@@ -1091,10 +1091,10 @@ struct LdsTable {
       // would also wait for the atomics of the rows before it
 #pragma unroll
       for (int r = 0; r < R; ++r) __asm__ volatile("" : "+v"(cur[r]));
-      if constexpr (!SUB) {
-        // Nearly every batch of a wave: each row of each lane finds its key at
-        // home (and its float in a window), tested for all of them at once, so
-        // a row is its adds and nothing else.
+      // Nearly every batch of a wave: each row of each lane finds its key at
+      // home (and its float in a window), tested for all of them at once, so
+      // a row is its adds and nothing else.
+      auto lost_lanes = [&]() -> uint64_t {  // lanes with a row that is not found
         KT differ = 0;
         uint32_t far = 0;
 #pragma unroll
@@ -1102,38 +1102,74 @@ struct LdsTable {
           differ |= cur[r] ^ b.x[r].k;
           if constexpr (kDig) far = max(far, (__float_as_uint(b.x[r].fv) << 1) + win_off);
         }
-        if (full && __all(differ == 0 && (!kDig || far < win_span))) {
+        return __ballot(differ != 0 || (kDig && far >= win_span));
+      };
+      bool found = false;
+      uint64_t lost = ~0ull;
+      if constexpr (!SUB) {
+        lost = lost_lanes();
+        found = full && lost == 0;
+      }
+      if constexpr (REP > 1) {
+        // Few keys, so many rows may be of one that is not at home: the next probes
+        // of the whole batch, up to three, until all are found (or no lane has all
+        // of its own: a table that is still empty).  Random int32 keys, 2^28 rows,
+        // with 128 slots and the loop below instead: 25 groups, int32 SUM 390 -> 315
+        // us, COUNT 327 -> 163, float SUM 516 -> 333; 32 groups 467 -> 324, 414 -> 186,
+        // 609 -> 349.
+        uint32_t h[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) h[r] = key_hash<KD>(b.x[r].k);
+#pragma unroll 1
+        for (int p = 0; p < 3 && full && !found && (p == 0 || lost != ~0ull); ++p) {
 #pragma unroll
           for (int r = 0; r < R; ++r) {
-            const int s = entry_of(home[r], hot);
-            if constexpr (kDig) {
-              const uint32_t fb = __float_as_uint(b.x[r].fv);
-              at_add<true>(&cnt[s], 1u);
-              add_window(s, fb, (fb << 1) + win_off);
-            } else {
-              apply<G, true>(&cnt[s], &val[kVal ? s : 0], nullptr, nullptr, (int64_t)b.x[r].iv, b.x[r].fv);
-            }
+            const bool hit = cur[r] == b.x[r].k;
+            h[r] = next_probe(h[r]);
+            home[r] = hit ? home[r] : home_of(h[r], 0);
           }
-          return;
+#pragma unroll
+          for (int r = 0; r < R; ++r) {  // (an empty slot is no match for the marker key)
+            cur[r] = key[home[r]];
+            cur[r] = b.x[r].k == kMark ? (KT)0 : cur[r];
+          }
+          lost = lost_lanes();
+          found = lost == 0;
         }
       }
-      // Somewhere a key is not at home: the second probes, four rows' in flight
-      // at once.
+      if (found) {
 #pragma unroll
-      for (int q = 0; q < R; q += 4) {
-        KT cur2[4];
-        uint32_t second[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          second[c] = home_of(next_probe(key_hash<KD>(b.x[q + c].k)), 0);
-          cur2[c] = key[second[c]];
+        for (int r = 0; r < R; ++r) {
+          const int s = entry_of(home[r], hot);
+          if constexpr (kDig) {
+            const uint32_t fb = __float_as_uint(b.x[r].fv);
+            at_add<true>(&cnt[s], 1u);
+            add_window(s, fb, (fb << 1) + win_off);
+          } else {
+            apply<G, true>(&cnt[s], &val[kVal ? s : 0], nullptr, nullptr, (int64_t)b.x[r].iv, b.x[r].fv);
+          }
         }
+        return;
+      }
+      if constexpr (REP == 1) {
+        // Somewhere a key is not at home: the second probes, four rows' in flight
+        // at once.
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          __asm__ volatile("" : "+v"(cur2[c]));
-          const bool home_hit = cur[q + c] == b.x[q + c].k;
-          home[q + c] = home_hit ? home[q + c] : second[c];
-          cur[q + c] = home_hit ? cur[q + c] : cur2[c];
+        for (int q = 0; q < R; q += 4) {
+          KT cur2[4];
+          uint32_t second[4];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            second[c] = home_of(next_probe(key_hash<KD>(b.x[q + c].k)), 0);
+            cur2[c] = key[second[c]];
+          }
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            __asm__ volatile("" : "+v"(cur2[c]));
+            const bool home_hit = cur[q + c] == b.x[q + c].k;
+            home[q + c] = home_hit ? home[q + c] : second[c];
+            cur[q + c] = home_hit ? cur[q + c] : cur2[c];
+          }
         }
       }
 #pragma unroll
@@ -1487,9 +1523,11 @@ struct LdsTable {
 // factor, and is cleared and flushed in one step.  2^28 rows, int32 keys,
 // full table -> this one: int64 SUM 1056 -> 478 us at 2 groups, 499 -> 478 at
 // 16; COUNT 545 -> 163 and 210 -> 163; float SUM 1580 -> 348 and 620 -> 343.
+// 256 slots: of 32 random keys in 128, four meet at home and one at its second
+// slot too (512 cost small calls another 0.3 us to clear and flush).
 constexpr int kFewGroups = 32;
 constexpr int kFewCopies = 8;
-constexpr int kFewSlots = 128;
+constexpr int kFewSlots = 256;
 
 // Where a launch's float-sum windows go, from one row per thread, spread evenly
 // over the launch's n rows (word `at` of every `stride`): the sampled

@@ -132,3 +132,18 @@ def test_scatter_carries_rows_between_tiles(agg, kdt, vdt, op):
             assert torch.equal(got[:, 3], count[seen]), ctx
             assert torch.equal(got.view(torch.float64)[:, 2], want[seen].to(torch.float64)), ctx
             g.close()
+
+
+@pytest.mark.parametrize("kdt", ["i32", "i64"])
+@pytest.mark.parametrize("vdt,op", [("i32", "sum"), ("i64", "max"), ("f32", "sum"), ("i32", "count")])
+def test_few_keys_that_meet(agg, kdt, vdt, op):
+    """Up to 32 random keys in the small table: several sets, so that keys meet at
+    home and at their second and third slots, the marker key and key 0 among them."""
+    low = np.iinfo(NP[kdt]).min
+    r = np.random.default_rng(17)
+    for groups in (2, 20, 32, 32, 32, 32):
+        pool = r.integers(low, -(low + 1), size=groups, dtype=np.int64)
+        pool[:2] = (low, 0)
+        for n in (8191, 120_001):
+            keys = pool[r.integers(0, groups, size=n)].astype(NP[kdt])
+            run(agg, keys, make_vals(n, vdt, seed=n), op, 32, f"{kdt}/{vdt} {op} n={n} groups={groups}")
