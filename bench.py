@@ -184,7 +184,7 @@ def energy_power(edges, t_lo, t_hi, res_uj, max_w=POWER_MAX_W, min_span_s=ENERGY
 
 def batch_profile_mode(agg, torch, stream):
     """Dispatches for a kernel trace of the 4096-column batch (both
-    configurations): 5 graph launches each after the autotuner; no JSON line."""
+    configurations): 5 runs each after the autotuner; no JSON line."""
     out = bench_batch(agg, torch, stream, {"i32_sum": {"GB/s": None}}, separate=False)
     log(json.dumps(out))
     log("batch profile mode done")
@@ -978,7 +978,7 @@ def main():
     if not args.no_energy:
         extra["energy"] = bench_energy(agg, torch, dev["i32"], host["i32"], stream)
 
-    # ---- batch: 4096 mixed columns in one persistent launch under a HIP graph
+    # ---- batch: 4096 mixed columns in one persistent launch and a combine
     if not args.no_batch:
         extra["batch"] = bench_batch(agg, torch, stream, table)
 

@@ -163,19 +163,21 @@ int agg_default_tune(int32_t dtype, int32_t op, int32_t prec, int64_t n, int32_t
  * workspace (segment partials, filtered-run counts and two zeroed words,
  * 128 KiB + 256 B; plus
  * staging_depth * chunk_bytes of device staging, a copy stream and events
- * for PINNED_HOST).  tune == NULL: agg_default_tune for max_n. */
+ * for PINNED_HOST).  tune == NULL: agg_default_tune for max_n; where that is
+ * the built-in table, each run takes its entry for the run's own size. */
 int agg_plan(agg_plan_t* out, int32_t dtype, int32_t op, int32_t prec, int64_t max_n,
              int32_t src, const agg_tune* tune);
 
 /* Aggregate col[0..n) into *out on `stream`.  col: an address in the memory
  * the plan's src names, aligned to the item width, with n items readable.
  * out: device memory or page-locked host memory, written by the GPU.
- * Enqueues the scan kernel and the one-workgroup combine kernel (DEVICE,
- * ZEROCOPY; a column of at most 1024 segment partials whose scan runs on at
- * most one workgroup per CU takes the scan launch alone, its last workgroup
- * merging the partials in the same canonical order, so the result bits are
- * the same), or one copy + scan kernel per chunk and then the combine
- * (PINNED_HOST); never allocates and never synchronises the stream, so it
+ * Enqueues the scan kernel and the one-workgroup combine kernel (a column of
+ * at most 1024 segment partials, 4096 with workgroups of eight waves, whose
+ * scan runs on at most one workgroup per CU takes the scan launch alone, its
+ * last workgroup merging the partials in the same canonical order, so the
+ * result bits are the same).  PINNED_HOST: the scan reads the column over the
+ * link, or, with given or cached parameters, one copy + scan kernel per chunk
+ * and then the combine.  Never allocates and never synchronises the stream, so it
  * may be captured into a HIP graph (DEVICE, ZEROCOPY).  Calls with one plan
  * must not overlap (they share its workspace). */
 int agg_run(agg_plan_t plan, const void* col, int64_t n, agg_result* out, void* stream);
@@ -361,7 +363,7 @@ int agg_pack_i32(const int32_t* x, int64_t n, agg_packed_block* blocks, uint32_t
  * src is AGG_SRC_DEVICE (blocks and payload in device memory) or
  * AGG_SRC_ZEROCOPY (in page-locked host memory, read by the kernel over PCIe
  * as it decodes).  n <= the plan's max_n.  Enqueues the decoding scan and the
- * combine on `stream`; results equal agg_run on the raw column.  The headers
+ * combine on `stream` (columns of at most 1024 partials: the scan alone); results equal agg_run on the raw column.  The headers
  * live in memory the host does not read here, so a corrupt one is found by
  * the kernel: it reads nothing through it and the result comes back with
  * is_null = -1 (COUNT reads no block and always gives n). */

@@ -6,9 +6,12 @@
 // INT64_MIN itself lives in one extra slot), every probe of a key hashed anew
 // and their number bounded -- no thread ever waits on another.  Rows are first
 // aggregated into a workgroup's own table in LDS (mostly one probe per row; a
-// row whose key finds no LDS slot goes straight to the global table) and each
-// LDS table is flushed into the global table once, so the global table sees
-// one update per (workgroup, key) instead of one per row.
+// row whose key finds no LDS slot goes straight to the global table).  An LDS
+// table that holds all rows of its keys writes its groups to the output; with
+// many workgroups the tables are written out and merged by a second launch;
+// else each is flushed into the global table, one update per (workgroup, key)
+// instead of one per row, and the emission reads that out.  The emission clears
+// the slots it reads, so the table is clean between calls.
 //
 // Two paths, chosen from the plan's max_groups:
 //  * direct: workgroups stride over the rows; every workgroup's LDS table
@@ -27,8 +30,9 @@
 // order.  A float32 SUM is accumulated exactly: every finite float is
 // m * 2^(k-149) with m < 2^24, added as whole numbers to a fixed-point one (64-bit
 // windows in LDS, base-2^32 digits in the global table), so the group sum is
-// exact whatever the order and is rounded once to double at the end.  The row order inside a partition (set
-// by LDS atomics) therefore never shows in a result.
+// exact whatever the order and is rounded once to double at the end.  The row
+// order inside a partition (set by LDS atomics) therefore never shows in a
+// result.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -111,7 +115,7 @@ constexpr int kDirectThreads = 1024;
 // Tables up to this many slots are emitted by the aggregation launch's last
 // workgroup, larger ones by a launch of their own.  With the table clean from
 // the call before and the group count written by the emission, a call of 1e5
-// rows and 25 groups is one launch instead of four (22.4 -> 12.9 us).  The one
+// rows and 25 groups is one launch instead of four (22.4 -> 13.3 us).  The one
 // workgroup reads past its L2 and a float slot has nine digits, so the line
 // lies lower there.  1e5 rows, int32 keys, one launch against two: 25 groups
 // 12.8 us (14.1); int32 SUM of 1000 groups, 2048 slots 33.6 (34.8), of 2000,
@@ -174,7 +178,8 @@ struct Table {
   int64_t* dig;        // float SUM: kDigits per slot
   int32_t* flags;      // float SUM: 1 NaN, 2 +Inf, 4 -Inf seen
   // [0] overflow (more distinct keys than slots), [2..3] groups emitted (uint64), [4] finished
-  // workgroups, [5] merged runs: the global table holds rows, [6] merged float sums: the windows' base.  State and slots are clean between calls: each call's emission clears what it reads.
+  // workgroups, [5] merged runs: the global table holds rows, [6] merged float sums: the windows'
+  // base.  State and slots are clean between calls: each call's emission clears what it reads.
   int32_t* state;
   int64_t cap;         // slots, a power of two >= 64
   int32_t cap_log2;
@@ -914,7 +919,8 @@ struct LdsTable {
         if constexpr (kVal) {
           if constexpr (G == G_SUM_INT)
             at_add<true>(reinterpret_cast<unsigned long long*>(&val[hot]), (unsigned long long)val[e]);
-          else if constexpr (G == G_MIN_INT || G == G_MIN_F32) atomicMin(reinterpret_cast<long long*>(&val[hot]), (long long)val[e]);
+          else if constexpr (G == G_MIN_INT || G == G_MIN_F32)
+            atomicMin(reinterpret_cast<long long*>(&val[hot]), (long long)val[e]);
           else atomicMax(reinterpret_cast<long long*>(&val[hot]), (long long)val[e]);
         }
         if constexpr (kDig)
@@ -1464,7 +1470,8 @@ struct LdsTable {
     const int64_t g = global_slot(t, (int64_t)k, h);
     if (g < 0) return;
     atomicAdd(reinterpret_cast<unsigned long long*>(t.cnt + g), (unsigned long long)rows);
-    if constexpr (G == G_SUM_INT) atomicAdd(reinterpret_cast<unsigned long long*>(t.val + g), (unsigned long long)get64(x));
+    if constexpr (G == G_SUM_INT)
+      atomicAdd(reinterpret_cast<unsigned long long*>(t.val + g), (unsigned long long)get64(x));
     else if constexpr (G == G_MIN_INT || G == G_MIN_F32)
       atomicMin(reinterpret_cast<long long*>(t.val + g), (long long)get64(x));
     else if constexpr (kVal) atomicMax(reinterpret_cast<long long*>(t.val + g), (long long)get64(x));
@@ -1813,7 +1820,8 @@ __global__ void __launch_bounds__(kDirectThreads) gb_merge_kernel(Args a) {
       else lo = mid + 1;
     }
     const uint32_t at = first[lo] + i - (lo ? upto[lo - 1] : 0u);
-    const uint32_t* r = a.dump + ((int64_t)lo * subs + sub) * region + kSections + 1 + (int64_t)at * decltype(tab)::kRecWords;
+    const uint32_t* records = a.dump + ((int64_t)lo * subs + sub) * region + kSections + 1;
+    const uint32_t* r = records + (int64_t)at * decltype(tab)::kRecWords;
     tab.add_record(a.t, r, (uint32_t)kSectionBits, win_base);
   }
   __syncthreads();
@@ -2166,7 +2174,8 @@ int agg_groupby_run(agg_groupby_t p, const void* keys, const void* vals, int64_t
   p->clean = false;
   const int64_t slots = p->t.cap + 1;
   if (first) {
-    rc = launch(init_kernel(p->gop), (int)std::min<int64_t>(ceil_div(slots, kThreads), (int64_t)cu * 8), kThreads, &a, stream);
+    const int64_t grid = std::min<int64_t>(ceil_div(slots, kThreads), (int64_t)cu * 8);
+    rc = launch(init_kernel(p->gop), (int)grid, kThreads, &a, stream);
     if (rc != AGG_OK) return rc;
   }
   if (n > 0 && p->pt.bits == 0) {
@@ -2188,8 +2197,8 @@ int agg_groupby_run(agg_groupby_t p, const void* keys, const void* vals, int64_t
     fold.emit = !merge && a.emit;
     rc = launch(agg_kernel(p->key_dtype, p->val_dtype, p->gop, p->path), (int)grid, kDirectThreads, &fold, stream);
     if (rc == AGG_OK && merge)
-      rc = launch_lds(p->key_dtype == AGG_I32 ? merge_kernel<AGG_I32>(p->gop) : merge_kernel<AGG_I64>(p->gop), kSections,
-                      kDirectThreads, 0, &a, stream);
+      rc = launch(p->key_dtype == AGG_I32 ? merge_kernel<AGG_I32>(p->gop) : merge_kernel<AGG_I64>(p->gop), kSections,
+                  kDirectThreads, &a, stream);
     if (rc != AGG_OK) return rc;
   } else if (n > 0) {
     const int64_t P = (int64_t)1 << p->pt.bits;
