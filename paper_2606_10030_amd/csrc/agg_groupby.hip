@@ -57,12 +57,12 @@ constexpr int kThreads = 256;
 constexpr int kLdsProbes = 32;
 constexpr int kGlobalProbes = 32;     // hashed probes of the global table, then linear ones
 constexpr int kMaxPartBits = 14;      // at most 16384 (sub-)partitions
-// At least 128 partitions (64 for 2^25 rows and more): with fewer than there are
+// At least 128 partitions (64 for 2^24 rows and more): with fewer than there are
 // aggregation workgroups, several flush the same keys, and their device-scope
 // atomics meet on the same addresses; more shorten the scatter's runs.  32 / 64
 // / 128 / 256 partitions, 50 000 groups: float SUM of 1.7M rows 111 / 83 / 69 / 72
 // us, int32 SUM 75 / 62 / 57 / 63, of 6M rows 106 / 90 / 83 / 83, of 60M rows
-// 420 / 411 / 422 / 439.
+// 420 / 411 / 422 / 439; 4096 groups, float SUM of 30M rows 64 / 128: 235 / 256.
 // With 2^17 groups and more, at least 256: then most partitions are one
 // workgroup's, and their groups leave from LDS (emit_all).  Partitions of few
 // keys are too uneven for that, and 16-byte rows pay more for short runs.  128
@@ -72,7 +72,7 @@ constexpr int kMaxPartBits = 14;      // at most 16384 (sub-)partitions
 // 60M rows 474 / 321.
 constexpr int kMinPartBits = 7, kMinPartBitsLarge = 6, kMinPartBitsMany = 8;
 constexpr int64_t kManyGroups = (int64_t)1 << 17;
-constexpr int64_t kLargeRows = (int64_t)1 << 25;
+constexpr int64_t kLargeRows = (int64_t)1 << 24;
 // Rows are partitioned in chunks of up to 2^28: every chunk ends with each
 // aggregation workgroup flushing the groups it holds, so fewer, larger
 // chunks flush less (the staging area holds one chunk: up to 4 GiB).
@@ -137,6 +137,8 @@ constexpr int64_t kDirectRows = 16 * kDirectThreads;  // rows per workgroup, at 
 constexpr int64_t kMergeMinWg = 16, kMergeMaxWg = 1024;
 constexpr int64_t kMergeMinUpdates = 16'000;  // workgroups x groups
 constexpr int64_t kMergeMaxRows = (int64_t)1 << 31;  // 32-bit row counts
+constexpr int64_t kMergeMaxFloatRows = (int64_t)1 << 24;  // what a window of the merged table holds
+constexpr int64_t kTwoPassFloatRows = (int64_t)1 << 27;
 constexpr int dump_words_of(int g, int kd) {  // a record: key, rows, value (float sum: windows, flags)
   return (kd == AGG_I32 ? 1 : 2) + 1 + (g == G_COUNT ? 0 : g == G_SUM_F32 ? 7 : 2);
 }
@@ -833,9 +835,10 @@ struct LdsTable {
   static_assert((L & (L - 1)) == 0, "home_of takes log2(L) hash bits");
   // Rows a thread folds at a time (two batches are in registers: the next
   // one's loads are in flight): 8, or 4 where a row has four 32-bit words (8
-  // ran 8% slower: spills).
+  // ran 8% slower: spills), or three and copies of float windows (1e5 rows 19.2 ->
+  // 14.1 us, 2^28 rows 512 -> 464).
   template <int VD>
-  static constexpr int tile_rows_of() { return row_words<KD, VD, G>() >= 4 ? 4 : 8; }
+  static constexpr int tile_rows_of() { return row_words<KD, VD, G>() >= (kDig && REP > 1 ? 3 : 4) ? 4 : 8; }
   KT key[L];
   uint32_t cnt[E];  // rows per table stay below 2^32 (a workgroup's share is at most 2^28 rows)
   int64_t val[kVal ? E : 1];
@@ -1006,6 +1009,7 @@ struct LdsTable {
     };
     const uint32_t tid = threadIdx.x;
     uint32_t hot = kNoHot;
+    bool cold = true;  // the first batch
     // a float's exponent is compared in place, as the top byte of its bits << 1
     // less the pass's first exponent (exponents below it wrap past the span);
     // no pass takes out_from and up, seen from the first one (zeros, subnormals
@@ -1100,7 +1104,7 @@ struct LdsTable {
       // Nearly every batch of a wave: each row of each lane finds its key at
       // home (and its float in a window), tested for all of them at once, so
       // a row is its adds and nothing else.
-      auto lost_lanes = [&]() -> uint64_t {  // lanes with a row that is not found
+      auto all_found = [&]() -> bool {
         KT differ = 0;
         uint32_t far = 0;
 #pragma unroll
@@ -1108,26 +1112,22 @@ struct LdsTable {
           differ |= cur[r] ^ b.x[r].k;
           if constexpr (kDig) far = max(far, (__float_as_uint(b.x[r].fv) << 1) + win_off);
         }
-        return __ballot(differ != 0 || (kDig && far >= win_span));
+        return full && __all(differ == 0 && (!kDig || far < win_span));
       };
       bool found = false;
-      uint64_t lost = ~0ull;
-      if constexpr (!SUB) {
-        lost = lost_lanes();
-        found = full && lost == 0;
-      }
+      if constexpr (!SUB) found = all_found();
       if constexpr (REP > 1) {
         // Few keys, so many rows may be of one that is not at home: the next probes
-        // of the whole batch, up to three, until all are found (or no lane has all
-        // of its own: a table that is still empty).  Random int32 keys, 2^28 rows,
-        // with 128 slots and the loop below instead: 25 groups, int32 SUM 390 -> 315
-        // us, COUNT 327 -> 163, float SUM 516 -> 333; 32 groups 467 -> 324, 414 -> 186,
-        // 609 -> 349.
+        // of the whole batch, up to three, until all are found (not in the first
+        // batch, which finds the table empty).  Random int32 keys, 2^28 rows, with 128
+        // slots and the loop below instead: 25 groups, int32 SUM 390 -> 315 us, COUNT
+        // 327 -> 163, float SUM 516 -> 333; 32 groups 467 -> 324, 414 -> 186, 609 ->
+        // 349 (a set of which a key is at its third slot: COUNT 240, at its fourth 310).
         uint32_t h[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) h[r] = key_hash<KD>(b.x[r].k);
 #pragma unroll 1
-        for (int p = 0; p < 3 && full && !found && (p == 0 || lost != ~0ull); ++p) {
+        for (int p = 0; p < 3 && full && !found && !cold; ++p) {
 #pragma unroll
           for (int r = 0; r < R; ++r) {
             const bool hit = cur[r] == b.x[r].k;
@@ -1139,8 +1139,7 @@ struct LdsTable {
             cur[r] = key[home[r]];
             cur[r] = b.x[r].k == kMark ? (KT)0 : cur[r];
           }
-          lost = lost_lanes();
-          found = lost == 0;
+          found = all_found();
         }
       }
       if (found) {
@@ -1248,6 +1247,7 @@ struct LdsTable {
         Batch B;
         load(B, more ? next : b);  // never behind a branch: the fold would wait for it (the last one is not used)
         fold(A, b, true, 0);
+        cold = false;
         b = next;
         if (!more) break;
         A = B;
@@ -2046,7 +2046,10 @@ int agg_groupby_plan(agg_groupby_t* out, int32_t key_dtype, int32_t val_dtype, i
   // pass costs about one direct run, so four would lose.)
   int bits = 0, direct_sub_bits = 0;
   const int64_t half_table = lds_slots_of(g, key_dtype) / 2;
-  if (max_groups > half_table && max_groups <= 2 * half_table && g != G_COUNT) {
+  // Float sums of fewer rows partition too: 4096 groups, 3e7 rows 335 us in two
+  // passes, 239 partitioned; 5e5 rows 61 and 53; 2^28 rows 1358 and 1594.
+  const bool two_passes = g != G_COUNT && !(g == G_SUM_F32 && max_n < kTwoPassFloatRows);
+  if (max_groups > half_table && max_groups <= 2 * half_table && two_passes) {
     direct_sub_bits = 1;
   } else if (max_groups > half_table) {
     auto bits_for = [max_groups](int64_t per_part) {
@@ -2188,7 +2191,7 @@ int agg_groupby_run(agg_groupby_t p, const void* keys, const void* vals, int64_t
                                            std::min<int64_t>(ceil_div(n, wg_rows), (int64_t)cu * p->agg_blocks));
     // (a float sum's windows take the rows of one table, merged or not)
     const bool merge = grid > kMergeMinWg && grid <= p->dump_wgs && grid * p->max_groups >= kMergeMinUpdates &&
-                       n <= (p->gop == G_SUM_F32 ? kMaxTableRows : kMergeMaxRows);
+                       n <= (p->gop == G_SUM_F32 ? kMergeMaxFloatRows : kMergeMaxRows);
     a.dump = p->dump;
     a.dump_max = p->dump_max;
     a.dumps = merge ? (int)grid : 0;

@@ -87,3 +87,25 @@ def test_plan_for_many_rows_run_on_few(agg, kdt, vdt, op):
         compare(g.run(torch.from_numpy(keys).cuda(), torch.from_numpy(vals).cuda()), oracle.groupby(keys, vals, op),
                 f"{kdt}/{vdt} {op} n={n}")
     g.close()
+
+
+@pytest.mark.parametrize("kdt", ["i32", "i64"])
+@pytest.mark.parametrize("op", ["sum", "avg"])
+def test_two_pass_float_plan(agg, kdt, op):
+    """Float sums by as many groups as take two passes of the direct path, which
+    plans for 2^27 rows and more do (smaller ones partition): few rows, flushed,
+    and more, merged, with rows outside the windows and without."""
+    import torch
+    groups = 4000
+    r = np.random.default_rng(23)
+    for max_n in ((1 << 27) - 1, 1 << 27):
+        g = agg.GroupBy(kdt, "f32", op, max_n=max_n, max_groups=groups)
+        for n in (1, 4097, 200_003, 600_001):
+            keys = (r.integers(-groups // 2, groups // 2, size=n) * 7919).astype(np.int32 if kdt == "i32" else np.int64)
+            vals = make_vals(n, "f32", seed=n)
+            for far in (False, True):
+                if far:
+                    vals[::1009] = np.float32(-1e33)
+                compare(g.run(torch.from_numpy(keys).cuda(), torch.from_numpy(vals).cuda()),
+                        oracle.groupby(keys, vals, op), f"{kdt} {op} max_n={max_n} n={n} far={far}")
+        g.close()
