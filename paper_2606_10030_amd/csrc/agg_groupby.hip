@@ -43,6 +43,7 @@
 #include "agg.h"
 #include "agg_device.hpp"
 #include "agg_digits.hpp"
+#include "agg_hash.hpp"
 #include "agg_internal.hpp"
 
 namespace agg {
@@ -50,11 +51,6 @@ namespace gb {
 
 constexpr int64_t kEmpty = INT64_MIN;
 constexpr int kThreads = 256;
-// Probes of an LDS table.  At half load a key finds none of 16 free once in 2^16:
-// with 4096 keys in 256 tables that was a row in the global table every few runs,
-// and merged tables (gb_merge_kernel) then went there too: 6M rows, float SUM of
-// 4096 groups 99 us, or 156.
-constexpr int kLdsProbes = 32;
 constexpr int kGlobalProbes = 32;     // hashed probes of the global table, then linear ones
 constexpr int kMaxPartBits = 14;      // at most 16384 (sub-)partitions
 // At least 128 partitions (64 for 2^24 rows and more): with fewer than there are
@@ -180,8 +176,8 @@ struct Table {
   int64_t* dig;        // float SUM: kDigits per slot
   int32_t* flags;      // float SUM: 1 NaN, 2 +Inf, 4 -Inf seen
   // [0] overflow (more distinct keys than slots), [2..3] groups emitted (uint64), [4] finished
-  // workgroups, [5] merged runs: the global table holds rows, [6] merged float sums: the windows'
-  // base.  State and slots are clean between calls: each call's emission clears what it reads.
+  // workgroups, merged runs: [5] the fold put rows into the global table, [6] float sums: the
+  // windows' base, [7] the merge put rows there.  State and slots are clean between calls: each call's emission clears what it reads.
   int32_t* state;
   int64_t cap;         // slots, a power of two >= 64
   int32_t cap_log2;
@@ -236,29 +232,10 @@ __device__ __forceinline__ void clear_slot(const Table& t, int64_t s) {
 
 __device__ __forceinline__ int64_t ceil_div_dev(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// The hash of a key: one 32-bit multiply by 2^32 / golden ratio (int64 keys
-// add the high word times a second odd constant, the fraction of sqrt 2).
-// Everything that places a key reads bits from the top of it downwards: its
-// partition, then its sub-partition pass, then its LDS slot, and its home in
-// the global table.  Dictionary codes and surrogate keys, which run densely,
-// then spread evenly by themselves (the multiples of the golden ratio mod 1),
-// so a wave's 64 first probes nearly all hit, and the slots of a workgroup's
-// table lie in the order of their homes in the global table, which a flush
-// walks almost sequentially.  Two quarter-rate multiplies (one for int32
-// keys) against the eight of a 64-bit finaliser: an LDS fold is bound by its
-// instructions, not by its bytes.
 template <int KD>
 __device__ __forceinline__ uint32_t key_hash(typename std::conditional<KD == AGG_I32, int32_t, int64_t>::type k) {
-  const uint32_t lo = (uint32_t)k * 0x9638806Du;
-  if constexpr (KD == AGG_I32) return lo;
-  else return lo + (uint32_t)((uint64_t)k >> 32) * 0x69C77F93u;
+  return key_hash_of(k);
 }
-
-// The hash of a key's next probe, again read from the top.  Each probe lands
-// somewhere new: with a fixed step (double hashing) a key of a dense set whose
-// step is the distance between two others' homes only ever meets occupied
-// slots.
-__device__ __forceinline__ uint32_t next_probe(uint32_t h) { return h * 0x85EBCA6Bu + 0x7FEB352Du; }
 
 // Partition of a key: the top bits of its hash.
 __device__ __forceinline__ uint32_t part_of(uint32_t h, int bits) { return h >> (32 - bits); }
@@ -1443,8 +1420,8 @@ struct LdsTable {
     return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
 
-  // Adds a record; to the global table if its key finds no slot (as any other
-  // record of the key then does too).
+  // The merge's: adds a record, to the global table if its key finds no slot (as
+  // any other record of the key then does too).
   __device__ __forceinline__ void add_record(const Table& t, const uint32_t* r, uint32_t skip, uint32_t win_base) {
     const KT k = kKeyWords == 2 ? (KT)get64(r) : (KT)(int32_t)r[0];
     const uint32_t rows = r[kKeyWords], h = key_hash<KD>(k);
@@ -1466,7 +1443,7 @@ struct LdsTable {
       }
       return;
     }
-    mark_global(t);
+    mark_global(t, 7);
     const int64_t g = global_slot(t, (int64_t)k, h);
     if (g < 0) return;
     atomicAdd(reinterpret_cast<unsigned long long*>(t.cnt + g), (unsigned long long)rows);
@@ -1482,9 +1459,12 @@ struct LdsTable {
       if (x[2 * kWindows]) atomicOr(t.flags + g, (int32_t)x[2 * kWindows]);
     }
   }
-  // Merged runs: the global table holds rows, so the merge's last workgroup emits it too.
-  static __device__ __forceinline__ void mark_global(const Table& t) {
-    __hip_atomic_store(&t.state[5], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // Merged runs: the global table holds rows, so the merge's last workgroup emits
+  // it too.  The fold and the merge have a mark each (state[word]): what a merge
+  // workgroup does must not hang on when it looks, so it goes by the fold's mark,
+  // which is final before the merge starts.
+  static __device__ __forceinline__ void mark_global(const Table& t, int word) {
+    __hip_atomic_store(&t.state[word], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 
   // A slot's flush is a chain of device-scope accesses (read the global home,
@@ -1694,7 +1674,7 @@ gb_aggregate_kernel(Args a) {
           const bool dumped = fw.passes == 1 && tab.dump(region, a.dump_max);
           if (fw.passes > 1 && threadIdx.x <= kSections) region[threadIdx.x] = 0;
           if (threadIdx.x == 0) {
-            if (!dumped || tab.spilled) decltype(tab)::mark_global(a.t);
+            if (!dumped || tab.spilled) decltype(tab)::mark_global(a.t, 5);
             if (blockIdx.x == 0) a.t.state[6] = (int32_t)fw.base(0);
           }
           if (dumped) written = true;
@@ -1780,8 +1760,11 @@ __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a)
 }
 
 // Merges the direct path's tables: workgroup s adds the records of section s of
-// every region in an LDS table and writes its groups.  If rows are in the
-// global table too, the tables go there instead and the last workgroup emits it.
+// every region in an LDS table and writes its groups.  If the fold left rows in
+// the global table too, the tables go there instead.  A key that finds no slot
+// here (a section holds far more than its share of the keys) is in no table here,
+// so its records go to the global table and the others' groups leave as usual.
+// The last workgroup emits what the global table holds.
 template <int KD, int G>
 __global__ void __launch_bounds__(kDirectThreads) gb_merge_kernel(Args a) {
   __shared__ LdsTable<G, KD, kMergeSlots, kDirectThreads> tab;
@@ -1810,8 +1793,8 @@ __global__ void __launch_bounds__(kDirectThreads) gb_merge_kernel(Args a) {
   __syncthreads();
   const uint32_t total = upto[kDirectThreads - 1];
   const uint32_t win_base = G == G_SUM_F32 ? (uint32_t)a.t.state[6] : 0u;
+  // the same in every wave and workgroup: nothing writes this word before the last workgroup below
   const bool global = __hip_atomic_load(&a.t.state[5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-  __syncthreads();  // (below, other workgroups may mark it)
   for (uint32_t i = tid; i < total; i += kDirectThreads) {
     int lo = 0, hi = a.dumps - 1;  // the first region that ends after record i
     while (lo < hi) {
@@ -1825,15 +1808,16 @@ __global__ void __launch_bounds__(kDirectThreads) gb_merge_kernel(Args a) {
     tab.add_record(a.t, r, (uint32_t)kSectionBits, win_base);
   }
   __syncthreads();
-  // (all workgroups read the mark before this launch's own marks count: a key
-  // that found no slot here is in no table here)
   if (global) tab.flush(a.t, win_base, true);
   else tab.emit_all(a, win_base);
   if (!last_to_finish(reinterpret_cast<uint32_t*>(a.t.state + 4))) return;
-  if (__hip_atomic_load(&a.t.state[5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
+  if (global || __hip_atomic_load(&a.t.state[7], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
     emit_slots<G, true, kDirectThreads>(a, 0, a.t.cap + 1);
-  __syncthreads();
-  if (tid == 0) __hip_atomic_store(&a.t.state[5], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();  // every wave has read the marks
+  if (tid == 0) {
+    __hip_atomic_store(&a.t.state[5], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&a.t.state[7], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   finish_emission(a);
 }
 
