@@ -134,7 +134,6 @@ constexpr int64_t kMergeMinWg = 16, kMergeMaxWg = 1024;
 constexpr int64_t kMergeMinUpdates = 16'000;  // workgroups x groups
 constexpr int64_t kMergeMaxRows = (int64_t)1 << 31;  // 32-bit row counts
 constexpr int64_t kMergeMaxFloatRows = (int64_t)1 << 24;  // what a window of the merged table holds
-constexpr int64_t kTwoPassFloatRows = (int64_t)1 << 27;
 constexpr int dump_words_of(int g, int kd) {  // a record: key, rows, value (float sum: windows, flags)
   return (kd == AGG_I32 ? 1 : 2) + 1 + (g == G_COUNT ? 0 : g == G_SUM_F32 ? 7 : 2);
 }
@@ -154,16 +153,42 @@ constexpr int lds_slots_of(int g, int kd) {
 // 1653, 2^20 groups 2982 -> 2343.
 constexpr int kWindows = 3;
 constexpr int kWinOctaves = 16;
-constexpr int kWinSpan = kWindows * kWinOctaves;  // 48 exponents a pass: 14 decades
 constexpr int64_t kMaxTableRows = (int64_t)1 << 23;
-// The exponents the windows cover: kWinSpan from `first` on in the first of
-// `passes` passes over the rows, the next kWinSpan in the second, and so on.
+// A column of more than kWindows windows' exponents (48: 14 decades) takes a table
+// of fewer slots with more windows each, in the same LDS: of 4-byte keys 2048 slots
+// of 7 (112 exponents) or 1024 of 14, of 8-byte keys 2048 of 6 or 1024 of 12.  Keys
+// that such a table does not hold in half of its slots take several passes over the
+// rows, by the next bits of their hash, and the columns that spread over more
+// exponents than 14 (12) windows two passes by exponent.  The few-groups table has
+// room for 9 windows.  (Before, every column took passes of kWindows windows, each
+// with its own reading of the rows and its own flush.  int32 keys, 60 exponents, 2^28
+// rows: 5 groups 1044 -> 332 us, 300 746 -> 550, 50 000 2066 -> 1914; 200 exponents: 300
+// groups 1774 -> 682, 50 000 3354 -> 2420; 10^6 rows of 200 exponents: 300 groups 96 ->
+// 52, 50 000 146 -> 94.)
+constexpr int kMidSlots = 2048, kAllSlots = 1024;
+constexpr int mid_windows_of(int kd) { return kd == AGG_I32 ? 7 : 6; }
+constexpr int kFewWindows = 9;
+// Rows outside the windows go to the global table one by one.  When a table of
+// kWindows has met this many (the sample was not of the column's kind), it is
+// flushed, and the workgroup's other rows go to tables of all windows.
+constexpr uint32_t kFarRows = 256;
+constexpr int64_t kTwoPassFloatRows = (int64_t)1 << 27;
+// A float sum's tables: 2^lg slots of nw windows, which cover `span` exponents from
+// `first` on in the first of `passes` passes over the rows, the next ones in the
+// second, and so on; each of these is 2^sub_bits passes by the keys' hash.
 struct FloatWindows {
   int first = 1;
   int passes = 1;
-  __device__ __forceinline__ uint32_t base(int pass) const { return (uint32_t)(first + pass * kWinSpan); }
+  int nw = kWindows;
+  int lg = 0;
+  int sub_bits = 0;
+  __device__ __forceinline__ uint32_t base(int pass) const { return (uint32_t)(first + pass * nw * kWinOctaves); }
   // exponents of the pass (255 marks non-finite floats and is never one of them)
-  __device__ __forceinline__ uint32_t span(int pass) const { return min((uint32_t)kWinSpan, 255u - base(pass)); }
+  __device__ __forceinline__ uint32_t span(int pass) const {
+    return min((uint32_t)(nw * kWinOctaves), 255u - base(pass));
+  }
+  __device__ __forceinline__ bool narrow() const { return nw == kWindows; }
+  __device__ __forceinline__ bool single() const { return narrow() && passes == 1; }
 };
 template <int G, int KD>
 constexpr int lds_slots() { return lds_slots_of(G, KD); }
@@ -213,6 +238,16 @@ struct Args {
   int32_t dump_max;    // records a region holds
   int32_t whole;       // partitioned path: all rows are in this launch (a table may emit its groups itself)
 };
+
+// The kernel's arguments, read again: what only the rare paths and the ends of the
+// aggregation kernels need of them does not stay in scalar registers during the
+// fold, which spills those.
+__device__ __forceinline__ const Args& late_args() {
+  typedef __attribute__((address_space(4))) const Args kernarg;
+  kernarg* p = (kernarg*)__builtin_amdgcn_kernarg_segment_ptr();
+  __asm__ volatile("" : "+s"(p));
+  return *(const Args*)p;
+}
 
 template <int G>
 constexpr int64_t val_identity() {
@@ -793,58 +828,74 @@ constexpr int row_words() {
 // integer merges: the results do not depend on REP).
 // HOT: the table finds a key that most of its rows have, and gives each lane an
 // entry for it (find_hot).
-template <int G, int KD, int L_, int NT, int REP = 1, bool HOT = false>
+// WORDS: 64-bit windows of a float sum in all; its slots and windows are those of
+// a FloatWindows `z` (2^z.lg slots of at most L_), all other tables have L_ slots.
+template <int G, int KD, int L_, int NT, int REP = 1, bool HOT = false, int WORDS = 0>
 struct LdsTable {
   using KT = typename std::conditional<KD == AGG_I32, int32_t, int64_t>::type;
   using UKT = typename std::conditional<KD == AGG_I32, unsigned int, unsigned long long>::type;
   static constexpr KT kMark = std::numeric_limits<KT>::min();  // empty hashed slot
-  static constexpr int L = L_;
-  static constexpr int kLog2L = __builtin_ctz((unsigned)L_);
+  static constexpr int kMaxL = L_;
   // Accumulator entries: slot s, copy c at s * REP + c; then one per lane for
   // the hot slot's rows (find_hot).
   static constexpr int kHotLanes = HOT ? 64 : 0;
-  static constexpr int E = (L + 1) * REP + kHotLanes;
+  static constexpr int kMaxE = (L_ + 1) * REP + kHotLanes;
   static constexpr uint32_t kNoHot = ~0u;
   static constexpr bool kDig = G == G_SUM_F32;
+  static constexpr bool kFlex = kDig && WORDS != 0;  // (else kWindows)
+  static constexpr bool kLeaves = kDig && !(kFlex && REP == 1);  // may leave rows to tables of more windows
+  static __device__ __forceinline__ int log2l(const FloatWindows& z) {
+    if constexpr (kFlex && REP == 1) return z.lg;
+    else return __builtin_ctz((unsigned)L_);
+  }
+  static __device__ __forceinline__ int slots(const FloatWindows& z) { return 1 << log2l(z); }
+  static __device__ __forceinline__ int entries(const FloatWindows& z) { return (slots(z) + 1) * REP + kHotLanes; }
+  static __device__ __forceinline__ int windows(const FloatWindows& z) { return kFlex ? z.nw : kWindows; }
   static constexpr bool kVal = !kDig && G != G_COUNT;
   static_assert((REP & (REP - 1)) == 0 && REP <= 64, "copies: a power of two, at most a wave");
   static_assert(!HOT || REP == 1, "one kind of copies");
-  static_assert((L & (L - 1)) == 0, "home_of takes log2(L) hash bits");
+  static_assert((L_ & (L_ - 1)) == 0, "home_of takes log2(L) hash bits");
   // Rows a thread folds at a time (two batches are in registers: the next
   // one's loads are in flight): 8, or 4 where a row has four 32-bit words (8
   // ran 8% slower: spills), or three and copies of float windows (1e5 rows 19.2 ->
   // 14.1 us, 2^28 rows 512 -> 464).
   template <int VD>
   static constexpr int tile_rows_of() { return row_words<KD, VD, G>() >= (kDig && REP > 1 ? 3 : 4) ? 4 : 8; }
-  KT key[L];
-  uint32_t cnt[E];  // rows per table stay below 2^32 (a workgroup's share is at most 2^28 rows)
-  int64_t val[kVal ? E : 1];
-  int64_t win[kDig ? kWindows * E : 1];    // float sum: window w of entry e at w * E + e
-  uint32_t flags[kDig ? L / 8 + 1 : 1];    // float sum: non-finite rows seen, four bits a slot
+  KT key[kMaxL];
+  uint32_t cnt[kMaxE];  // rows per table stay below 2^32 (a workgroup's share is at most 2^28 rows)
+  int64_t val[kVal ? kMaxE : 1];
+  int64_t win[kFlex ? WORDS : kDig ? kWindows * kMaxE : 1];  // float sum: window w of entry e at w * entries + e
+  uint32_t flags[kDig ? kMaxL / 8 + 1 : 1];  // float sum: non-finite rows seen, four bits a slot
   uint16_t list[NT / 64][128];             // per wave: slots to flush
   uint32_t spilled;                        // a row went to the global table
+  uint32_t far_rows;                       // float sum: rows outside the windows
   uint32_t emit_base[2];                   // emit_all: the output range's first group
   uint32_t wave_groups[NT / 64];           // emit_all: groups per wave
   uint32_t hot_sh;                         // the hot slot + 1; 0: there is none
 
-  __device__ __forceinline__ void clear(uint32_t skip) {
+  __device__ __forceinline__ void clear(uint32_t skip, const FloatWindows& z) {
+    const int L = slots(z), E = entries(z);
     // The marker key's home holds key 0 from the start: a row of the marker key
     // then never finds its key at home (it would take an empty slot for its
     // own), and goes on to slot L.  Key 0 may use the slot like any other it
     // finds itself in; with no rows it is not flushed.
-    const int marker_home = (int)home_of(key_hash<KD>(kMark), skip);
+    const int marker_home = (int)home_of(key_hash<KD>(kMark), skip, z);
     for (int e = threadIdx.x; e < L; e += NT) key[e] = e == marker_home ? (KT)0 : kMark;
     for (int e = threadIdx.x; e < E; e += NT) {
       cnt[e] = 0;
       if constexpr (kVal) val[e] = val_identity<G>();
-      if constexpr (kDig)
+      if constexpr (kDig && !kFlex)
         for (int w = 0; w < kWindows; ++w) win[w * E + e] = 0;
     }
-    if constexpr (kDig)
+    if constexpr (kDig) {
+      if constexpr (kFlex)
+        for (int i = threadIdx.x; i < windows(z) * E; i += NT) win[i] = 0;
       for (int e = threadIdx.x; e <= L / 8; e += NT) flags[e] = 0;
+    }
     if (threadIdx.x == 0) {
       hot_sh = 0;
       spilled = 0;
+      far_rows = 0;
     }
   }
 
@@ -884,13 +935,14 @@ struct LdsTable {
     return h - 1;  // 0: none
   }
   // The entry that this lane's row of slot s goes to.
-  static __device__ __forceinline__ int entry_of(uint32_t s, uint32_t hot) {
+  static __device__ __forceinline__ int entry_of(uint32_t s, uint32_t hot, int L) {
     if constexpr (HOT) return (int)(s == hot ? L + 1 + (threadIdx.x & 63) : s);
     else return (int)(s * REP + (threadIdx.x & (REP - 1)));
   }
   // Between the fold's barrier and the flush.
-  __device__ __forceinline__ void merge_hot() {
+  __device__ __forceinline__ void merge_hot(const FloatWindows& z) {
     if constexpr (kHotLanes != 0) {
+      const int L = slots(z), E = entries(z);
       const uint32_t hot = hot_slot();
       if (hot == kNoHot) return;  // the whole workgroup
       if (threadIdx.x < 64) {
@@ -904,7 +956,7 @@ struct LdsTable {
           else atomicMax(reinterpret_cast<long long*>(&val[hot]), (long long)val[e]);
         }
         if constexpr (kDig)
-          for (int w = 0; w < kWindows; ++w)
+          for (int w = 0; w < windows(z); ++w)
             at_add<true>(reinterpret_cast<unsigned long long*>(&win[w * E + hot]), (unsigned long long)win[w * E + e]);
       }
       __syncthreads();
@@ -913,15 +965,19 @@ struct LdsTable {
 
   // The home slot of a key with hash h: the log2(L) hash bits below the
   // `skip` that chose its partition and pass.
-  static __device__ __forceinline__ uint32_t home_of(uint32_t h, uint32_t skip) {
-    return __builtin_amdgcn_ubfe(h, (uint32_t)(32 - kLog2L) - skip, (uint32_t)kLog2L);
+  static __device__ __forceinline__ uint32_t home_of(uint32_t h, uint32_t skip, const FloatWindows& z) {
+    // (two operands in scalar registers would cost a bit-field extract a vector register)
+    if constexpr (kFlex && REP == 1) return (h << skip) >> (32 - log2l(z));
+    else return __builtin_amdgcn_ubfe(h, (uint32_t)(32 - log2l(z)) - skip, (uint32_t)log2l(z));
   }
+  // The slot of its next probe, of hash h.
+  static __device__ __forceinline__ uint32_t probe_of(uint32_t h, const FloatWindows& z) { return h >> (32 - log2l(z)); }
 
   // The slot of key k with hash h, claiming an empty one; -1 if there is none
   // within kLdsProbes probes.
-  __device__ __forceinline__ int slot_of(KT k, uint32_t h, uint32_t skip) {
-    if (k == kMark) return L;
-    uint32_t s = home_of(h, skip);
+  __device__ __forceinline__ int slot_of(KT k, uint32_t h, uint32_t skip, const FloatWindows& z) {
+    if (k == kMark) return slots(z);
+    uint32_t s = home_of(h, skip, z);
 #pragma unroll 1
     for (int p = 0; p < kLdsProbes; ++p) {
       const KT cur = key[s];
@@ -931,21 +987,25 @@ struct LdsTable {
         if (prev == kMark || prev == k) return (int)s;
       }
       h = next_probe(h);
-      s = home_of(h, 0);
+      s = probe_of(h, z);
     }
     return -1;
   }
 
   // Adds the float of bits fb to the windows of entry s; u = its bits << 1
-  // less the pass's first exponent << 24, below kWinSpan << 24.
-  __device__ __forceinline__ void add_window(int s, uint32_t fb, uint32_t u) {
+  // less the pass's first exponent << 24, below the windows' span << 24; E: entries.
+  __device__ __forceinline__ void add_window(int s, uint32_t fb, uint32_t u, int E) {
     const int32_t sign = (int32_t)fb >> 31;
     const int32_t m = (int32_t)(((fb & 0x7FFFFFu) | 0x800000u) ^ (uint32_t)sign) - sign;
     const uint32_t w = u >> 28, sh = __builtin_amdgcn_ubfe(u, 24, 4);
     static_assert(kWinOctaves == 16, "a window is the exponent's upper four bits");
     // m is never 0, so its sign word is the upper half of the 64-bit value
     const uint64_t v = (((uint64_t)(uint32_t)sign << 32) | (uint32_t)m) << sh;
-    at_add<true>(reinterpret_cast<unsigned long long*>(&win[__umul24(w, E) + (uint32_t)s]), (unsigned long long)v);
+    uint32_t at;
+    if constexpr (kFlex)  // one full-rate instruction: left to itself the compiler takes a 32-bit multiply for an E it does not know
+      __asm__("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(at) : "v"(w), "s"(E), "v"(s));
+    else at = __umul24(w, E) + (uint32_t)s;
+    at_add<true>(reinterpret_cast<unsigned long long*>(&win[at]), (unsigned long long)v);
   }
 
   // Folds the rows of the tiles first, first + tile_step, ... (kTile rows
@@ -953,8 +1013,10 @@ struct LdsTable {
   // sub_mask equal to sub; a row whose key finds no slot within kLdsProbes
   // probes goes to the global table.
   // ROWS: keys holds staged (key, value) records.  SUB: the plan has
-  // sub-partition passes (else every row belongs to the single pass and the
-  // per-row test of its hash bits is left out).
+  // sub-partition passes (0: every row belongs to the single pass and the
+  // per-row test of its hash bits is left out; 2: sub_mask 0 is a single pass).
+  // Returns the first row that this wave leaves to another table (kFarRows), or
+  // last.
   //
   // Bound by instructions and LDS atomics, so a full tile's rows carry neither
   // bounds test nor address arithmetic (a uniform base per row and one lane
@@ -967,13 +1029,14 @@ struct LdsTable {
   // each lane at a time.  (Random keys that fill half a table, 2^28 rows:
   // int64 SUM of 4096 groups 830 -> 721 us; with the loop right after the
   // first probes 923.)
-  template <int VD, bool ROWS, bool SUB>
-  __device__ __forceinline__ void fold_rows(const Table& t_, const void* keys, const void* vals, int64_t first,
-                                            int64_t last, int64_t tile_step, uint32_t skip, uint32_t sub_shift,
-                                            uint32_t sub_mask, uint32_t sub, const FloatWindows& fw, int pass) {
+  template <int VD, bool ROWS, int SUB>
+  __device__ __forceinline__ int64_t fold_rows(const Args& a_, const void* keys, const void* vals, int64_t first,
+                                               int64_t last, int64_t tile_step, uint32_t skip, uint32_t sub_shift,
+                                               uint32_t sub_mask, uint32_t sub, const FloatWindows& fw, int pass) {
     constexpr int R = tile_rows_of<VD>();
     constexpr int TR = R * NT;
     constexpr bool kStaged = ROWS && G != G_COUNT;
+    const int L = slots(fw), E = entries(fw);
     using IVT = typename std::conditional<VD == AGG_I64, int64_t, int32_t>::type;
     using SR = StagedRow<KD, VD == AGG_I64 ? AGG_I64 : AGG_I32>;
     struct Row {
@@ -993,7 +1056,7 @@ struct LdsTable {
     // and non-finite floats among them)
     const uint32_t win_off = 0u - (fw.base(pass) << 24), win_span = fw.span(pass) << 24;
     const uint32_t out_from =
-        pass == 0 ? min((uint32_t)(fw.passes * kWinSpan), 255u - fw.base(0)) << 24 : UINT32_MAX;
+        pass == 0 ? min((uint32_t)(fw.passes * fw.nw * kWinOctaves), 255u - fw.base(0)) << 24 : UINT32_MAX;
     auto load_row = [&](Row& x, int64_t base, uint32_t lane) {  // row base + lane (base uniform)
       x.iv = 0;
       x.fv = 0.0f;
@@ -1054,7 +1117,8 @@ struct LdsTable {
 #pragma unroll
       for (int r = 0; r < R; ++r) load_row(b.x[r], base, std::min<uint32_t>(row_at(r), left - 1));
     };
-    auto fold = [&](Batch& b, int64_t base, bool full, uint32_t left) {
+    // true: the wave's other rows are for another table
+    auto fold = [&](Batch& b, int64_t base, bool full, uint32_t left) -> bool {
       // the batch's loads are complete before its first row is folded: left
       // alone, the compiler sinks a value load into the branch that uses it,
       // and that load's whole latency then stalls the wave
@@ -1071,7 +1135,7 @@ struct LdsTable {
       KT cur[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        home[r] = home_of(key_hash<KD>(b.x[r].k), skip);
+        home[r] = home_of(key_hash<KD>(b.x[r].k), skip, fw);
         cur[r] = key[home[r]];
       }
       // one wait for all of the batch's probes: left alone, each row's check
@@ -1092,7 +1156,7 @@ struct LdsTable {
         return full && __all(differ == 0 && (!kDig || far < win_span));
       };
       bool found = false;
-      if constexpr (!SUB) found = all_found();
+      if constexpr (SUB != 1) found = (SUB == 0 || sub_mask == 0) && all_found();
       if constexpr (REP > 1) {
         // Few keys, so many rows may be of one that is not at home: the next probes
         // of the whole batch, up to three, until all are found (not in the first
@@ -1109,7 +1173,7 @@ struct LdsTable {
           for (int r = 0; r < R; ++r) {
             const bool hit = cur[r] == b.x[r].k;
             h[r] = next_probe(h[r]);
-            home[r] = hit ? home[r] : home_of(h[r], 0);
+            home[r] = hit ? home[r] : probe_of(h[r], fw);
           }
 #pragma unroll
           for (int r = 0; r < R; ++r) {  // (an empty slot is no match for the marker key)
@@ -1122,16 +1186,16 @@ struct LdsTable {
       if (found) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          const int s = entry_of(home[r], hot);
+          const int s = entry_of(home[r], hot, L);
           if constexpr (kDig) {
             const uint32_t fb = __float_as_uint(b.x[r].fv);
             at_add<true>(&cnt[s], 1u);
-            add_window(s, fb, (fb << 1) + win_off);
+            add_window(s, fb, (fb << 1) + win_off, E);
           } else {
             apply<G, true>(&cnt[s], &val[kVal ? s : 0], nullptr, nullptr, (int64_t)b.x[r].iv, b.x[r].fv);
           }
         }
-        return;
+        return false;
       }
       if constexpr (REP == 1) {
         // Somewhere a key is not at home: the second probes, four rows' in flight
@@ -1142,7 +1206,7 @@ struct LdsTable {
           uint32_t second[4];
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            second[c] = home_of(next_probe(key_hash<KD>(b.x[q + c].k)), 0);
+            second[c] = probe_of(next_probe(key_hash<KD>(b.x[q + c].k)), fw);
             cur2[c] = key[second[c]];
           }
 #pragma unroll
@@ -1160,22 +1224,24 @@ struct LdsTable {
         bool mine = full || row_at(r) < left;
         if constexpr (SUB) mine = mine && ((key_hash<KD>(k) >> sub_shift) & sub_mask) == sub;
         const bool hit = cur[r] == k && k != kMark && mine;
-        const int s = entry_of(home[r], hot);
+        const int s = entry_of(home[r], hot, L);
         bool miss = mine && !hit;
         if constexpr (kDig) {
           const uint32_t fb = __float_as_uint(b.x[r].fv), u = (fb << 1) + win_off;
           const bool in = u < win_span, zero = pass == 0 && b.x[r].fv == 0.0f;
-          const bool hot = hit && (in || zero);
-          if (hot) {
+          const bool done = hit && (in || zero);
+          if (done) {
             at_add<true>(&cnt[s], 1u);
-            if (in) add_window(s, fb, u);
+            if (in) add_window(s, fb, u, E);
           }
-          miss = mine && !hot && (in || u >= out_from);
+          miss = mine && !done && (in || u >= out_from);
+
         } else {
           if (hit) apply<G, true>(&cnt[s], &val[kVal ? s : 0], nullptr, nullptr, (int64_t)b.x[r].iv, b.x[r].fv);
         }
         rest = rest + rest + (miss ? 1u : 0u);
       }
+      bool far_row = false;  // a row of this lane was outside the windows
       while (rest) {
         const int r = R - 1 - __builtin_ctz(rest);
         rest &= rest - 1;
@@ -1189,12 +1255,12 @@ struct LdsTable {
         const uint32_t h = key_hash<KD>(x.k), fb = __float_as_uint(x.fv), u = (fb << 1) + win_off;
         const bool nonfinite = (fb << 1) >= 0xFF000000u;
         const bool in = !kDig || u < win_span || x.fv == 0.0f || nonfinite;  // an LDS slot can take it
-        const int slot = in ? slot_of(x.k, h, skip) : -1;
+        const int slot = in ? slot_of(x.k, h, skip, fw) : -1;
         if (slot >= 0) {
-          const int s = entry_of((uint32_t)slot, hot);
+          const int s = entry_of((uint32_t)slot, hot, L);
           if constexpr (kDig) {
             at_add<true>(&cnt[s], 1u);
-            if (u < win_span) add_window(s, fb, u);
+            if (u < win_span) add_window(s, fb, u, E);
             else if (nonfinite)
               at_or<true>(reinterpret_cast<int*>(&flags[slot >> 3]),
                           (__builtin_isnan(x.fv) ? 1 : (x.fv > 0 ? 2 : 4)) << (4 * (slot & 7)));
@@ -1203,19 +1269,28 @@ struct LdsTable {
           }
         } else {
           spilled = 1;
-          const int64_t g = global_slot(t_, (int64_t)x.k, h);
-          if (g >= 0) apply_global<G>(t_, g, (int64_t)x.iv, x.fv);
+          if constexpr (kLeaves)
+            if (!in) {
+              at_add<true>(&far_rows, 1u);
+              far_row = true;
+            }
+          const Table t = (kFlex && REP == 1 ? a_ : late_args()).t;
+          const int64_t g = global_slot(t, (int64_t)x.k, h);
+          if (g >= 0) apply_global<G>(t, g, (int64_t)x.iv, x.fv);
         }
       }
+      // (read only by a wave that has just met such a row: it waits for the wave's atomics)
+      return kLeaves && fw.single() && __any(far_row) && __builtin_amdgcn_readfirstlane((int)far_count()) != 0;
     };
     int64_t b = first;
     Batch A;
     if (b + TR <= last) {
+      bool leaves = false;
       load(A, b);
-      if constexpr (kHotLanes != 0 && !SUB) {
+      if constexpr (kHotLanes != 0 && SUB != 1) {
         uint32_t home[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) home[r] = home_of(key_hash<KD>(A.x[r].k), skip);
+        for (int r = 0; r < R; ++r) home[r] = home_of(key_hash<KD>(A.x[r].k), skip, fw);
         hot = find_hot<R>(home);
       }
       for (;;) {
@@ -1223,39 +1298,53 @@ struct LdsTable {
         const bool more = next + TR <= last;
         Batch B;
         load(B, more ? next : b);  // never behind a branch: the fold would wait for it (the last one is not used)
-        fold(A, b, true, 0);
+        const bool leave = fold(A, b, true, 0);
         cold = false;
         b = next;
-        if (!more) break;
+        leaves = kLeaves && leave;
+        if (!more || leaves) break;
         A = B;
       }
+      if (leaves) return b;
     }
     if (b < last) {  // the partial tile
       load_tail(A, b, (uint32_t)(last - b));
       fold(A, b, false, (uint32_t)(last - b));
     }
+    return last;
+  }
+  __device__ __forceinline__ bool far_count() const {
+    return __hip_atomic_load((const lds_u32*)&far_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > kFarRows;
+  }
+  // Rows of the workgroup are left for a table of all windows (between barriers).
+  // In a scalar register: all that depends on the windows is else kept per lane.
+  __device__ __forceinline__ bool left(const FloatWindows& z) const {
+    return kLeaves && z.single() && __builtin_amdgcn_readfirstlane((int)far_count()) != 0;
   }
 
-  // Entry e's windows as a whole number of 2^(32 d - 149), d = (win_base - 1) / 32.
-  __device__ __forceinline__ __int128 window_total(int e, uint32_t win_base) const {
+  // Window w of slot e.
+  __device__ __forceinline__ int64_t window_of(int e, int w, int E) const {
+    uint64_t v = 0;  // the copies' rows are at most kMaxTableRows in all
+    for (int r = 0; r < REP; ++r) v += (uint64_t)win[w * E + e * REP + r];
+    return (int64_t)v;
+  }
+  // Slot e's kWindows windows as a whole number of 2^(32 d - 149), d = (win_base - 1) / 32.
+  __device__ __forceinline__ __int128 window_total(int e, uint32_t win_base, int E) const {
     __int128 sum = 0;
-    for (int w = kWindows - 1; w >= 0; --w) {
-      uint64_t v = 0;  // the copies' rows are at most kMaxTableRows in all
-      for (int r = 0; r < REP; ++r) v += (uint64_t)win[w * E + e * REP + r];
-      sum = sum * (1 << kWinOctaves) + (int64_t)v;
-    }
+    for (int w = kWindows - 1; w >= 0; --w) sum = sum * (1 << kWinOctaves) + window_of(e, w, E);
     return sum * ((int64_t)1 << (((int)win_base - 1) & 31));
   }
 
   // The group of entry e, which holds all of its rows.
-  __device__ __forceinline__ agg_group group_of(int e, uint32_t win_base, int32_t is_avg) const {
+  __device__ __forceinline__ agg_group group_of(int e, uint32_t win_base, int32_t is_avg, const FloatWindows& z) const {
     static_assert(REP == 1, "one entry per slot");
+    const int L = slots(z), E = entries(z);
     int64_t v = 0, d[kDig ? kDigits : 1] = {};
     int32_t f = 0;
     if constexpr (kVal) v = val[e];
     if constexpr (kDig) {
       f = (int32_t)((flags[e >> 3] >> (4 * (e & 7))) & 7u);
-      const __int128 sum = window_total(e, win_base);
+      const __int128 sum = window_total(e, win_base, E);
       const int first = ((int)win_base - 1) >> 5;
 #pragma unroll
       for (int k = 0; k < kDigits; ++k) {  // digit 8 takes all there is from it on
@@ -1271,7 +1360,8 @@ struct LdsTable {
   // Lists the wave's slots with rows, 64 at a time: fn(slot, rank among the
   // wave's listed slots), or slot -1 for a lane with none.
   template <class F>
-  __device__ __forceinline__ void each_listed(int off, F fn) {
+  __device__ __forceinline__ void each_listed(int off, const FloatWindows& z, F fn) {
+    const int L = slots(z);
     const int lane = threadIdx.x & 63;
     volatile uint16_t* mine = list[threadIdx.x / 64];
     uint32_t pending = 0, done = 0;  // the same in all lanes
@@ -1296,7 +1386,8 @@ struct LdsTable {
   // Writes the table's groups straight to the caller's array: for a table that
   // holds all rows of its keys.  One range of the output per table, one
   // contiguous piece per 64 groups.
-  __device__ __forceinline__ void emit_all(const Args& a, uint32_t win_base) {
+  __device__ __forceinline__ void emit_all(const Args& a, uint32_t win_base, const FloatWindows& z) {
+    const int L = slots(z);
     const int w = threadIdx.x / 64;
     uint32_t mine = 0;
     for (int i = threadIdx.x; i < L; i += NT) mine += (uint32_t)__popcll(__ballot(cnt[i] != 0));
@@ -1313,16 +1404,17 @@ struct LdsTable {
     }
     __syncthreads();
     int64_t base = (int64_t)((uint64_t)emit_base[1] << 32 | emit_base[0]);
-    if (marker && threadIdx.x == NT - 1 && base < a.max_groups) a.out[base] = group_of(L, win_base, a.is_avg);
+    if (marker && threadIdx.x == NT - 1 && base < a.max_groups) a.out[base] = group_of(L, win_base, a.is_avg, z);
     base += marker ? 1 : 0;
     for (int v = 0; v < w; ++v) base += wave_groups[v];
-    each_listed(0, [&](int e, uint32_t rank) {
-      if (base + rank < a.max_groups) a.out[base + rank] = group_of(e, win_base, a.is_avg);
+    each_listed(0, z, [&](int e, uint32_t rank) {
+      if (base + rank < a.max_groups) a.out[base + rank] = group_of(e, win_base, a.is_avg, z);
     });
   }
 
   // Adds entry e (which has rows) to the global table.
-  __device__ __forceinline__ void flush_entry(const Table& t, int e, uint32_t win_base) {
+  __device__ __forceinline__ void flush_entry(const Table& t, int e, uint32_t win_base, const FloatWindows& z) {
+    const int L = slots(z);
     const KT k = e < L ? key[e] : kMark;
     uint64_t c = 0;
     for (int r = 0; r < REP; ++r) c += cnt[e * REP + r];
@@ -1344,11 +1436,24 @@ struct LdsTable {
     if constexpr (kDig) {
       const int32_t f = (int32_t)((flags[e >> 3] >> (4 * (e & 7))) & 7u);
       if (f) atomicOr(t.flags + g, f);
-      // The windows' total, a whole number of 2^(base - 150), as 32-bit digits
-      // from digit (base - 1) / 32 on: three unsigned ones and a signed top one.
-      // Digit 8 takes all there is from it on (floats end at 2^128, which
-      // keeps that below 2^53 over 2^31 rows).
-      add_digits(t, g, window_total(e, win_base), win_base);
+      // The windows, whole numbers of 2^(win_base - 150), 2^(win_base - 134), ..., as
+      // 32-bit digits from digit (win_base - 1) / 32 on: unsigned ones and a signed
+      // top one.  Digit 8 takes all there is from it on (floats end at 2^128,
+      // which keeps that below 2^53 over 2^31 rows).
+      const int E = entries(z), nw = windows(z);
+      unsigned long long* dig = reinterpret_cast<unsigned long long*>(t.dig + g * kDigits);
+      __int128 sum = 0;
+      int w = 0, shift = ((int)win_base - 1) & 31;
+#pragma unroll 1
+      for (int d = ((int)win_base - 1) >> 5;; ++d) {
+        for (; w < nw && shift < 32; ++w, shift += kWinOctaves) sum += (__int128)window_of(e, w, E) * ((int64_t)1 << shift);
+        shift -= 32;
+        const bool top = d == kDigits - 1 || (w == nw && sum == (int32_t)sum);
+        const int64_t v = top ? (int64_t)sum : (int64_t)(uint32_t)sum;
+        if (v) atomicAdd(dig + d, (unsigned long long)v);
+        if (top) break;
+        sum >>= 32;
+      }
     }
   }
 
@@ -1371,11 +1476,12 @@ struct LdsTable {
   // Writes the table to its region: the sections' starts, then the records by
   // section (a counting sort).  False, with nothing written but the empty
   // sections, if the region is too small: more keys than the plan allows.
-  __device__ __forceinline__ bool dump(uint32_t* region, int most) {
+  __device__ __forceinline__ bool dump(uint32_t* region, int most, const FloatWindows& z) {
     static_assert(sizeof(list) >= 2 * kSections * 4, "the counters lie over the list");
     uint32_t* count = reinterpret_cast<uint32_t*>(&list[0][0]);
     if (threadIdx.x <= kSections) count[threadIdx.x] = 0;
     __syncthreads();
+    const int L = slots(z), E = entries(z);
     auto section_of = [&](int e) { return key_hash<KD>(e < L ? key[e] : kMark) >> (32 - kSectionBits); };
     for (int e = threadIdx.x; e <= L; e += NT)
       if (cnt[e] != 0) at_add<true>(&count[section_of(e)], 1u);
@@ -1426,7 +1532,8 @@ struct LdsTable {
     const KT k = kKeyWords == 2 ? (KT)get64(r) : (KT)(int32_t)r[0];
     const uint32_t rows = r[kKeyWords], h = key_hash<KD>(k);
     const uint32_t* x = r + kKeyWords + 1;
-    const int s = slot_of(k, h, skip);
+    const FloatWindows z;
+    const int E = entries(z), s = slot_of(k, h, skip, z);
     if (s >= 0) {
       at_add<true>(&cnt[s], rows);
       if constexpr (G == G_SUM_INT)
@@ -1475,7 +1582,8 @@ struct LdsTable {
   // Not where many workgroups have the same keys (direct path): more of them
   // would claim a key at the same moment (6M rows, 2000 groups, 256 workgroups:
   // COUNT 56.5 -> 72.4 us; 31 workgroups 54.9 -> 34.6).
-  __device__ __forceinline__ void flush(const Table& t, uint32_t win_base, bool listed) {
+  __device__ __forceinline__ void flush(const Table& t, uint32_t win_base, bool listed, const FloatWindows& z) {
+    const int L = slots(z);
     // Every workgroup's table holds its keys in about the same slots (same
     // hash), so flushing all tables in slot order would have every workgroup
     // update the same global slots at the same moment, and device-scope
@@ -1484,19 +1592,19 @@ struct LdsTable {
     // the other cases within noise).
     const int off = (int)(blockIdx.x * 2654435761u >> 16);
     if (listed) {
-      each_listed(off & (L - 1), [&](int e, uint32_t) { flush_entry(t, e, win_base); });
+      each_listed(off & (L - 1), z, [&](int e, uint32_t) { flush_entry(t, e, win_base, z); });
     } else {
       for (int i = threadIdx.x; i < L; i += NT) {
         const int e = (i + off) & (L - 1);
         uint32_t c = 0;
         for (int r = 0; r < REP; ++r) c |= cnt[e * REP + r];
-        if (c != 0) flush_entry(t, e, win_base);
+        if (c != 0) flush_entry(t, e, win_base, z);
       }
     }
     if (threadIdx.x == NT - 1) {  // slot L
       uint32_t c = 0;
       for (int r = 0; r < REP; ++r) c |= cnt[L * REP + r];
-      if (c != 0) flush_entry(t, L, win_base);
+      if (c != 0) flush_entry(t, L, win_base, z);
     }
   }
 };
@@ -1516,17 +1624,48 @@ constexpr int kFewGroups = 32;
 constexpr int kFewCopies = 8;
 constexpr int kFewSlots = 256;
 
-// Where a launch's float-sum windows go, from one row per thread, spread evenly
-// over the launch's n rows (word `at` of every `stride`): the sampled
+// The tables for the exponents emin..emax and `groups` keys a table (FEW: the few-groups
+// table).  Slots enough for the keys at up to 5/8 of them, else passes by the keys'
+// hash.  MANY (partitions, and the direct path's two passes): or, if those are not
+// more, passes by exponent of the full-size table, whose rows need no other test (10^6
+// rows and groups, 60 exponents 236 us, by hash 276; with fewer groups the flushes
+// cost more than the test: 10^6 rows, 2000 groups 118 us by exponent, 93 by hash).
+template <int KD, bool FEW, bool MANY>
+__device__ __forceinline__ FloatWindows place_windows(int emin, int emax, int64_t groups) {
+  const int n = emax - emin + 1;
+  FloatWindows f;
+  const int least = (n + kWinOctaves - 1) / kWinOctaves, mid = mid_windows_of(KD);
+  if (FEW) {
+    f.nw = least <= kWindows ? kWindows : kFewWindows;
+  } else if (least > kWindows) {
+    f.nw = least <= mid ? mid : 2 * mid;
+    f.lg = __builtin_ctz(least <= mid ? kMidSlots : kAllSlots);
+    while (groups >> f.sub_bits > (5 << f.lg) / 8) ++f.sub_bits;
+    if (MANY && f.sub_bits && (least + kWindows - 1) / kWindows <= (least + f.nw - 1) / f.nw << f.sub_bits) {
+      f.nw = kWindows;
+      f.sub_bits = 0;
+    }
+  }
+  const int span = f.nw * kWinOctaves;
+  f.passes = (n + span - 1) / span;
+  f.first = std::max(1, emax + std::min((f.passes * span - n) / 2, 8) - f.passes * span + 1);
+  return f;
+}
+
+// Where a launch's float-sum windows go, from one row of each of blockDim.x equal
+// parts of the launch's n rows (word `at` of every `stride`): the sampled
 // exponents, with most of the slack below them (sums of small parts) and up to
-// 2^8 of room above.  More than kWinSpan exponents take several passes over the
-// rows; a row outside all of them goes to the global table.  Every workgroup
-// reads the same rows and gets the same answer.  (1024 rows:
+// 2^8 of room above.  The row's place in its part differs from part to part, so that
+// no period of the column's shows it one kind of row only.  Every workgroup reads
+// the same rows and gets the same answer.  (1024 rows:
 // a sample is bound by page-table misses, 4096 rows took 13 to 20 us at 2^28;
 // reduced by shuffles, 2 us: LDS min / max of one address by every lane took 8.)
-__device__ __forceinline__ FloatWindows sample_windows(const uint32_t* words, int stride, int at, int64_t n) {
+template <int KD, bool FEW, bool MANY>
+__device__ __forceinline__ FloatWindows sample_windows(const uint32_t* words, int stride, int at, int64_t n, int64_t groups) {
   __shared__ int range[2][16];
-  const int64_t row = (int64_t)((uint64_t)n * threadIdx.x / blockDim.x);
+  const int64_t part = (int64_t)((uint64_t)n * threadIdx.x / blockDim.x);
+  const uint32_t size = (uint32_t)((uint64_t)n / blockDim.x);  // n <= 2^31
+  const int64_t row = part + (int64_t)__umulhi(next_probe(threadIdx.x), size);
   const int e = (int)((words[row * stride + at] >> 23) & 0xFFu);
   const bool placed = e != 0 && e != 255;  // zeros, subnormals and non-finite rows do not place a window
   int emin = placed ? e : 255, emax = placed ? e : 0;
@@ -1543,13 +1682,27 @@ __device__ __forceinline__ FloatWindows sample_windows(const uint32_t* words, in
     emin = std::min(emin, range[0][w]);
     emax = std::max(emax, range[1][w]);
   }
+  // every wave has the same two numbers: in scalar registers from here on
+  emin = __builtin_amdgcn_readfirstlane(emin);
+  emax = __builtin_amdgcn_readfirstlane(emax);
   if (emin > emax) emin = emax = 127;
-  FloatWindows f;
-  f.passes = (emax - emin + kWinSpan) / kWinSpan;
-  const int slack = f.passes * kWinSpan - (emax - emin + 1);
-  f.first = std::max(1, emax + std::min(slack / 2, 8) - f.passes * kWinSpan + 1);
-  return f;
+  return place_windows<KD, FEW, MANY>(emin, emax, groups);
 }
+
+// An aggregation kernel's tables, in the same LDS: one of full size, and for a
+// float sum those of fewer slots and more windows (the table of few groups is both:
+// its windows' number is all that changes).  The full-size one's shape is known to
+// the compiler, so that columns of few exponents pay nothing for the others (with
+// one table for all, 2^28 rows, 300 groups 376 -> 433 us).
+template <int KD>
+constexpr int flex_words() { return 2 * mid_windows_of(KD) * (kAllSlots + 1); }
+template <int G, int KD, bool FEW, bool HOT>
+union AggTables {
+  static_assert(mid_windows_of(KD) * (kMidSlots + 1) <= flex_words<KD>(), "the other shape needs no more");
+  LdsTable<G, KD, FEW ? kFewSlots : lds_slots<G, KD>(), kDirectThreads, FEW ? kFewCopies : 1, HOT,
+           FEW && G == G_SUM_F32 ? kFewWindows*(kFewSlots + 1) * kFewCopies : 0> full;
+  LdsTable<G, KD, kMidSlots, kDirectThreads, 1, false, G == G_SUM_F32 && !FEW ? flex_words<KD>() : 0> flex;
+};
 
 // ---- emission: the global table's groups to the caller's array ----
 
@@ -1638,6 +1791,53 @@ __device__ __forceinline__ void finish_emission(const Args& a) {
   __hip_atomic_store(&a.t.state[4], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Folds a workgroup's rows from `from` on (each wave its own) of the plan's pass
+// `sub` into tables of more windows.  A function of its own, so that its registers
+// are not the fold's of the full-size table (within the kernels: 41 registers
+// spilled instead of 7, 2^28 rows, 300 groups 353 -> 373 us, 1e5 rows 22 -> 25; as it
+// is 353 -> 368 and 22 -> 23).  A function's arguments come in vector registers;
+// these are the same in all lanes.
+typedef __attribute__((address_space(3))) char lds_char;
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int64_t uniform(int64_t v) {
+  return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 |
+                   (uint32_t)__builtin_amdgcn_readfirstlane((int)v));
+}
+template <int VD, bool ROWS, class Tab>
+__device__ __attribute__((noinline)) void fold_flex(lds_char* space, const Args* ap, int first, int passes, int nw, int lg,
+                                                    int fsub, int64_t from, int64_t last, int64_t step,
+                                                    int sub) {
+  Tab& tab = *(Tab*)space;
+  typedef __attribute__((address_space(4))) const Args kernarg;
+  const Args& a = *(const Args*)(kernarg*)uniform((int64_t)ap);  // the kernel's own, scalar loads
+  FloatWindows fw;
+  fw.first = uniform(first);
+  fw.passes = uniform(passes);
+  fw.nw = uniform(nw);
+  fw.lg = uniform(lg);
+  fw.sub_bits = uniform(fsub);
+  from = uniform(from);
+  last = uniform(last);
+  step = uniform(step);
+  sub = uniform(sub);
+  const int bits = ROWS ? a.pt.bits : 0, sub_bits = a.pt.sub_bits;
+  const void* keys = ROWS ? a.pt.pk : a.keys;
+  const void* vals = ROWS ? a.pt.pv : a.vals;
+  const int pass_bits = sub_bits + fw.sub_bits;
+#pragma unroll 1
+  for (uint32_t i = 0; i < (uint32_t)fw.passes << fw.sub_bits; ++i) {
+    const int pass = (int)(i >> fw.sub_bits);
+    tab.clear((uint32_t)(bits + pass_bits), fw);
+    __syncthreads();
+    tab.template fold_rows<VD, ROWS, 2>(a, keys, vals, from, last, step, (uint32_t)(bits + pass_bits),
+                                        pass_bits ? (uint32_t)(32 - bits - pass_bits) : 0u, (1u << pass_bits) - 1u,
+                                        (uint32_t)sub << fw.sub_bits | (i & ((1u << fw.sub_bits) - 1u)), fw, pass);
+    __syncthreads();
+    tab.flush(a.t, fw.base(pass), ROWS || gridDim.x <= 64, fw);
+    __syncthreads();
+  }
+}
+
 // Direct path: every workgroup sweeps its share of the rows' tiles into one
 // LDS table, in 2^sub_bits passes (each taking the keys of one sub-partition:
 // the top bits of the key's hash) when the groups need more than one table.
@@ -1650,42 +1850,59 @@ __device__ __forceinline__ void finish_emission(const Args& a) {
 template <int KD, int VD, int G, bool FEW, bool SUB>
 __global__ void __launch_bounds__(kDirectThreads)
 gb_aggregate_kernel(Args a) {
-  
-  __shared__ LdsTable<G, KD, FEW ? kFewSlots : lds_slots<G, KD>(), kDirectThreads, FEW ? kFewCopies : 1> tab;
-  constexpr int TR = decltype(tab)::template tile_rows_of<VD>() * kDirectThreads;
+  __shared__ AggTables<G, KD, FEW, false> tables;
+  auto& tab = tables.full;
+  constexpr int TR = decltype(tables.full)::template tile_rows_of<VD>() * kDirectThreads;
+  const int64_t step = (int64_t)gridDim.x * TR;
   const uint32_t sub_mask = (1u << a.pt.sub_bits) - 1u;
   const uint32_t sub_shift = a.pt.sub_bits ? (uint32_t)(32 - a.pt.sub_bits) : 0u;
   FloatWindows fw;
-  if constexpr (G == G_SUM_F32) fw = sample_windows(static_cast<const uint32_t*>(a.vals), 1, 0, a.n);
+  if constexpr (G == G_SUM_F32) {
+    fw = sample_windows<KD, FEW, SUB>(static_cast<const uint32_t*>(a.vals), 1, 0, a.n, a.max_groups >> a.pt.sub_bits);
+    // (-1: no workgroup writes its table out)
+    if (a.dumps && blockIdx.x == 0 && threadIdx.x == 0) a.t.state[6] = fw.single() ? (int32_t)fw.base(0) : -1;
+  }
   for (uint32_t sub = 0; sub <= sub_mask; ++sub) {
-    for (int pass = 0; pass < fw.passes; ++pass) {
-      bool written = false;
-      tab.clear((uint32_t)a.pt.sub_bits);
+    int64_t from = (int64_t)blockIdx.x * TR;
+    bool dumped = false, global = !fw.narrow();  // the table was written out; rows are in the global table
+    for (int pass = 0; pass < (FEW || fw.narrow() ? fw.passes : 0); ++pass) {
+      tab.clear((uint32_t)a.pt.sub_bits, fw);
       __syncthreads();
-      tab.template fold_rows<VD, false, SUB>(a.t, a.keys, a.vals, (int64_t)blockIdx.x * TR, a.n,
-                                             (int64_t)gridDim.x * TR, (uint32_t)a.pt.sub_bits, sub_shift, sub_mask, sub,
-                                             fw, pass);
+      const int64_t next = tab.template fold_rows<VD, false, SUB>(a, a.keys, a.vals, from, a.n, step, (uint32_t)a.pt.sub_bits,
+                                                                  sub_shift, sub_mask, sub, fw, pass);
       __syncthreads();
+      const bool left = tab.left(fw);
+      const Args& b = late_args();
       if constexpr (!FEW)
-        if (a.dumps) {
-          // one region per workgroup and hash half; its rows may be in the global
-          // table as well (spilled), and several windows' passes all are
-          uint32_t* region = a.dump + ((int64_t)blockIdx.x * (sub_mask + 1) + sub) * dump_region_of(G, KD, a.dump_max);
-          const bool dumped = fw.passes == 1 && tab.dump(region, a.dump_max);
-          if (fw.passes > 1 && threadIdx.x <= kSections) region[threadIdx.x] = 0;
-          if (threadIdx.x == 0) {
-            if (!dumped || tab.spilled) decltype(tab)::mark_global(a.t, 5);
-            if (blockIdx.x == 0) a.t.state[6] = (int32_t)fw.base(0);
-          }
-          if (dumped) written = true;
-        }
-      if (!written) tab.flush(a.t, fw.base(pass), gridDim.x <= 64);
+        if (b.dumps && !left && fw.single())  // its region; its rows may be in the global table as well (spilled)
+          dumped = tab.dump(b.dump + ((int64_t)blockIdx.x * (sub_mask + 1) + sub) * dump_region_of(G, KD, b.dump_max),
+                            b.dump_max, fw);
+      global = !dumped || tab.spilled;
+      if (!dumped) tab.flush(b.t, fw.base(pass), gridDim.x <= 64, fw);
       __syncthreads();
+      if constexpr (G == G_SUM_F32)
+        if (left) {  // the rows that are left, in tables of all windows
+          fw = place_windows<KD, FEW, SUB>(1, 254, a.max_groups >> a.pt.sub_bits);
+          from = next;
+          pass = -1;
+        }
+    }
+    if constexpr (!FEW) {
+      const Args& b = late_args();
+      if (b.dumps) {  // one region per workgroup and hash half
+        uint32_t* region = b.dump + ((int64_t)blockIdx.x * (sub_mask + 1) + sub) * dump_region_of(G, KD, b.dump_max);
+        if (!dumped && threadIdx.x <= kSections) region[threadIdx.x] = 0;
+        if (threadIdx.x == 0 && global) decltype(tables.full)::mark_global(b.t, 5);
+      }
+      if constexpr (G == G_SUM_F32)
+        if (!fw.narrow())
+          fold_flex<VD, false, decltype(tables.flex)>((lds_char*)&tables, &b, fw.first, fw.passes, fw.nw, fw.lg, fw.sub_bits, from, b.n, step, (int)sub);
     }
   }
-  if (a.emit && last_to_finish(reinterpret_cast<uint32_t*>(a.t.state + 4))) {
-    emit_slots<G, true, kDirectThreads>(a, 0, a.t.cap + 1);
-    finish_emission(a);
+  const Args& b = late_args();
+  if (b.emit && last_to_finish(reinterpret_cast<uint32_t*>(b.t.state + 4))) {
+    emit_slots<G, true, kDirectThreads>(b, 0, b.t.cap + 1);
+    finish_emission(b);
   }
 }
 
@@ -1699,12 +1916,15 @@ gb_aggregate_kernel(Args a) {
 // the key's hash) and flushing the table after it.
 template <int KD, int VD, int G, bool SUB>
 __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a) {
-  __shared__ LdsTable<G, KD, lds_slots<G, KD>(), kPartThreads, 1, !SUB> tab;
-  constexpr int TR = decltype(tab)::template tile_rows_of<VD>() * kPartThreads;
+  static_assert(kPartThreads == kDirectThreads, "one AggTable");
+  __shared__ AggTables<G, KD, false, !SUB> tables;
+  auto& tab = tables.full;
+  constexpr int TR = decltype(tables.full)::template tile_rows_of<VD>() * kPartThreads;
+  const int64_t groups = a.max_groups >> (a.pt.bits + a.pt.sub_bits);  // keys of a table
   FloatWindows fw;
   if constexpr (G == G_SUM_F32) {
     using SR = StagedRow<KD, AGG_F32>;
-    fw = sample_windows(static_cast<const uint32_t*>(a.pt.pk), SR::KW + SR::VW, SR::KW, a.n);
+    fw = sample_windows<KD, false, true>(static_cast<const uint32_t*>(a.pt.pk), SR::KW + SR::VW, SR::KW, a.n, groups);
   }
   const int P = 1 << a.pt.bits;
   // The workgroup's rows: an equal share.  Where there are as many partitions as
@@ -1739,21 +1959,32 @@ __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a)
   while (r < r1) {
     while ((int64_t)a.pt.start[p + 1] <= r) ++p;  // skip partitions that end before r
     const int64_t seg_end = std::min<int64_t>(r1, (int64_t)a.pt.start[p + 1]);
-    // the workgroup has all rows of the partition's keys, folded in one pass
-    const bool whole =
-        a.whole && fw.passes == 1 && r == (int64_t)a.pt.start[p] && seg_end == (int64_t)a.pt.start[p + 1];
+    // the workgroup has all rows of the partition's keys
+    const bool whole = a.whole && r == (int64_t)a.pt.start[p] && seg_end == (int64_t)a.pt.start[p + 1];
     for (uint32_t sub = 0; sub <= sub_mask; ++sub) {
-      for (int pass = 0; pass < fw.passes; ++pass) {
-        tab.clear((uint32_t)(a.pt.bits + a.pt.sub_bits));
+      int64_t from = r;
+      for (int pass = 0; pass < (fw.narrow() ? fw.passes : 0); ++pass) {
+        tab.clear((uint32_t)(a.pt.bits + a.pt.sub_bits), fw);
         __syncthreads();
-        tab.template fold_rows<VD, true, SUB>(a.t, a.pt.pk, a.pt.pv, r, seg_end, TR,
-                                              (uint32_t)(a.pt.bits + a.pt.sub_bits), sub_shift, sub_mask, sub, fw, pass);
+        const int64_t next = tab.template fold_rows<VD, true, SUB>(a, a.pt.pk, a.pt.pv, from, seg_end, TR,
+                                                                   (uint32_t)(a.pt.bits + a.pt.sub_bits), sub_shift,
+                                                                   sub_mask, sub, fw, pass);
         __syncthreads();
-        tab.merge_hot();
-        if (whole && tab.spilled == 0) tab.emit_all(a, fw.base(pass));
-        else tab.flush(a.t, fw.base(pass), true);
+        const bool left = tab.left(fw);
+        tab.merge_hot(fw);
+        if (whole && fw.single() && tab.spilled == 0) tab.emit_all(late_args(), fw.base(0), fw);
+        else tab.flush(late_args().t, fw.base(pass), true, fw);
         __syncthreads();
+        if constexpr (G == G_SUM_F32)
+          if (left) {  // the rows that are left, in tables of all windows
+            fw = place_windows<KD, false, true>(1, 254, groups);
+            from = next;
+            pass = -1;
+          }
       }
+      if constexpr (G == G_SUM_F32)
+        if (!fw.narrow())
+          fold_flex<VD, true, decltype(tables.flex)>((lds_char*)&tables, &late_args(), fw.first, fw.passes, fw.nw, fw.lg, fw.sub_bits, from, seg_end, TR, (int)sub);
     }
     r = seg_end;
   }
@@ -1770,6 +2001,16 @@ __global__ void __launch_bounds__(kDirectThreads) gb_merge_kernel(Args a) {
   __shared__ LdsTable<G, KD, kMergeSlots, kDirectThreads> tab;
   __shared__ uint32_t first[kMergeMaxWg], upto[kMergeMaxWg];  // a region's records of the section; their running total
   __shared__ uint32_t wave_sum[kDirectThreads / 64];
+  if constexpr (G == G_SUM_F32)
+    if (a.t.state[6] < 0) {  // tables of more windows, all flushed: the launch emits the global table
+      const int64_t slots = a.t.cap + 1, per = ceil_div_dev(slots, gridDim.x);
+      emit_slots<G, false, kDirectThreads>(a, blockIdx.x * per, std::min<int64_t>((blockIdx.x + 1) * per, slots));
+      if (!last_to_finish(reinterpret_cast<uint32_t*>(a.t.state + 4))) return;
+      if (threadIdx.x == 0) __hip_atomic_store(&a.t.state[5], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      finish_emission(a);
+      return;
+    }
+  const FloatWindows fw;  // (the merge's table has kWindows)
   const uint32_t section = blockIdx.x;
   const uint32_t subs = 1u << a.pt.sub_bits, sub = section >> (kSectionBits - a.pt.sub_bits);
   const int64_t region = dump_region_of(G, KD, a.dump_max);
@@ -1780,7 +2021,7 @@ __global__ void __launch_bounds__(kDirectThreads) gb_merge_kernel(Args a) {
     first[tid] = mine[section];
     n = mine[section + 1] - first[tid];
   }
-  tab.clear((uint32_t)kSectionBits);
+  tab.clear((uint32_t)kSectionBits, fw);
   uint32_t incl = n;
   for (int off = 1; off < 64; off <<= 1) {
     const uint32_t y = __shfl_up(incl, off, 64);
@@ -1808,8 +2049,8 @@ __global__ void __launch_bounds__(kDirectThreads) gb_merge_kernel(Args a) {
     tab.add_record(a.t, r, (uint32_t)kSectionBits, win_base);
   }
   __syncthreads();
-  if (global) tab.flush(a.t, win_base, true);
-  else tab.emit_all(a, win_base);
+  if (global) tab.flush(a.t, win_base, true, fw);
+  else tab.emit_all(a, win_base, fw);
   if (!last_to_finish(reinterpret_cast<uint32_t*>(a.t.state + 4))) return;
   if (global || __hip_atomic_load(&a.t.state[7], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
     emit_slots<G, true, kDirectThreads>(a, 0, a.t.cap + 1);
@@ -1856,7 +2097,7 @@ int gop_of(int32_t val_dtype, int32_t op) {
 }
 
 // PATH: 0 direct, 1 partitioned, 2 direct with few groups (accumulator copies),
-// 3 direct in sub-partition passes (no COUNT: it partitions instead), 4
+// 3 direct in sub-partition passes (no COUNT and no float SUM: they partition instead), 4
 // partitioned in sub-partition passes.  Plans without passes take kernels whose fold has no
 // per-row pass test.
 template <int KD, int VD, int PATH>
@@ -1866,8 +2107,9 @@ const void* agg_row(int g) {
        ? reinterpret_cast<const void*>(&gb_aggregate_part_kernel<KD, VD, GG, PATH == 4>)                  \
        : reinterpret_cast<const void*>(&gb_aggregate_kernel<KD, VD, GG, PATH == 2, PATH == 3>))
   if constexpr (VD == AGG_F32) {
+    if constexpr (PATH != 3 || KD == AGG_I64)
+      if (g == G_SUM_F32) return GB_AGG(G_SUM_F32);
     switch (g) {
-      case G_SUM_F32: return GB_AGG(G_SUM_F32);
       case G_MIN_F32: return GB_AGG(G_MIN_F32);
       case G_MAX_F32: return GB_AGG(G_MAX_F32);
       default: return nullptr;
@@ -2030,9 +2272,12 @@ int agg_groupby_plan(agg_groupby_t* out, int32_t key_dtype, int32_t val_dtype, i
   // pass costs about one direct run, so four would lose.)
   int bits = 0, direct_sub_bits = 0;
   const int64_t half_table = lds_slots_of(g, key_dtype) / 2;
-  // Float sums of fewer rows partition too: 4096 groups, 3e7 rows 335 us in two
-  // passes, 239 partitioned; 5e5 rows 61 and 53; 2^28 rows 1358 and 1594.
-  const bool two_passes = g != G_COUNT && !(g == G_SUM_F32 && max_n < kTwoPassFloatRows);
+  // Float sums of int32 keys, or of fewer rows, partition too: 4096 groups, 3e7 rows
+  // 335 us in two passes, 239 partitioned; 5e5 rows 61 and 53; 2^28 rows, int32 keys,
+  // 1411 and 1640, but with 60 exponents 2311 and 1660.  int64 keys, 2^28 rows, whose
+  // staged rows are 12 bytes: 1480 in two passes, 2490 partitioned; with 60 exponents
+  // 2600 and 2480 (and 5670 and 3950 with 200).
+  const bool two_passes = g != G_COUNT && !(g == G_SUM_F32 && (key_dtype == AGG_I32 || max_n < kTwoPassFloatRows));
   if (max_groups > half_table && max_groups <= 2 * half_table && two_passes) {
     direct_sub_bits = 1;
   } else if (max_groups > half_table) {
