@@ -161,10 +161,11 @@ int agg_default_tune(int32_t dtype, int32_t op, int32_t prec, int64_t n, int32_t
 
 /* Create a plan for columns of up to max_n items.  Allocates the device
  * workspace (segment partials, filtered-run counts and two zeroed words,
- * 128 KiB + 256 B; plus
- * staging_depth * chunk_bytes of device staging, a copy stream and events
- * for PINNED_HOST).  tune == NULL: agg_default_tune for max_n; where that is
- * the built-in table, each run takes its entry for the run's own size. */
+ * 128 KiB + 256 B; for PINNED_HOST also staging_depth * chunk_bytes of device
+ * staging, a copy stream and events, or 8 MiB of it where the runs read the
+ * column over the link and only one that the device cannot address would be
+ * staged).  tune == NULL: agg_default_tune for max_n; where that is the built-in
+ * table, each run takes its entry for the run's own size. */
 int agg_plan(agg_plan_t* out, int32_t dtype, int32_t op, int32_t prec, int64_t max_n,
              int32_t src, const agg_tune* tune);
 
@@ -201,7 +202,9 @@ int agg_run(agg_plan_t plan, const void* col, int64_t n, agg_result* out, void* 
 int agg_run_noalloc(int32_t dtype, int32_t op, int32_t prec, int32_t src, const void* col, int64_t n,
                     agg_result* out, void* stream);
 
-/* The canonical shape and launch parameters the plan uses for n items. */
+/* The canonical shape and launch parameters the plan uses for n items
+ * (PINNED_HOST without given or cached parameters: those of the scan that reads
+ * the column over the link, which stages nothing). */
 int agg_plan_info(agg_plan_t plan, int64_t n, agg_shape* shape, agg_tune* tune);
 
 int agg_plan_destroy(agg_plan_t plan);

@@ -360,13 +360,23 @@ void batch_release(agg_batch_s* b) {
 
 int alloc_device(void** p, size_t bytes) { return device_alloc(p, bytes); }
 
+// Page-locked columns without given or cached parameters: the scan reads them
+// over the link itself.
+bool reads_link(const agg_plan_s* p) { return p->src == AGG_SRC_PINNED_HOST && p->tune_builtin; }
+
 // The launch parameters of a run over `bytes` bytes of the plan's column: its
-// own, or the built-in ones of that size (the staging ring's stay the plan's).
+// own, or the built-in ones of that size and of the way that the run takes.
 agg_tune plan_tune(const agg_plan_s* p, int64_t bytes) {
   agg_tune t = p->tune;
-  if (p->tune_builtin) builtin_tune_for(p->kind, p->src, bytes, &t);
+  if (p->tune_builtin) builtin_tune_for(p->kind, reads_link(p) ? AGG_SRC_ZEROCOPY : p->src, bytes, &t);
   return t;
 }
+
+// The staging ring of a plan whose runs read the link: only a column that the
+// device cannot address goes through it (none that hipHostMalloc or torch gave),
+// so it is small instead of three chunks of 64 MiB.
+constexpr int kSpareDepth = 2;
+constexpr int64_t kSpareChunk = 4ll << 20;
 
 #define RET_IF(x)            \
   do {                       \
@@ -388,8 +398,8 @@ int plan_create(agg_plan_s* p) {
   if (p->src == AGG_SRC_PINNED_HOST) {
     agg_shape s;
     shape_of(p->dtype, p->max_n, &s);
-    p->depth = p->tune.staging_depth;
-    p->stage_bytes = std::max<int64_t>(p->tune.chunk_bytes, s.seg_bytes);
+    p->depth = reads_link(p) ? kSpareDepth : p->tune.staging_depth;
+    p->stage_bytes = std::max<int64_t>(reads_link(p) ? kSpareChunk : p->tune.chunk_bytes, s.seg_bytes);
     p->stage_bytes = std::min<int64_t>(p->stage_bytes, std::max<int64_t>(s.nseg, 1) * s.seg_bytes);
     for (int i = 0; i < p->depth; ++i) {
       RET_IF(alloc_device(reinterpret_cast<void**>(&p->stage[i]), (size_t)p->stage_bytes));
@@ -628,16 +638,13 @@ int agg_run(agg_plan_t p, const void* col, int64_t n, agg_result* out, void* str
   // copies to wait for: int32 SUM 256 MiB 4834 -> 4675 us, 4 MiB 121 -> 82,
   // float 1 MiB 66 -> 25.
   void* mapped = nullptr;
-  if (p->tune_builtin) {
+  if (reads_link(p)) {
     if (hipHostGetDevicePointer(&mapped, const_cast<void*>(col), 0) != hipSuccess) {
       (void)hipGetLastError();
       mapped = nullptr;
     }
-    if (mapped) {
-      agg_tune z;
-      builtin_tune_for(p->kind, AGG_SRC_ZEROCOPY, bytes, &z);
-      return enqueue_resident(p->kind, p->dtype, p->op, p->prec, z, cu, mapped, n, out, p->part, p->done, stream);
-    }
+    if (mapped)
+      return enqueue_resident(p->kind, p->dtype, p->op, p->prec, t, cu, mapped, n, out, p->part, p->done, stream);
   }
 
   // Otherwise: copy chunks of whole segments into the staging ring on the
