@@ -152,8 +152,8 @@ int agg_canonical_shape(int32_t dtype, int64_t n, agg_shape* out);
 
 /* Default launch parameters for (dtype, op, prec, n, src): the tuning-cache
  * entry of the nearest size bucket for that fold kind and source (filled by
- * agg_autotune or agg_tune_load), else the built-in table measured on
- * MI355X. */
+ * agg_autotune or agg_tune_load) if it is at most one bucket away, else the
+ * built-in table measured on MI355X. */
 int agg_default_tune(int32_t dtype, int32_t op, int32_t prec, int64_t n, int32_t src,
                      agg_tune* out);
 
@@ -165,7 +165,8 @@ int agg_default_tune(int32_t dtype, int32_t op, int32_t prec, int64_t n, int32_t
  * staging, a copy stream and events, or 8 MiB of it where the runs read the
  * column over the link and only one that the device cannot address would be
  * staged).  tune == NULL: agg_default_tune for max_n; where that is the built-in
- * table, each run takes its entry for the run's own size. */
+ * table, each run takes its entry for the run's own size, and so does a run
+ * whose size is more than one bucket away from that of a cached entry's plan. */
 int agg_plan(agg_plan_t* out, int32_t dtype, int32_t op, int32_t prec, int64_t max_n,
              int32_t src, const agg_tune* tune);
 
@@ -240,9 +241,12 @@ int agg_batch_autotune(agg_batch_t batch, void* stream, agg_tune* best, double* 
 /* Time a fixed set of candidate launch parameters for (dtype, op, prec) on
  * the caller's column col[0..n) in memory of kind `src` (device: waves per
  * block x blocks per CU x loads in flight, then temporal vs non-temporal
- * loads; pinned host: staging chunk x depth), on `stream`.  The fastest goes
- * into the process-wide tuning cache under (fold kind, src, size bucket
- * ceil(log2(n * width))) and is returned with its GB/s.  Creates and destroys
+ * loads; pinned host: staging chunk x depth), the built-in parameters among
+ * them, on `stream`.  The fastest goes into the process-wide tuning cache under
+ * (fold kind, src, size bucket ceil(log2(n * width))) and is returned with its
+ * GB/s.  Pinned host: if reading the column over the link is faster than
+ * staging, plans without parameters go on reading it; best_gbs is that rate
+ * then, and *best the fastest staging parameters.  Creates and destroys
  * temporary plans (so it allocates) and synchronises `stream`. */
 int agg_autotune(int32_t dtype, int32_t op, int32_t prec, const void* col, int64_t n, int32_t src,
                  void* stream, agg_tune* best, double* best_gbs);

@@ -318,7 +318,8 @@ def make_tune(**kw) -> Tune:
 
 def autotune(dtype, op, col, n: Optional[int] = None, prec="neumaier", src="device", stream=None):
     """Time candidate launch parameters on `col`; the fastest enters the tuning
-    cache (used by later plans without explicit parameters).  Returns (Tune, GB/s)."""
+    cache (used by later plans without explicit parameters, for sizes near the
+    tuned one).  Returns (Tune, GB/s)."""
     if isinstance(col, int):
         ptr, nn = col, int(n)
     else:

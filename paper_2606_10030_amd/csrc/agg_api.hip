@@ -360,15 +360,21 @@ void batch_release(agg_batch_s* b) {
 
 int alloc_device(void** p, size_t bytes) { return device_alloc(p, bytes); }
 
+// Whether a run over `bytes` bytes takes built-in parameters: the plan was given
+// none, and the cache has none for that size.
+bool runs_builtin(const agg_plan_s* p, int64_t bytes) {
+  return p->tune_builtin || (!p->tune_given && !tune_applies(p->max_n * p->width, bytes));
+}
+
 // Page-locked columns without given or cached parameters: the scan reads them
 // over the link itself.
-bool reads_link(const agg_plan_s* p) { return p->src == AGG_SRC_PINNED_HOST && p->tune_builtin; }
+bool reads_link(const agg_plan_s* p, int64_t bytes) { return p->src == AGG_SRC_PINNED_HOST && runs_builtin(p, bytes); }
 
 // The launch parameters of a run over `bytes` bytes of the plan's column: its
 // own, or the built-in ones of that size and of the way that the run takes.
 agg_tune plan_tune(const agg_plan_s* p, int64_t bytes) {
   agg_tune t = p->tune;
-  if (p->tune_builtin) builtin_tune_for(p->kind, reads_link(p) ? AGG_SRC_ZEROCOPY : p->src, bytes, &t);
+  if (runs_builtin(p, bytes)) builtin_tune_for(p->kind, reads_link(p, bytes) ? AGG_SRC_ZEROCOPY : p->src, bytes, &t);
   return t;
 }
 
@@ -398,8 +404,8 @@ int plan_create(agg_plan_s* p) {
   if (p->src == AGG_SRC_PINNED_HOST) {
     agg_shape s;
     shape_of(p->dtype, p->max_n, &s);
-    p->depth = reads_link(p) ? kSpareDepth : p->tune.staging_depth;
-    p->stage_bytes = std::max<int64_t>(reads_link(p) ? kSpareChunk : p->tune.chunk_bytes, s.seg_bytes);
+    p->depth = p->tune_builtin ? kSpareDepth : p->tune.staging_depth;
+    p->stage_bytes = std::max<int64_t>(p->tune_builtin ? kSpareChunk : p->tune.chunk_bytes, s.seg_bytes);
     p->stage_bytes = std::min<int64_t>(p->stage_bytes, std::max<int64_t>(s.nseg, 1) * s.seg_bytes);
     for (int i = 0; i < p->depth; ++i) {
       RET_IF(alloc_device(reinterpret_cast<void**>(&p->stage[i]), (size_t)p->stage_bytes));
@@ -556,8 +562,9 @@ int agg_default_tune(int32_t dtype, int32_t op, int32_t prec, int64_t n, int32_t
   return AGG_OK;
 }
 
-int agg_plan(agg_plan_t* out, int32_t dtype, int32_t op, int32_t prec, int64_t max_n, int32_t src,
-             const agg_tune* tune) {
+namespace {
+int make_plan(agg_plan_t* out, int32_t dtype, int32_t op, int32_t prec, int64_t max_n, int32_t src, const agg_tune* tune,
+              bool use_cache) {
   if (!out) return AGG_E_INVALID;
   *out = nullptr;
   const int kind = kind_of(dtype, op, prec);
@@ -568,7 +575,7 @@ int agg_plan(agg_plan_t* out, int32_t dtype, int32_t op, int32_t prec, int64_t m
   if (tune) {
     t = *tune;
     if (!valid_tune(t)) return AGG_E_INVALID;
-  } else if (!tune_cache_lookup(kind, src, max_n * width_of(dtype), &t)) {
+  } else if (!use_cache || !tune_cache_lookup(kind, src, max_n * width_of(dtype), &t)) {
     builtin = true;
     builtin_tune_for(kind, src, max_n * width_of(dtype), &t);
   }
@@ -592,7 +599,19 @@ int agg_plan(agg_plan_t* out, int32_t dtype, int32_t op, int32_t prec, int64_t m
   *out = p;
   return AGG_OK;
 }
+}  // namespace
 
+int agg_plan(agg_plan_t* out, int32_t dtype, int32_t op, int32_t prec, int64_t max_n, int32_t src,
+             const agg_tune* tune) {
+  return make_plan(out, dtype, op, prec, max_n, src, tune, true);
+}
+}  // extern "C"
+
+int agg::plan_untuned(agg_plan_t* out, int32_t dtype, int32_t op, int32_t prec, int64_t max_n, int32_t src) {
+  return make_plan(out, dtype, op, prec, max_n, src, nullptr, false);
+}
+
+extern "C" {
 int agg_plan_info(agg_plan_t plan, int64_t n, agg_shape* shape, agg_tune* tune) {
   if (!plan || n < 0 || n > plan->max_n) return AGG_E_INVALID;
   if (shape) shape_of(plan->dtype, n, shape);
@@ -638,7 +657,7 @@ int agg_run(agg_plan_t p, const void* col, int64_t n, agg_result* out, void* str
   // copies to wait for: int32 SUM 256 MiB 4834 -> 4675 us, 4 MiB 121 -> 82,
   // float 1 MiB 66 -> 25.
   void* mapped = nullptr;
-  if (reads_link(p)) {
+  if (reads_link(p, bytes)) {
     if (hipHostGetDevicePointer(&mapped, const_cast<void*>(col), 0) != hipSuccess) {
       (void)hipGetLastError();
       mapped = nullptr;

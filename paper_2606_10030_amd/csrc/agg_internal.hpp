@@ -154,6 +154,9 @@ int64_t ceil_div(int64_t a, int64_t b);
 bool tune_is_valid(const agg_tune& t);
 bool tune_cache_lookup(int kind, int32_t src, int64_t bytes, agg_tune* out);
 void builtin_tune_for(int kind, int32_t src, int64_t bytes, agg_tune* out);
+bool tune_applies(int64_t tuned_bytes, int64_t bytes);  // a cached entry for one size is one for the other
+// A plan as agg_plan makes it without parameters where the cache has none.
+int plan_untuned(agg_plan_t* out, int32_t dtype, int32_t op, int32_t prec, int64_t max_n, int32_t src);
 
 // fused: the single-launch form (ScanArgs::done set)
 const void* scan_kernel_ptr(int kind, int unroll, bool nontemporal, bool fused = false);

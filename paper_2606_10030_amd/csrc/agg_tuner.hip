@@ -5,7 +5,8 @@
 // bit, so they are free for the tuner.  agg_autotune times a fixed set of
 // candidates on the caller's column with HIP events and keeps the fastest in
 // an in-memory cache keyed by (fold kind, source, size bucket); plans created
-// without explicit parameters look the cache up (agg_default_tune).  The
+// without explicit parameters look the cache up (agg_default_tune) for sizes
+// near the tuned one, and keep to the built-in table for others.  The
 // cache persists as a small JSON file keyed by gfx arch and CU count; a file
 // for another device, or one that does not parse, is ignored.
 #include <hip/hip_runtime.h>
@@ -36,7 +37,12 @@ struct Key {
 struct Entry {
   agg_tune tune;
   double gbs;
+  bool link = false;  // PINNED_HOST: reading the column over the link was faster than staging it
 };
+// An entry speaks for its own size bucket and the ones beside it: the best shapes
+// differ from size to size (int32 MIN of 48 MB takes 46 us in the shape that is
+// best at 4 GiB, 11.8 in its own), and the built-in table knows them.
+constexpr int kNearBuckets = 1;
 
 std::mutex g_tmu;
 std::map<Key, Entry> g_cache;
@@ -45,6 +51,11 @@ int bucket_of(int64_t bytes) {  // ceil(log2(bytes)), at least 10
   int b = 10;
   while (b < 62 && ((int64_t)1 << b) < bytes) ++b;
   return b;
+}
+
+bool same_tune(const agg_tune& a, const agg_tune& b) {
+  return a.waves_per_block == b.waves_per_block && a.blocks_per_cu == b.blocks_per_cu && a.unroll == b.unroll &&
+         a.nontemporal == b.nontemporal;
 }
 
 // Measured bests on MI355X.
@@ -160,14 +171,14 @@ std::vector<agg_tune> kernel_candidates(int kind, int32_t src, int64_t bytes) {
   agg_tune base;
   builtin_for(kind, src, bytes, &base);
   const int wb[][2] = {{1, 2}, {2, 1}, {4, 1}, {1, 3}, {2, 2}, {4, 2}, {8, 1}, {1, 4}};
-  if (src == AGG_SRC_ZEROCOPY) v.push_back(base);
+  v.push_back(base);  // the shape of an untuned plan, which is not always one of the others
   for (int u : {8, 16, 32})
     for (auto& p : wb) {
       agg_tune t = base;
       t.unroll = u;
       t.waves_per_block = p[0];
       t.blocks_per_cu = p[1];
-      v.push_back(t);
+      if (!same_tune(t, base)) v.push_back(t);
     }
   return v;
 }
@@ -187,9 +198,13 @@ bool tune_cache_lookup(int kind, int32_t src, int64_t bytes, agg_tune* out) {
       best = &kv.second;
     }
   }
-  if (!best) return false;
+  if (!best || best_d > kNearBuckets || best->link) return false;
   *out = best->tune;
   return true;
+}
+
+bool tune_applies(int64_t tuned_bytes, int64_t bytes) {
+  return std::abs(bucket_of(tuned_bytes) - bucket_of(bytes)) <= kNearBuckets;
 }
 
 void builtin_tune_for(int kind, int32_t src, int64_t bytes, agg_tune* out) { builtin_for(kind, src, bytes, out); }
@@ -258,12 +273,27 @@ int agg_autotune(int32_t dtype, int32_t op, int32_t prec, const void* col, int64
       }
     }
   }
+  // a page-locked column: staged, or read over the link as plans without
+  // parameters do
+  bool link = false;
+  if (rc == AGG_OK && best_ms > 0 && src == AGG_SRC_PINNED_HOST) {
+    agg_plan_t p = nullptr;
+    rc = plan_untuned(&p, dtype, op, prec, n, src);
+    if (rc == AGG_OK) {
+      const double ms = time_runs([&] { return agg_run(p, col, n, static_cast<agg_result*>(out), stream); }, stream, 1, 1);
+      agg_plan_destroy(p);
+      if (ms > 0 && ms < best_ms) {
+        best_ms = ms;
+        link = true;
+      }
+    }
+  }
   (void)hipFree(out);
   if (rc != AGG_OK) return rc;
   const double gbs = (double)bytes / (best_ms * 1e-3) / 1e9;
   {
     std::lock_guard<std::mutex> lk(g_tmu);
-    g_cache[Key{kind, src, bucket_of(bytes)}] = Entry{best_t, gbs};
+    g_cache[Key{kind, src, bucket_of(bytes)}] = Entry{best_t, gbs, link};
   }
   if (best) *best = best_t;
   if (best_gbs) *best_gbs = gbs;
@@ -290,10 +320,10 @@ int agg_tune_save(const char* path) {
     std::fprintf(f,
                  "  {\"kind\": %d, \"src\": %d, \"bucket\": %d, \"waves_per_block\": %d, \"blocks_per_cu\": %d, "
                  "\"unroll\": %d, \"nontemporal\": %d, \"chunk_bytes\": %lld, \"staging_depth\": %d, "
-                 "\"gbs\": %.1f}%s\n",
+                 "\"gbs\": %.1f, \"link\": %d}%s\n",
                  kv.first.kind, kv.first.src, kv.first.bucket, t.waves_per_block, t.blocks_per_cu, t.unroll,
                  t.nontemporal, (long long)t.chunk_bytes, t.staging_depth, kv.second.gbs,
-                 ++i < g_cache.size() ? "," : "");
+                 kv.second.link ? 1 : 0, ++i < g_cache.size() ? "," : "");
   }
   std::fprintf(f, "]}\n");
   const bool ok = std::fclose(f) == 0;
@@ -340,11 +370,13 @@ int agg_tune_load(const char* path) {
         !json_num(s, e, "chunk_bytes", &chunk) || !json_num(s, e, "staging_depth", &depth) ||
         !json_num(s, e, "gbs", &gbs))
       return AGG_E_INVALID;
+    double link = 0;  // absent in older files: staged
+    json_num(s, e, "link", &link);
     // every field an integer in its range before it is converted (NaN fails every comparison)
     auto whole = [](double v, double lo, double hi) { return v >= lo && v <= hi && v == std::floor(v); };
     if (!whole(kind, 0, K_NUM - 1) || !whole(src, AGG_SRC_DEVICE, AGG_SRC_ZEROCOPY) || !whole(bucket, 0, 64) ||
         !whole(w, 1, 16) || !whole(b, 1, 32) || !whole(u, 4, 32) || !whole(nt, 0, 1) ||
-        !whole(chunk, 1 << 20, (double)((int64_t)1 << 32)) || !whole(depth, 2, 4) || !(gbs >= 0.0 && gbs < 1e9))
+        !whole(chunk, 1 << 20, (double)((int64_t)1 << 32)) || !whole(depth, 2, 4) || !whole(link, 0, 1) || !(gbs >= 0.0 && gbs < 1e9))
       return AGG_E_INVALID;
     agg_tune t;
     t.waves_per_block = (int32_t)w;
@@ -355,7 +387,7 @@ int agg_tune_load(const char* path) {
     t.staging_depth = (int32_t)depth;
     t.reserved = 0;
     if (!tune_is_valid(t)) return AGG_E_INVALID;
-    loaded[Key{(int)kind, (int)src, (int)bucket}] = Entry{t, gbs};
+    loaded[Key{(int)kind, (int)src, (int)bucket}] = Entry{t, gbs, link != 0 && src == AGG_SRC_PINNED_HOST};
     pos = end;
   }
   const std::string dev = device_key();

@@ -9,6 +9,7 @@ pytestmark = pytest.mark.gpu
 def test_pinned_plan_reports_what_its_runs_take(dtype, op):
     import torch
     import paper_2606_10030_amd as agg
+    assert torch.cuda.is_available()
     agg.tune_clear()
     n = 1 << 26
     fields = ("waves_per_block", "blocks_per_cu", "unroll", "nontemporal")
