@@ -311,7 +311,8 @@ typedef struct agg_groupby_s* agg_groupby_t;
  * hash table (2 x max_groups slots rounded up to a power of two; float SUM /
  * AVG tables carry 9 fixed-point digits per slot); with more groups than a
  * workgroup's LDS table holds, also a staging copy of min(max_n, 2^28) rows
- * and a partition histogram.  max_n <= 2^36; float SUM / AVG plans take at most
+ * and a partition histogram; with fewer, and more than 2^18 rows, also room for
+ * one such table per 16384 rows, a CU's worth of them at most (up to 54 MB).  max_n <= 2^36; float SUM / AVG plans take at most
  * 2^31 items per run. */
 int agg_groupby_plan(agg_groupby_t* out, int32_t key_dtype, int32_t val_dtype, int32_t op, int64_t max_n,
                      int64_t max_groups);

@@ -2306,10 +2306,13 @@ int agg_groupby_plan(agg_groupby_t* out, int32_t key_dtype, int32_t val_dtype, i
   const int64_t b_dig = dig ? up(slots * 8 * kDigits) : 256, b_flags = up(slots * 4), b_state = 256;
   const int64_t b_hist = up(P * kMaxHistWg * 4), b_tot = up(P * 4 + 4), b_start = up(P * 4 + 4),
                 b_pk = up(crow * kw), b_pv = up(crow * vw);
-  // Regions for one table per CU and hash half, if a run can have enough
-  // workgroups to merge them: room for the groups (for a half of them, half and
-  // a quarter more; a table with more than that is flushed as usual).
-  const int wgs = bits || max_groups <= kFewGroups || max_n <= kMergeMinWg * kDirectRows ? 0 : device_cu(dev);
+  // Regions for one table per workgroup and hash half, if a run can have enough
+  // of them to merge: room for the groups (for a half of them, half and a quarter
+  // more; a table with more than that is flushed as usual).  A run has at most a
+  // workgroup per CU and per kDirectRows rows (10^6 rows of 2000 groups: 62 regions,
+  // 1.0 MB of COUNT, for 256 of them 4.2), and too few updates are never merged.
+  int64_t wgs = bits || max_groups <= kFewGroups ? 0 : std::min<int64_t>(device_cu(dev), ceil_div(max_n, kDirectRows));
+  if (wgs <= kMergeMinWg || wgs * max_groups < kMergeMinUpdates) wgs = 0;
   const int64_t dump_max = sub_bits ? max_groups / 2 + max_groups / 8 + 64 : max_groups + 1;
   const int64_t b_dump = up(wgs * (dump_region_of(g, key_dtype, dump_max) << sub_bits) * 4);
   const int64_t total = b_key + b_cnt + b_val + b_dig + b_flags + b_state + b_hist + b_tot + b_start +
@@ -2341,7 +2344,7 @@ int agg_groupby_plan(agg_groupby_t* out, int32_t key_dtype, int32_t val_dtype, i
   p->pt.pk = take(b_pk);
   p->pt.pv = vw ? take(b_pv) : nullptr;  // right after pk: staged (key, value) records span both
   p->dump = wgs ? reinterpret_cast<uint32_t*>(take(b_dump)) : nullptr;
-  p->dump_wgs = wgs;
+  p->dump_wgs = (int)wgs;
   p->dump_max = (int)dump_max;
   p->pt.bits = bits;
   p->pt.sub_bits = sub_bits;
