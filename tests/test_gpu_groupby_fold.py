@@ -49,7 +49,7 @@ def test_fold_tile_edges(agg, kdt, vdt, op):
     ("i32", 0, 1), ("i32", -5000, 1), ("i32", 7, 1 << 12), ("i32", 0, 75_025), ("i32", -2**31, 2**32 // 10_000),
     ("i64", 0, 1), ("i64", 10**12, 86_400), ("i64", 0, 1 << 32), ("i64", -2**63, (1 << 32) + 1), ("i64", 5, 1 << 50)])
 def test_regular_key_sets(agg, kdt, first, stride):
-    """Arithmetic key sequences (dense codes, powers of two, a Fibonacci stride,
+    """Arithmetic key sequences (dense codes, powers of two, other strides,
     keys that differ in their high words only) through the direct, two-pass,
     partitioned and sub-partition paths."""
     n = 100_003
@@ -81,7 +81,7 @@ def window_values(kind, n, r):
         "zeros": lambda: np.where(r.random(n) < 0.5, 0.0, -0.0),
         "mostly zeros": lambda: np.where(r.random(n) < 0.9, 0.0, r.standard_normal(n)),
         "non-finite": lambda: np.where(r.random(n) < 0.1, r.choice([np.nan, np.inf, -np.inf], size=n), r.standard_normal(n)),
-        # the sample of 4096 rows spread over the column misses these
+        # most of these are not among the 1024 rows that place the windows
         "rare outliers": lambda: np.where(np.arange(n) % 9973 == 17, r.choice([1e38, -1e-38, 1e-44], size=n), r.random(n)),
         "ascending": lambda: np.sort(np.abs(spread(-60, 60))),
     }[kind]()
@@ -107,8 +107,8 @@ def test_float_windows(agg, kind):
                                         ("i32", "i64", "sum"), ("i64", "i32", "sum"), ("i64", "i64", "sum")])
 def test_scatter_carries_rows_between_tiles(agg, kdt, vdt, op):
     """Partitioned plans whose workgroups scatter several tiles each (and a
-    partial last one), with partition counts on both sides of every tile form
-    (32 to 2048), uniform and skewed keys (a partition with nearly all rows,
+    partial last one), with partition counts on both sides of the tile forms
+    (64 to 2048; keys only to 1024), uniform and skewed keys (a partition with nearly all rows,
     and empty ones), against torch's whole-number sums per key."""
     import torch
     n, card = 35_000_011, 19_997
