@@ -2262,7 +2262,7 @@ int agg_groupby_plan(agg_groupby_t* out, int32_t key_dtype, int32_t val_dtype, i
   while (cap < 2 * max_groups) cap <<= 1;
   const int64_t slots = cap + 1;
   const bool dig = g == G_SUM_F32;
-  // LDS tables are filled at most half (with double hashing a half-full
+  // LDS tables are filled at most half (every probe hashed anew, a half-full
   // table still probes fast; measured, linear probing slowed sharply past a
   // quarter): the direct path up to half of its table, or in two passes over
   // the rows up to a whole table's worth, partitions sized for half of
