@@ -59,6 +59,11 @@ constexpr int kMaxPartBits = 14;      // at most 16384 (sub-)partitions
 // / 128 / 256 partitions, 50 000 groups: float SUM of 1.7M rows 111 / 83 / 69 / 72
 // us, int32 SUM 75 / 62 / 57 / 63, of 6M rows 106 / 90 / 83 / 83, of 60M rows
 // 420 / 411 / 422 / 439; 4096 groups, float SUM of 30M rows 64 / 128: 235 / 256.
+// From 2^21 rows on, though, partitions of fewer than about 64 keys only shorten the
+// runs, so 32 are the least there.  32 / 64 / 128, float SUM by random int32 keys: 2500
+// groups, 3M rows 73 / 79 / 81 us, 6M 90 / 100 / 106, 12M 124 / 134 / 140; 8000 groups,
+// 3M 80 / 75 / 80, 12M 129 / 124 / 129; 12 000 groups, 6M 99 / 94 / 92; 4000 dense keys
+// of 1M rows 55 / 57 / 46.
 // With 2^17 groups and more, at least 256: then most partitions are one
 // workgroup's, and their groups leave from LDS (emit_all).  Partitions of few
 // keys are too uneven for that, and 16-byte rows pay more for short runs.  128
@@ -66,7 +71,8 @@ constexpr int kMaxPartBits = 14;      // at most 16384 (sub-)partitions
 // 174 / 115, of 2^28 rows 1881 / 1812, int64 SUM 3075 / 3261; 90 000 groups:
 // int32 SUM of 6M rows 95 / 89, of 2^28 rows 1575 / 1716; 10^6 groups, COUNT of
 // 60M rows 474 / 321.
-constexpr int kMinPartBits = 7, kMinPartBitsLarge = 6, kMinPartBitsMany = 8;
+constexpr int kMinPartBits = 7, kMinPartBitsLarge = 6, kMinPartBitsMany = 8, kLeastPartBits = 5;
+constexpr int64_t kFewKeysRows = (int64_t)1 << 21, kFewKeys = 128;  // at most, of a partition
 constexpr int64_t kManyGroups = (int64_t)1 << 17;
 constexpr int64_t kLargeRows = (int64_t)1 << 24;
 // Rows are partitioned in chunks of up to 2^28: every chunk ends with each
@@ -2289,9 +2295,10 @@ int agg_groupby_plan(agg_groupby_t* out, int32_t key_dtype, int32_t val_dtype, i
     bits = bits_for(half_table);
     const bool large = max_n >= kLargeRows;
     const bool wide = width_of(key_dtype) + (op == AGG_COUNT ? 0 : width_of(val_dtype)) >= 16;
+    const int few_keys = max_n < kFewKeysRows ? kMinPartBits : std::max(kLeastPartBits, bits_for(kFewKeys));
     bits = std::max(bits, max_groups >= kManyGroups && !(large && wide) ? kMinPartBitsMany
                           : large                                      ? kMinPartBitsLarge
-                                                                       : kMinPartBits);
+                                                                       : std::min(few_keys, kMinPartBits));
   }
   // The scatter takes at most 2^kTileMaxBits partitions (its per-partition
   // counters live in LDS, and more would shorten the coalesced runs); past

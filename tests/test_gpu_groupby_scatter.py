@@ -1,9 +1,12 @@
 """GPU: the scatter of keys only (COUNT) into more partitions than carry rows
 between tiles (1024 of int32 keys, 2048), several tiles a workgroup, against
-torch's whole-number counts per key."""
+torch's whole-number counts per key; and the fewest partitions, against the
+oracle."""
+import numpy as np
 import pytest
 
-from test_gpu_groupby import agg  # noqa: F401
+import oracle
+from test_gpu_groupby import agg, compare, make_vals  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -30,3 +33,24 @@ def test_key_only_tiles(agg, kdt, declared):
             assert torch.equal(got[:, 0], seen), ctx
             assert torch.equal(got[:, 3], count[seen]) and torch.equal(got[:, 1], count[seen]), ctx
     g.close()
+
+
+@pytest.mark.parametrize("groups", [2049, 4096, 4097, 8193, 16_385])
+@pytest.mark.parametrize("kdt,vdt,op", [("i32", "f32", "sum"), ("i64", "f32", "avg"), ("i64", "i64", "sum"),
+                                        ("i32", "i32", "count")])
+def test_few_partitions(agg, kdt, vdt, op, groups):
+    """Plans of 2^21 rows and one fewer: 32, 64 and 128 partitions (and the direct
+    path where the table holds the groups)."""
+    import torch
+    low = np.iinfo(np.int32 if kdt == "i32" else np.int64).min
+    r = np.random.default_rng(groups)
+    pool = np.unique(r.integers(low, -(low + 1), size=groups, dtype=np.int64))
+    pool[0] = low
+    for max_n in ((1 << 21) - 1, 1 << 21):
+        g = agg.GroupBy(kdt, vdt, op, max_n=max_n, max_groups=groups)
+        for n in (1, 5000, 400_003):
+            keys = pool[r.integers(0, pool.size, size=n)].astype(np.int32 if kdt == "i32" else np.int64)
+            vals = make_vals(n, vdt, seed=n)
+            compare(g.run(torch.from_numpy(keys).cuda(), torch.from_numpy(vals).cuda()), oracle.groupby(keys, vals, op),
+                    f"{kdt}/{vdt} {op} max_n={max_n} groups={groups} n={n}")
+        g.close()
