@@ -807,12 +807,20 @@ int agg_run_filtered(agg_plan_t p, const void* col, int64_t n, const agg_filter*
     // 4 waves everywhere: float SUM WHERE int32, 6e6 items 28.4 -> 24.8 us,
     // 3e7 62.8 -> 52.1, 6e7 102.0 -> 87.1, 2.5e8 341 -> 308; int64 SUM WHERE
     // int64, 6e7 160 -> 147; int32 MAX WHERE int64, 6e6 20.9 -> 17.7.
+    // From 257 segments on, one launch's 8 waves leave CUs without a workgroup, which
+    // only the compensated sum's arithmetic outweighs (2.5e6 items WHERE int32: 17.9
+    // us, 19.6 with 4 waves; int32 SUM 10.1 and 9.0, 3.2e6 items 10.4 and 9.5) up to
+    // about 640; that pair takes 2 workgroups of 2 (int32 SUM WHERE int64, 2.5e6: 15.8
+    // -> 12.0, 4.1e6 17.0 -> 13.1), its compensated sum 4 waves (21.9 -> 20.4, 1e6 items
+    // 18.1 -> 15.5).
     agg_tune t = p->tune;
     if (!p->tune_given) {
       const bool pair48 = p->width == 4 && fw == 8;
-      if (s.nseg <= kFuseMaxPartials) {  // one launch: at most one workgroup per CU
-        t.waves_per_block = s.nseg > 256 ? 8 : pair48 ? 2 : 4;
-        t.blocks_per_cu = 1;
+      if (s.nseg <= kFuseMaxPartials) {  // one launch where that is at most one workgroup per CU
+        const bool heavy = p->kind == K_SUM_F32_NEU;
+        if (pair48) t.waves_per_block = heavy ? 4 : 2;
+        else t.waves_per_block = s.nseg > (heavy ? 256 : 640) ? 8 : 4;
+        t.blocks_per_cu = pair48 && !heavy && s.nseg > 256 ? 2 : 1;
       } else {
         t.waves_per_block = 2;
         t.blocks_per_cu = pair48 ? 2 : 4;
