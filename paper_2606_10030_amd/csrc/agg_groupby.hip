@@ -176,8 +176,12 @@ constexpr int mid_windows_of(int kd) { return kd == AGG_I32 ? 7 : 6; }
 constexpr int kFewWindows = 9;
 // Rows outside the windows go to the global table one by one.  When a table of
 // kWindows has met this many (the sample was not of the column's kind), it is
-// flushed, and the workgroup's other rows go to tables of all windows.
-constexpr uint32_t kFarRows = 256;
+// flushed, and the workgroup's other rows go to a table whose windows take the
+// exponents of those rows in; if that is one of kWindows again and meets as many,
+// to tables of all windows.  (2^28 rows of N(0, 1), 0.3% of them times 1e20, against
+// staying: 16 groups 912 -> 335 us, 300 groups 695 -> 382; half of them from the middle
+// on 695 -> 331 and 682 -> 384.)
+constexpr uint32_t kFarRows = 256, kFewFarRows = 32;  // (few groups: the rows meet on the same slots, and a flush is cheap)
 constexpr int64_t kTwoPassFloatRows = (int64_t)1 << 27;
 // A float sum's tables: 2^lg slots of nw windows, which cover `span` exponents from
 // `first` on in the first of `passes` passes over the rows, the next ones in the
@@ -188,6 +192,8 @@ struct FloatWindows {
   int nw = kWindows;
   int lg = 0;
   int sub_bits = 0;
+  int lo = 255, hi = 0;  // the exponents it was made for
+  int moves = 0;         // times it was made anew
   __device__ __forceinline__ uint32_t base(int pass) const { return (uint32_t)(first + pass * nw * kWinOctaves); }
   // exponents of the pass (255 marks non-finite floats and is never one of them)
   __device__ __forceinline__ uint32_t span(int pass) const {
@@ -874,7 +880,7 @@ struct LdsTable {
   uint32_t flags[kDig ? kMaxL / 8 + 1 : 1];  // float sum: non-finite rows seen, four bits a slot
   uint16_t list[NT / 64][128];             // per wave: slots to flush
   uint32_t spilled;                        // a row went to the global table
-  uint32_t far_rows;                       // float sum: rows outside the windows
+  uint32_t far_rows, far_lo, far_hi;       // float sum: rows outside the windows, and their exponents
   uint32_t emit_base[2];                   // emit_all: the output range's first group
   uint32_t wave_groups[NT / 64];           // emit_all: groups per wave
   uint32_t hot_sh;                         // the hot slot + 1; 0: there is none
@@ -902,6 +908,8 @@ struct LdsTable {
       hot_sh = 0;
       spilled = 0;
       far_rows = 0;
+      far_lo = 255;
+      far_hi = 0;
     }
   }
 
@@ -1276,8 +1284,10 @@ struct LdsTable {
         } else {
           spilled = 1;
           if constexpr (kLeaves)
-            if (!in) {
+            if (!in && fb << 1 >= 1u << 24) {  // (a subnormal is outside all windows)
               at_add<true>(&far_rows, 1u);
+              __hip_atomic_fetch_min((lds_u32*)&far_lo, (fb >> 23) & 0xFFu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+              __hip_atomic_fetch_max((lds_u32*)&far_hi, (fb >> 23) & 0xFFu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
               far_row = true;
             }
           const Table t = (kFlex && REP == 1 ? a_ : late_args()).t;
@@ -1320,9 +1330,10 @@ struct LdsTable {
     return last;
   }
   __device__ __forceinline__ bool far_count() const {
-    return __hip_atomic_load((const lds_u32*)&far_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > kFarRows;
+    return __hip_atomic_load((const lds_u32*)&far_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >
+           (REP > 1 ? kFewFarRows : kFarRows);
   }
-  // Rows of the workgroup are left for a table of all windows (between barriers).
+  // Rows of the workgroup are left for another table (between barriers).
   // In a scalar register: all that depends on the windows is else kept per lane.
   __device__ __forceinline__ bool left(const FloatWindows& z) const {
     return kLeaves && z.single() && __builtin_amdgcn_readfirstlane((int)far_count()) != 0;
@@ -1637,7 +1648,7 @@ constexpr int kFewSlots = 256;
 // rows and groups, 60 exponents 236 us, by hash 276; with fewer groups the flushes
 // cost more than the test: 10^6 rows, 2000 groups 118 us by exponent, 93 by hash).
 template <int KD, bool FEW, bool MANY>
-__device__ __forceinline__ FloatWindows place_windows(int emin, int emax, int64_t groups) {
+__device__ __forceinline__ FloatWindows place_windows(int emin, int emax, int64_t groups, int moves = 0) {
   const int n = emax - emin + 1;
   FloatWindows f;
   const int least = (n + kWinOctaves - 1) / kWinOctaves, mid = mid_windows_of(KD);
@@ -1655,7 +1666,17 @@ __device__ __forceinline__ FloatWindows place_windows(int emin, int emax, int64_
   const int span = f.nw * kWinOctaves;
   f.passes = (n + span - 1) / span;
   f.first = std::max(1, emax + std::min((f.passes * span - n) / 2, 8) - f.passes * span + 1);
+  f.lo = emin;
+  f.hi = emax;
+  f.moves = moves;
   return f;
+}
+// The tables for the rows that a table of `fw` left.  (Scalars: see left().)
+template <int KD, bool FEW, bool MANY, class Tab>
+__device__ __forceinline__ FloatWindows move_windows(const Tab& tab, const FloatWindows& fw, int64_t groups) {
+  const int lo = __builtin_amdgcn_readfirstlane((int)tab.far_lo), hi = __builtin_amdgcn_readfirstlane((int)tab.far_hi);
+  return fw.moves ? place_windows<KD, FEW, MANY>(1, 254, groups, fw.moves + 1)
+                  : place_windows<KD, FEW, MANY>(std::min(fw.lo, lo), std::max(fw.hi, hi), groups, 1);
 }
 
 // Where a launch's float-sum windows go, from one row of each of blockDim.x equal
@@ -1691,8 +1712,10 @@ __device__ __forceinline__ FloatWindows sample_windows(const uint32_t* words, in
   // every wave has the same two numbers: in scalar registers from here on
   emin = __builtin_amdgcn_readfirstlane(emin);
   emax = __builtin_amdgcn_readfirstlane(emax);
-  if (emin > emax) emin = emax = 127;
-  return place_windows<KD, FEW, MANY>(emin, emax, groups);
+  FloatWindows f = emin > emax ? place_windows<KD, FEW, MANY>(127, 127, groups) : place_windows<KD, FEW, MANY>(emin, emax, groups);
+  f.lo = emin;  // none sampled: as such
+  f.hi = emax;
+  return f;
 }
 
 // An aggregation kernel's tables, in the same LDS: one of full size, and for a
@@ -1880,18 +1903,18 @@ gb_aggregate_kernel(Args a) {
       const bool left = tab.left(fw);
       const Args& b = late_args();
       if constexpr (!FEW)
-        if (b.dumps && !left && fw.single())  // its region; its rows may be in the global table as well (spilled)
+        if (b.dumps && !left && fw.single() && !fw.moves)  // its region; its rows may be in the global table as well (spilled)
           dumped = tab.dump(b.dump + ((int64_t)blockIdx.x * (sub_mask + 1) + sub) * dump_region_of(G, KD, b.dump_max),
                             b.dump_max, fw);
       global = !dumped || tab.spilled;
       if (!dumped) tab.flush(b.t, fw.base(pass), gridDim.x <= 64, fw);
-      __syncthreads();
       if constexpr (G == G_SUM_F32)
-        if (left) {  // the rows that are left, in tables of all windows
-          fw = place_windows<KD, FEW, SUB>(1, 254, a.max_groups >> a.pt.sub_bits);
+        if (left) {  // (before the barrier: the next table is cleared after it)
+          fw = move_windows<KD, FEW, SUB>(tab, fw, a.max_groups >> a.pt.sub_bits);
           from = next;
           pass = -1;
         }
+      __syncthreads();
     }
     if constexpr (!FEW) {
       const Args& b = late_args();
@@ -1969,6 +1992,7 @@ __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a)
     const bool whole = a.whole && r == (int64_t)a.pt.start[p] && seg_end == (int64_t)a.pt.start[p + 1];
     for (uint32_t sub = 0; sub <= sub_mask; ++sub) {
       int64_t from = r;
+      bool flushed = false;  // rows of these keys are in the global table already
       for (int pass = 0; pass < (fw.narrow() ? fw.passes : 0); ++pass) {
         tab.clear((uint32_t)(a.pt.bits + a.pt.sub_bits), fw);
         __syncthreads();
@@ -1978,15 +2002,16 @@ __global__ void __launch_bounds__(kPartThreads) gb_aggregate_part_kernel(Args a)
         __syncthreads();
         const bool left = tab.left(fw);
         tab.merge_hot(fw);
-        if (whole && fw.single() && tab.spilled == 0) tab.emit_all(late_args(), fw.base(0), fw);
+        if (whole && fw.single() && tab.spilled == 0 && !flushed) tab.emit_all(late_args(), fw.base(0), fw);
         else tab.flush(late_args().t, fw.base(pass), true, fw);
-        __syncthreads();
         if constexpr (G == G_SUM_F32)
-          if (left) {  // the rows that are left, in tables of all windows
-            fw = place_windows<KD, false, true>(1, 254, groups);
+          if (left) {  // (before the barrier: the next table is cleared after it)
+            fw = move_windows<KD, false, true>(tab, fw, groups);
+            flushed = true;
             from = next;
             pass = -1;
           }
+        __syncthreads();
       }
       if constexpr (G == G_SUM_F32)
         if (!fw.narrow())

@@ -57,6 +57,18 @@ def test_many_exponents(agg, kdt, groups, max_n):
             run(keys, vals, f"rows near {far} that the sample misses")
             vals[:n // 2] = spread(r, n // 2, -3, 3)
             run(keys, vals, f"rows near {far} in the second half only")
+        # the sample sees zeros only: windows at 1, then where the rows are, then all
+        vals = spread(r, n, 60, 70)
+        vals[sampled_rows(n)] = 0.0
+        run(keys, vals, "the sample sees zeros only")
+        vals[n // 3:] *= np.float32(2.0**-130)
+        vals[sampled_rows(n)] = 0.0
+        run(keys, vals, "and the rows change on the way")
+        vals[2 * n // 3:] = spread(r, n - 2 * n // 3, 100, 120)
+        run(keys, vals, "twice")
+        vals[::3] = np.float32(3e-40)
+        vals[sampled_rows(n)] = 1.0
+        run(keys, vals, "with subnormal rows")
         run(keys, spread(r, n, 0, 3), "few exponents")
     g.close()
 
